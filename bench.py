@@ -144,21 +144,26 @@ def run_nve(P, model, x0, v0, box, steps, warmup, precision, mode=0, keep=False,
     return out
 
 
-def kernel_work(N, sum_nei, sum_seg, rs, d_in_emb):
+def kernel_work(N, sum_nei, sum_seg, rs):
     """Algorithmic work per launch of each kernel (FMA = 2 FLOP) and its
     bound: the fitting GEMMs count the model's 240 columns (not the padded
     256) and one pass of K (not the BF16 hi/lo split's three); the embedding
     kernels count the interval-moment form they execute: forward 24 moments
-    per neighbor, 24 per (segment, column), and D 16 x 128 x 4 where it forms
-    D (d_in_emb: the mixed mode; in FP32 and FP64 the first fitting layer
-    forms D from T, VALU work beside its MFMA product that is not counted);
-    backward dE/dT 2 x 16 x 128 x 4, 24 per (segment, column), 40 per
-    neighbor."""
+    per neighbor and 24 per (segment, column); backward 24 per (segment,
+    column) and 40 per neighbor.  (D and dE/dT, 3 x 16 x 128 x 4 per atom, are
+    VALU work of the fitting net's kernels that is not counted.)  The FP32
+    first layer runs as six BF16 products: they are what its row counts,
+    against the BF16 peak."""
     fit_in = N * 2.0 * 240 * 2048          # 2048 -> 240 (and its transpose)
     fit_hid = N * 2.0 * 240 * 240          # 240 -> 240
     return {
-        "emb_fwd": (2.0 * (24 * sum_nei + 24 * 128 * sum_seg + (8192 * N if d_in_emb else 0)), "alu"),
-        "emb_bwd": (2.0 * (16384 * N + 24 * 128 * sum_seg + 40 * sum_nei), "alu"),
+        "emb_fwd": (2.0 * (24 * sum_nei + 24 * 128 * sum_seg), "alu"),
+        "emb_bwd": (2.0 * (24 * 128 * sum_seg + 40 * sum_nei), "alu"),
+        # the compressed step's net: first layer, the four 240 -> 240 products, input gradient;
+        # fit_fwd: the first two in one timer (mixed)
+        "fit_in": (fit_in, "mfma") if rs == 8 else (6 * fit_in, "mfma", "bf16"),
+        "fit_mid": (4 * fit_hid, "mfma"), "fit_out": (fit_in, "mfma"), "fit_fwd": (fit_in + 4 * fit_hid, "mfma"),
+        # the other modes' net
         "fit_fwd1": (fit_in, "mfma"), "fit_bwd1": (fit_in, "mfma"),
         "fit_fwd2": (fit_hid, "mfma"), "fit_fwd3": (fit_hid, "mfma"),
         "fit_bwd3": (fit_hid, "mfma"), "fit_bwd2": (fit_hid, "mfma"),
@@ -179,11 +184,11 @@ def roofline(res, steps, work, dt_alu, dt_mfma, counter_tag):
         avg = tot_ms / max(cnt, 1)
         row = dict(avg_ms=round(avg, 4), launches_per_step=round(cnt / steps, 3))
         if name in work:
-            w, bound = work[name]
+            w, bound, own = (*work[name], None)[:3]
             if bound == "hbm":
                 ach, peak, unit = w / (avg * 1e-3) / 1e9, HBM_PEAK_GBS, "GB/s"
             else:
-                dt = dt_alu if bound == "alu" else dt_mfma
+                dt = own or (dt_alu if bound == "alu" else dt_mfma)
                 ach, peak, unit = w / (avg * 1e-3) / 1e12, PEAK[(bound, dt)], "TFLOP/s"
             row.update(bound=bound, achieved=round(ach, 3), peak=peak, unit=unit, frac=round(ach / peak, 4))
             if bound == "alu" and dt_alu == "f32":
@@ -270,7 +275,7 @@ def main():
     summary = {}
     for name, prec, dt_alu, dt_mfma, rs in legs:
         r = runs[name]
-        roof, per = roofline(r, K, kernel_work(N, sum_nei, sum_seg, rs, name == "mixed_bf16"), dt_alu, dt_mfma,
+        roof, per = roofline(r, K, kernel_work(N, sum_nei, sum_seg, rs), dt_alu, dt_mfma,
                              {"fp64": "f64", "fp32": "f32", "mixed_bf16": "bf16"}[name])
         th = r["thermo"]
         etot = th[:, 0] + th[:, 1]

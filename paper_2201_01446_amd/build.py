@@ -28,7 +28,8 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # accumulation registers the compiler copied the FP64 accumulators out and
 # back on every K stage); the other MFMA kernel, the fused fitting tail,
 # gets VGPR results without it
-FILE_FLAGS = {"gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+FILE_FLAGS = {"gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "fitnet.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "fitsplit.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src):

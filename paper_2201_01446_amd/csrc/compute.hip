@@ -88,6 +88,64 @@ WS carve(void *base, int np, int precision, int sel)
     return w;
 }
 
+// The compressed step's fitting net from T to dE/dT: fitnet.hip (FP64; FP32
+// but for its first layer) and fitsplit.hip (FP32's first layer, mixed).  z and
+// the parts of dE/dT that sum over all columns take dD's place, dz1 that of D.
+template <typename TA, typename TR>
+struct FitNet {
+    const FitWeights &fw;
+    const TR *fb;
+    const WS &w;
+    FitRows fr;
+    int n, nt;   // atoms, tiles of 16 columns of the net's width
+    const TR *tab;
+    static constexpr bool mixed = !std::is_same<TA, TR>::value, f64 = std::is_same<TR, double>::value;
+
+    FitNet(const ComputeArgs &a, const WS &ws, const FitWeights &weights, const TR *vectors)
+        : fw(weights), fb(vectors), w(ws), n(a.natoms), nt(div_up(a.m->f1, 16))
+    {
+        const dp_nlist *nl = a.nl;
+        if (nl->ntypes > 1) {
+            fr.ntr = nl->ntypes;
+            for (int t = 0; t <= kMaxTypes; t++) fr.trow[t] = nl->trow[t];
+            fr.ratom = nl->ratom;
+        }
+        fr.nlive = n;
+        for (int t = 0; t < kMaxTypes; t++) fr.b4[t] = a.m->b4[t];
+        const long ks = div_up(nt, 2);
+        fr.w_in = f64 ? (long)kM * nt * 256 : mixed ? kM * ks * 2 * 64 : kM * ks * 3 * 64;
+        fr.w_mid = mixed ? 16 * ks * ks * 64 : 4L * nt * nt * 256;
+        fr.w_out = mixed ? kM * ks * 2 * 64 : (long)kM * nt * 256;
+        tab = !a.m->tanh_on ? nullptr : (const TR *)(f64 ? (const void *)a.m->tanh_tab64 : (const void *)a.m->tanh_tab);
+    }
+    // E_i, and dz1 for a backward that follows
+    void forward(hipStream_t st) const
+    {
+        if constexpr (mixed) {
+            DP_TIMED("fit_fwd", st, launch_mix_fwd(fr, nt, (const float *)w.T, fw, fb, tab, (float *)w.dDr, w.e_atom, w.D, st));
+        } else {
+            int zt = nt, parts;
+            if constexpr (f64) {
+                parts = fit_in_parts(fr);
+                DP_TIMED("fit_in", st, launch_fit_in(fr, nt, (const double *)w.T, fw.in, (double *)w.dDr, st));
+            } else {
+                zt = 2 * div_up(nt, 2);
+                parts = split_in_parts(fr);
+                DP_TIMED("fit_in", st, launch_split_in(fr, nt, (const float *)w.T, fw.in, (float *)w.dDr, st));
+            }
+            DP_TIMED("fit_mid", st, launch_fit_mid<TR>(fr, nt, zt, parts, (const TR *)w.dDr, fw.mid, fb, tab, w.e_atom, (TR *)w.D, st));
+        }
+    }
+    void backward(hipStream_t st) const
+    {
+        if constexpr (mixed)
+            DP_TIMED("fit_out", st, launch_mix_out(fr, nt, n, w.D, (const float *)w.T, fw.out, (float *)w.dT, (float *)w.dDr, st));
+        else
+            DP_TIMED("fit_out", st, launch_fit_out<TR>(fr, nt, n, (const TR *)w.D, (const TR *)w.T, fw.out, (TR *)w.dT, (TR *)w.dDr, st));
+    }
+    int dT_parts() const { return mixed ? mix_out_parts(fr) : fit_out_parts(fr); }
+};
+
 template <typename TA, typename TR, bool PLAIN>
 dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw, const TR *fb,
                 hipStream_t st)
@@ -125,15 +183,13 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
     }
     for (int t = 0; t < kMaxTypes; t++) rt.b4[t] = m->b4[t];
     bool fwd = a.phase != 2, bwd = a.need_forces && a.phase != 1;
-    // FP64 / FP32: every forward runs the fitting net's 256-wide layers, the
-    // energy and their input gradients as one fused kernel (so a backward
-    // that follows, in this call or a later one, starts at dz1); BF16 runs
-    // them as separate GEMMs
+    // the other modes' FP64 / FP32 forward runs the fitting net's 256-wide
+    // layers, the energy and their input gradients as one fused kernel (so a
+    // backward that follows, in this call or a later one, starts at dz1);
+    // BF16 runs them as separate GEMMs
     constexpr bool tail = std::is_same<TA, TR>::value;
-    // FP32 / FP64 compressed forward: the first fitting layer forms D = T<^T T
-    // from T as it stages its operand, and the embedding kernel writes no D
-    // (unless the caller asks for D)
-    const bool dfuse = tail && !PLAIN && a.mode == DP_COMPRESSED && !a.D_out;
+    const bool net = !PLAIN && a.mode == DP_COMPRESSED;
+    const FitNet<TA, TR> fn(a, w, fw, fb);
     // decides the early end of the candidate scans, and flags moves beyond the list's reach
     launch_displacement(nl, n, a.x, nl->rc_build - m->cfg.rcut, st);
     if (fwd) {
@@ -141,7 +197,7 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
             bool tab = a.mode == DP_TAB_UNFUSED;
             if ((s = plain_forward<TR, TA>(m, a.nl, n, a.x, w.T, w.D, a.nnei_out, st, tab)) != DP_OK) return s;
         } else if (a.mode == DP_COMPRESSED) {
-            DP_TIMED("emb_fwd", st, launch_emb_fwd(m, a.nl, n, a.x, a.precision, w.T, dfuse ? nullptr : w.D, w.rec, w.rcnt, a.nnei_out, a.nseg_out, st));
+            DP_TIMED("emb_fwd", st, launch_emb_fwd(m, a.nl, n, a.x, a.precision, w.T, a.D_out ? w.D : nullptr, w.rec, w.rcnt, a.nnei_out, a.nseg_out, st));
             if ((s = step_check("emb_fwd", st)) != DP_OK) return s;
         } else {
             bool pad = a.mode == DP_FUSED_PADDED;
@@ -154,6 +210,11 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
             else launch_to_double<TR>((long)n * 4 * kM, (const TR *)w.T, a.T_out, st);
         }
         if (a.D_out) launch_op_to_double<TA>(n, kDdim, (const TA *)w.D, typed ? nl->row : nullptr, a.D_out, st);
+    }
+    if (fwd && net) {
+        fn.forward(st);
+        if ((s = step_check("fitting_forward", st)) != DP_OK) return s;
+    } else if (fwd) {
         // the fitting net's tanh: native, or the table (in the epilogue's precision) when enabled
         const float *ttab = m->tanh_on ? m->tanh_tab : nullptr;
         const double *ttab64 = m->tanh_on ? m->tanh_tab64 : nullptr;
@@ -166,15 +227,7 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
         e.tanh_tab = ttab;
         e.tanh_tab64 = ttab64;
         e = grouped(e, kFitPad, ks * kDdim);
-        if (dfuse) {
-            e.dt_T = w.T;
-            e.dt_ratom = typed ? nl->ratom : nullptr;
-            e.dt_nlive = n;
-            if constexpr (std::is_same<TA, TR>::value)
-                DP_TIMED("fit_fwd1", st, launch_gemm_dt<TA, TR>(mr, kFitPad, (const TA *)fw.V1tp, e, st));
-        } else {
-            DP_TIMED("fit_fwd1", st, launch_gemm<TA, TR>(EPI_T1, mr, kFitPad, ks * kDdim, (const TA *)w.D, (const TA *)fw.V1t, e, st));
-        }
+        DP_TIMED("fit_fwd1", st, launch_gemm<TA, TR>(EPI_T1, mr, kFitPad, ks * kDdim, (const TA *)w.D, (const TA *)fw.V1t, e, st));
         if (!tail) {
             e = Epi{c2, w.y1r, nullptr, nullptr, w.y2r, y2op, w.t2r};
             e.tanh_tab = ttab;
@@ -188,7 +241,7 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
             DP_TIMED("fit_fwd3", st, launch_gemm<TA, TR>(EPI_T3, mr, kFitPad, ks * kFitPad, y2in, (const TA *)fw.V3t, e, st));
         }
     }
-    if (tail && fwd) {
+    if (!net && tail && fwd) {
         // y1 in; E_i and dz1 out
         TailLaunch tl;
         if (typed) {
@@ -204,27 +257,31 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
         if constexpr (std::is_same<TA, TR>::value)
             DP_TIMED("fit_tail", st, launch_fit_tail<TA>(mr, (const TA *)w.y1r, fw, fb, tl, w.e_atom, (TA *)w.dz1o, (TA *)w.t2r, (TA *)w.dy2r, st));
         if ((s = step_check("fitting_tail", st)) != DP_OK) return s;
-    } else if (!tail) {
+    } else if (!net && !tail) {
         // E_i always (also from kept activations); dz3 = w4 (1 - t3^2) when the backward follows
         launch_energy<TA, TR>(typed ? mr : n, (const TR *)w.y2r, (const TR *)w.t3r, w4, rt, w.e_atom,
                               bwd ? (TA *)w.dz3o : nullptr, st);
         if ((s = step_check("fitting_forward", st)) != DP_OK) return s;
     }
     if (bwd) {
-        if (!tail) {
-            e = grouped(Epi{nullptr, nullptr, w4, w.t2r, w.dy2r, w.dz2o, nullptr}, kFitPad, ks * kFitPad);
-            DP_TIMED("fit_bwd3", st, launch_gemm<TA, TR>(EPI_BWD, mr, kFitPad, ks * kFitPad, (const TA *)w.dz3o, (const TA *)fw.V3, e, st));
-            e = grouped(Epi{nullptr, w.dy2r, nullptr, w.y1r, nullptr, w.dz1o, nullptr}, kFitPad, ks * kFitPad);
-            DP_TIMED("fit_bwd2", st, launch_gemm<TA, TR>(EPI_BWD, mr, kFitPad, ks * kFitPad, (const TA *)w.dz2o, (const TA *)fw.V2, e, st));
+        if (net) {
+            fn.backward(st);
+        } else {
+            if (!tail) {
+                e = grouped(Epi{nullptr, nullptr, w4, w.t2r, w.dy2r, w.dz2o, nullptr}, kFitPad, ks * kFitPad);
+                DP_TIMED("fit_bwd3", st, launch_gemm<TA, TR>(EPI_BWD, mr, kFitPad, ks * kFitPad, (const TA *)w.dz3o, (const TA *)fw.V3, e, st));
+                e = grouped(Epi{nullptr, w.dy2r, nullptr, w.y1r, nullptr, w.dz1o, nullptr}, kFitPad, ks * kFitPad);
+                DP_TIMED("fit_bwd2", st, launch_gemm<TA, TR>(EPI_BWD, mr, kFitPad, ks * kFitPad, (const TA *)w.dz2o, (const TA *)fw.V2, e, st));
+            }
+            e = grouped(Epi{nullptr, nullptr, nullptr, nullptr, w.dDr, nullptr, nullptr}, kDdim, ks * kFitPad);
+            // K = the net's width in half K stages (dz1 and V1 are zero past it), rows kFitPad long
+            int k1 = ks * kFitPad;
+            if (ks == 1) {
+                k1 = (int)std::min<long>(kFitPad, round_up(m->f1, 64 / (long)sizeof(TA)));
+                e.kld = kFitPad;
+            }
+            DP_TIMED("fit_bwd1", st, launch_gemm<TA, TR>(EPI_LIN, mr, kDdim, k1, (const TA *)w.dz1o, (const TA *)fw.V1, e, st));
         }
-        e = grouped(Epi{nullptr, nullptr, nullptr, nullptr, w.dDr, nullptr, nullptr}, kDdim, ks * kFitPad);
-        // K = the net's width in half K stages (dz1 and V1 are zero past it), rows kFitPad long
-        int k1 = ks * kFitPad;
-        if (ks == 1) {
-            k1 = (int)std::min<long>(kFitPad, round_up(m->f1, 64 / (long)sizeof(TA)));
-            e.kld = kFitPad;
-        }
-        DP_TIMED("fit_bwd1", st, launch_gemm<TA, TR>(EPI_LIN, mr, kDdim, k1, (const TA *)w.dz1o, (const TA *)fw.V1, e, st));
         if (PLAIN) {
             DP_TIMED("dT", st, launch_dT<TR>(n, (const TR *)w.dDr, (const TR *)w.T, (TR *)w.dT, st));
             if ((s = step_check("fitting_backward", st)) != DP_OK) return s;
@@ -232,9 +289,8 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
             if ((s = plain_backward<TR>(m, a.nl, n, w.dT, a.force, w.w_atom, st, tab)) != DP_OK) return s;
         } else {
             if ((s = step_check("fitting_backward", st)) != DP_OK) return s;
-            // dE/dT is formed inside the fused backward from dE/dD and T
             if (a.mode == DP_COMPRESSED) {
-                DP_TIMED("emb_bwd", st, launch_emb_bwd(m, a.nl, n, a.x, a.precision, w.T, w.dDr, w.rec, w.rcnt, a.force, w.w_atom, st));
+                DP_TIMED("emb_bwd", st, launch_emb_bwd(m, a.nl, n, a.x, a.precision, w.dT, w.dDr, fn.dT_parts(), w.rec, w.rcnt, a.force, w.w_atom, st));
             } else {
                 bool pad = a.mode == DP_FUSED_PADDED;
                 DP_TIMED("emb_bwd_pn", st, launch_emb_bwd_pn(m, a.nl, n, a.x, a.precision, w.T, w.dDr, w.rec, w.rcnt, pad, a.force, w.w_atom, st));

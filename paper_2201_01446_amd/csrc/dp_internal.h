@@ -52,9 +52,9 @@ struct TableInfo {
 struct FitWeights {
     void *V1 = nullptr, *V2 = nullptr, *V3 = nullptr;
     void *V1t = nullptr, *V2t = nullptr, *V3t = nullptr;
-    // V1t with its columns in the order k' = b M< + a of the D operand formed
-    // from T (column a M + b of V1t at k'); FP32 and FP64
-    void *V1tp = nullptr;
+    // the weights of the compressed step's fitting net in the order its
+    // lanes read them (fitnet.hip, fitsplit.hip), one copy per center type
+    void *in = nullptr, *mid = nullptr, *out = nullptr;
 };
 
 // An atom binned into a cell of the neighbor grid: its wrapped position,
@@ -290,12 +290,6 @@ struct Epi {
     int trow[dp::kMaxTypes + 1] = {0, 0, 0, 0, 0};
     long bstride = 0;
     int vstride = 0;
-    // launch_gemm_dt: T (TA[atoms][kM][4], by column) whose D = T<^T T is the A operand,
-    // the atom of each row (several types; -1: padding) or, with one type,
-    // the rows below dt_nlive are the atoms
-    const void *dt_T = nullptr;
-    const int *dt_ratom = nullptr;
-    int dt_nlive = 0;
     // row length of A and Bt (elements) when it exceeds K: the last kld - K
     // elements of every row are zero padding that the product skips; 0: K.
     // K is a whole number of half stages (64 bytes of K); a K that ends in
@@ -304,10 +298,6 @@ struct Epi {
 };
 template <typename TA, typename TR>
 void launch_gemm(int epi, int M, int N, int K, const TA *A, const TA *Bt, const Epi &e, hipStream_t st);
-// y1 = tanh(D V1 + c1) (the EPI_T1 epilogue) with D formed from e.dt_T as the
-// operand is staged; Bt is V1tp, K = kDdim (FP32, FP64)
-template <typename TA, typename TR>
-void launch_gemm_dt(int M, int N, const TA *Bt, const Epi &e, hipStream_t st);
 // E_i and dz3 for rows [0, rows); several types: w4 and b4 of the row's
 // type group (Epi trow / vstride), E written to e_atom[ratom[row]] (pad rows
 // skipped); one type: e_atom[row].
@@ -337,6 +327,41 @@ struct TailLaunch {
 template <typename T>
 void launch_fit_tail(int rows, const T *y1, const FitWeights &fw, const T *fb, const TailLaunch &tl, double *e_atom,
                      T *dz1, T *t2s, T *dy2s, hipStream_t st);
+// The fitting net of the compressed step (fitnet.hip, fitsplit.hip): its rows
+// of 16 atoms (several types: grouped by type, ratom row -> atom, -1: padding;
+// one type: the atoms below nlive) and the size of one type's weights (in
+// reals, or in pieces of 16 bytes for split operands).
+struct FitRows {
+    int ntr = 0;
+    int trow[kMaxTypes + 1] = {0, 0, 0, 0, 0};
+    const int *ratom = nullptr;
+    int nlive = 0;
+    double b4[kMaxTypes] = {0, 0, 0, 0};
+    long w_in = 0, w_mid = 0, w_out = 0;
+};
+constexpr int kFitSegs = 4;      // segments of K of the first layer, summed in order (FP64, FP32)
+constexpr int kOutParts = 32;    // innermost sums of the part of dE/dT that runs over all columns
+// FP64: z [fit_in_parts][row tile][nt][256], the first layer's sums before bias and tanh
+int fit_in_parts(const FitRows &fr);
+void launch_fit_in(const FitRows &fr, int nt, const double *T, const void *W, double *z, hipStream_t st);
+// FP32: z [split_in_parts][row tile][nt rounded up to even][256]
+int split_in_parts(const FitRows &fr);
+void launch_split_in(const FitRows &fr, int nt, const float *T, const void *W, float *z, hipStream_t st);
+// FP64 and FP32: E_i and dz1 [row tile][nt][256] from z [parts][row tile][zt][256]
+template <typename real>
+void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z, const void *W, const real *fb,
+                    const real *tanh_tab, double *e_atom, real *dz1, hipStream_t st);
+// dT [atom][column][4] without, and part [fit_out_parts][atom][16][4] with, the sums over all columns
+int fit_out_parts(const FitRows &fr);
+template <typename real>
+void launch_fit_out(const FitRows &fr, int nt, long natoms, const real *dz1, const real *T, const void *W, real *dT,
+                    real *part, hipStream_t st);
+// Mixed: from T to E_i and dz1 (z: its scratch), and from dz1 to dT and its mix_out_parts
+void launch_mix_fwd(const FitRows &fr, int nt, const float *T, const FitWeights &fw, const float *fb,
+                    const float *tanh_tab, float *z, double *e_atom, void *dz1, hipStream_t st);
+int mix_out_parts(const FitRows &fr);
+void launch_mix_out(const FitRows &fr, int nt, long natoms, const void *dz1, const float *T, const void *W, float *dT,
+                    float *part, hipStream_t st);
 template <typename TR>
 void launch_dT(int n, const TR *dD, const TR *T, TR *dT, hipStream_t st);
 // E = sum E_i and W = sum W_i in a fixed order; kFlagNonFinite when either
@@ -362,9 +387,9 @@ void launch_emb_bwd_pn(const dp_model *m, const dp_nlist *nl, int n, const doubl
 // their counts, written by launch_emb_fwd and read by launch_emb_bwd
 void launch_emb_fwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, void *T,
                     void *D, void *rec, int *rcnt, int *nnei, int *nseg, hipStream_t st);
-void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision,
-                    const void *T, const void *dD, const void *rec, const int *rcnt, double *force,
-                    double *w_atom, hipStream_t st);
+void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, const void *dT,
+                    const void *dTp, int nparts, const void *rec, const int *rcnt, double *force, double *w_atom,
+                    hipStream_t st);
 
 struct ComputeArgs {
     const dp_model *m;

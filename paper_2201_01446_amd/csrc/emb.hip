@@ -109,31 +109,6 @@ __device__ inline double quad_sum(double v)
     return v;
 }
 
-// Sum over the GL lanes of a group, result in every lane of the group.
-template <int GL>
-__device__ inline float group_sum(float v)
-{
-    v += dpp_f<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp_f<0x4E>(v);    // quad_perm [2,3,0,1]
-    v += dpp_f<0x141>(v);   // row_half_mirror
-    v += dpp_f<0x140>(v);   // row_mirror
-    if (GL >= 32) v += __shfl_xor(v, 16);
-    if (GL >= 64) v += __shfl_xor(v, 32);
-    return v;
-}
-
-template <int GL>
-__device__ inline double group_sum(double v)
-{
-    v += dpp_d<0xB1>(v);
-    v += dpp_d<0x4E>(v);
-    v += dpp_d<0x141>(v);
-    v += dpp_d<0x140>(v);
-    if (GL >= 32) v += __shfl_xor(v, 16);
-    if (GL >= 64) v += __shfl_xor(v, 32);
-    return v;
-}
-
 // One DPP move of a float or a double.
 template <int CTRL>
 __device__ inline float dpp_any(float v) { return dpp_f<CTRL>(v); }
@@ -430,14 +405,50 @@ __device__ inline void round_B(const NbrLDS<real> &L, const int *seg, int s0, in
     }
 }
 
-// CPL: columns per lane in the dE/dT prologue (lanes in NG groups of GL).
-template <typename real, int CPL>
+// dE/dT of one atom: load() starts its reads, finish() puts it, scaled, into
+// the wave's LDS as (dT_0c, .., dT_3c) per column c.  The part dT2 of the
+// columns c < M< that sums over all columns comes in nparts groups and is
+// added here: 1, the whole; 8, groups of 16 columns; 32, groups of 4, four to
+// one of 16.
+template <typename real>
+struct DTRegs {
+    V4<real> d0, d1;
+    real s;   // dT2[k = lane mod 4] of column lane / 4
+    __device__ inline void load(int i, long n, int lane, const real *dT, const real *dTp, int nparts)
+    {
+        const V4<real> *D = reinterpret_cast<const V4<real> *>(dT) + (long)i * kM;
+        d0 = D[lane];
+        d1 = D[lane + 64];
+        const real *p = dTp + (long)i * 64 + lane;
+        if (nparts <= 8) {
+            s = p[0];
+            for (int w = 1; w < nparts; w++) s += p[(long)w * n * 64];
+        } else {
+            for (int w = 0; w < nparts; w += 4) {
+                real t = p[(long)w * n * 64];
+#pragma unroll
+                for (int u = 1; u < 4; u++) t += p[(long)(w + u) * n * 64];
+                s = w ? s + t : t;
+            }
+        }
+    }
+    __device__ inline void finish(int lane, real sigma, V4<real> *dTl)
+    {
+        const int c = (lane & 15) * 4;
+        const real a0 = __shfl(s, c), a1 = __shfl(s, c + 1), a2 = __shfl(s, c + 2), a3 = __shfl(s, c + 3);
+        if (lane < kMlt) d0 = V4<real>{d0.x + a0, d0.y + a1, d0.z + a2, d0.w + a3};
+        dTl[lane] = V4<real>{sigma * d0.x, sigma * d0.y, sigma * d0.z, sigma * d0.w};
+        dTl[lane + 64] = V4<real>{sigma * d1.x, sigma * d1.y, sigma * d1.z, sigma * d1.w};
+    }
+};
+
+template <typename real>
 __global__ void __launch_bounds__(256) k_emb_bwd(int natoms, EnvArgs A, const real *__restrict__ tab,
-                                                 real sigma, const real *__restrict__ T,
-                                                 const real *__restrict__ dD, double *__restrict__ force,
+                                                 real sigma, const real *__restrict__ dT,
+                                                 const real *__restrict__ dTp, int nparts,
+                                                 double *__restrict__ force,
                                                  double *__restrict__ w_atom)
 {
-    constexpr int GL = kM / CPL, NG = 64 / GL;
     HIP_DYNAMIC_SHARED(uint4, smem_raw)   // 16-byte aligned
     char *base = reinterpret_cast<char *>(smem_raw);
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -451,80 +462,16 @@ __global__ void __launch_bounds__(256) k_emb_bwd(int natoms, EnvArgs A, const re
     p += kSegRound * 24 * sizeof(real);
     int *seg = reinterpret_cast<int *>(p);
     bool live = i < natoms;
-    // this lane's part of dE/dD (see below) into registers first: its loads
-    // stream from HBM while the neighbor scan runs
-    constexpr int APG = kMlt / NG;
-    const int g = lane / GL, l = lane % GL;
-    real dv[APG][CPL];
-    if (live) {
-        const real *dDi = dD + fit_row(A, i) * kDdim;
-#pragma unroll
-        for (int qa = 0; qa < APG; qa++)
-#pragma unroll
-            for (int c = 0; c < CPL; c++) dv[qa][c] = dDi[(g * APG + qa) * kM + l + GL * c];
-    }
+    // dE/dT into registers first: its loads stream from HBM while the
+    // neighbor scan runs
+    DTRegs<real> dt;
+    if (live) dt.load(i, natoms, lane, dT, dTp, nparts);
     int nn = 0;
     if (live) nn = load_env<real>(i, A, L, lane);
     __syncthreads();
     if (!live) return;
 
-    // dE/dT from dE/dD through D = T<^T T (Eq. 2; T already carries desc_scale):
-    //   dT[k][b] = sum_{a<M<} dD[a][b] T[k][a] + [b<M<] sum_c dD[b][c] T[k][c].
-    // Group g takes the rows a of dD in [g APG, (g+1) APG), each lane its CPL
-    // columns b = l + GL c; the second term's sum over c is a group
-    // reduction, added at the lane that owns column b = a; the groups'
-    // partials are then summed and group 0 parks dT in LDS.
-    {
-        const V4<real> *Ti = reinterpret_cast<const V4<real> *>(T) + (long)i * kM;   // T by column
-        real dt[4][CPL], tc[4][CPL];
-#pragma unroll
-        for (int c = 0; c < CPL; c++) {
-            V4<real> t = Ti[l + GL * c];
-            tc[0][c] = t.x;
-            tc[1][c] = t.y;
-            tc[2][c] = t.z;
-            tc[3][c] = t.w;
-#pragma unroll
-            for (int k = 0; k < 4; k++) dt[k][c] = 0;
-        }
-#pragma unroll
-        for (int qa = 0; qa < APG; qa++) {
-            int a0 = g * APG + qa;
-            real ta[4], s2[4];
-            V4<real> t = Ti[a0];
-            ta[0] = t.x;
-            ta[1] = t.y;
-            ta[2] = t.z;
-            ta[3] = t.w;
-#pragma unroll
-            for (int k = 0; k < 4; k++) s2[k] = 0;
-#pragma unroll
-            for (int c = 0; c < CPL; c++) {
-                real v = dv[qa][c];
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    dt[k][c] = fma(v, ta[k], dt[k][c]);
-                    s2[k] = fma(v, tc[k][c], s2[k]);
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                s2[k] = group_sum<GL>(s2[k]);
-                dt[k][0] += l == a0 ? s2[k] : (real)0;
-            }
-        }
-#pragma unroll
-        for (int off = GL; off < 64; off <<= 1)
-#pragma unroll
-            for (int c = 0; c < CPL; c++)
-#pragma unroll
-                for (int k = 0; k < 4; k++) dt[k][c] += __shfl_xor(dt[k][c], off);
-        if (g == 0) {
-#pragma unroll
-            for (int c = 0; c < CPL; c++)
-                dTl[l + GL * c] = V4<real>{sigma * dt[0][c], sigma * dt[1][c], sigma * dt[2][c], sigma * dt[3][c]};
-        }
-    }
+    dt.finish(lane, sigma, dTl);
     int nseg = find_segments(L, nn, lane, seg);   // its wave barrier also publishes dT
 
     real Fi0 = 0, Fi1 = 0, Fi2 = 0;
@@ -621,9 +568,9 @@ static void launch_fwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
                        (real)m->cfg.desc_scale, (real *)T, (TD *)D, nnei, nseg);
 }
 
-template <typename real, int CPL>
-static void launch_bwd_t(const dp_model *m, const dp_nlist *nl, int n, const double *x, const void *T,
-                         const void *dD, const void *rec, const int *rcnt, double *force, double *w_atom,
+template <typename real>
+static void launch_bwd_t(const dp_model *m, const dp_nlist *nl, int n, const double *x, const void *dT,
+                         const void *dTp, int nparts, const void *rec, const int *rcnt, double *force, double *w_atom,
                          hipStream_t st)
 {
     EnvArgs A = make_env_args(m, nl, x);
@@ -633,8 +580,9 @@ static void launch_bwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
     int wpb = lds_wpb(bwd_lds_bytes<real>(A.sel));
     size_t lds = (size_t)wpb * bwd_lds_bytes<real>(A.sel);
-    hipLaunchKernelGGL((k_emb_bwd<real, CPL>), dim3(xcd_grid(div_up(n, wpb))), dim3(64 * wpb), lds, st, n, A, tab,
-                       (real)m->cfg.desc_scale, (const real *)T, (const real *)dD, force, w_atom);
+    hipLaunchKernelGGL((k_emb_bwd<real>), dim3(xcd_grid(div_up(n, wpb))), dim3(64 * wpb), lds, st, n, A, tab,
+                       (real)m->cfg.desc_scale, (const real *)dT, (const real *)dTp, nparts,
+                       force, w_atom);
 }
 
 void launch_emb_fwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision,
@@ -645,12 +593,12 @@ void launch_emb_fwd(const dp_model *m, const dp_nlist *nl, int n, const double *
     else launch_fwd_t<float, __bf16>(m, nl, n, x, T, D, rec, rcnt, nnei, nseg, st);
 }
 
-void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision,
-                    const void *T, const void *dD, const void *rec, const int *rcnt, double *force,
-                    double *w_atom, hipStream_t st)
+void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, const void *dT,
+                    const void *dTp, int nparts, const void *rec, const int *rcnt, double *force, double *w_atom,
+                    hipStream_t st)
 {
-    if (precision == DP_FP64) launch_bwd_t<double, 4>(m, nl, n, x, T, dD, rec, rcnt, force, w_atom, st);
-    else launch_bwd_t<float, 8>(m, nl, n, x, T, dD, rec, rcnt, force, w_atom, st);
+    if (precision == DP_FP64) launch_bwd_t<double>(m, nl, n, x, dT, dTp, nparts, rec, rcnt, force, w_atom, st);
+    else launch_bwd_t<float>(m, nl, n, x, dT, dTp, nparts, rec, rcnt, force, w_atom, st);
 }
 
 }  // namespace dp

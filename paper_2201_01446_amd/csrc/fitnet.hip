@@ -1,0 +1,600 @@
+// fitnet.hip -- the fitting net of the compressed step in FP64 and FP32, from T
+// to dE/dT, with every operand in MFMA register order (gfx950).
+//
+// The transposed products put the atoms on the columns of the 16 x 16 MFMA
+// tile: A holds 16 outputs of a layer (weights), B holds 16 atoms.  Lane
+// (r, q) = (lane mod 16, lane / 16) then carries atom r throughout, and
+// register i of a result tile holds its column col(i, q) (4 i + q in FP64,
+// 4 q + i in FP32), which is what K step i of the next product takes from lane
+// group q.  So a layer's result is the next layer's operand as it stands:
+// tiles go through LDS only to reach the other waves, each lane reading back
+// what the lane of its own number wrote (16 bytes a lane, contiguous, no
+// conflicts).  The weights are stored in the order the lanes read them (a
+// tile and four K steps contiguous) and stream from L2 straight into
+// registers, once per 16 or 32 atoms.
+//
+//   k_fit_in    z1 = D V1 (D = T<^T T formed in registers, 4 FMA per element
+//               and K step)
+//   k_fit_mid   y1 = tanh(z1 + c1), the two inner layers, E_i, and their
+//               input gradients down to dz1
+//   k_fit_out   dE/dD = dz1 V1^T tile by tile, contracted at once with T into
+//               dE/dT (dE/dD is never stored)
+//
+// Sums run in the same order whatever the number of rows, so an atom's
+// results do not depend on the atoms beside it: z1 is the sum of four
+// segments of K, added in order, and the part of dE/dT that sums over all
+// columns b is built from groups of 4, 16 and 128 of them; few rows compute
+// the innermost ones side by side.
+//
+// Bound by the matrix cores.  FP64 MFMA and FP64 vector instructions take
+// turns on one pipe (measured: an FMA between two MFMAs costs its full four
+// cycles), and the chip clocks down to about 2.13 GHz under FP64 MFMA, so 71
+// TFLOP/s is the ceiling here.  Against the tiled GEMMs that kept D or dE/dD in
+// HBM (FP64, microseconds; 108 / 2,917 / 108,000 atoms): first layer 104 / 110 /
+// 1,990 -> 13 / 68 / 1,850, the 240-wide layers 106 / 110 / 1,180 -> 40 / 45 /
+// 1,040, dE/dD and dE/dT 14 + / 59 + / 1,620 + 450 (in the embedding backward)
+// -> 15 / 68 / 1,910.
+
+#include "dp_internal.h"
+#include "emb_common.h"
+#include "fit_common.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace dp {
+
+namespace {
+
+// Rows of the net: row -> atom (-1: padding), and the type group of a tile.
+__device__ inline int row_atom(const FitRows &fr, int row)
+{
+    if (fr.ratom) return fr.ratom[row];
+    return row < fr.nlive ? row : -1;
+}
+__device__ inline int row_type(const FitRows &fr, int row)
+{
+    int ty = 0;
+    for (int g = 1; g < fr.ntr; g++) ty += row >= fr.trow[g] ? 1 : 0;
+    return ty;
+}
+
+// The wave's number in its block, in a scalar register: what follows from it
+// (the weights' addresses) is then computed by the scalar unit.  FP64 MFMA and
+// the vector ALU share their pipe, so vector address arithmetic costs MFMA time.
+__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// Keeps the loads issued before it where they are: the compiler otherwise
+// moves a ring's loads down to their use, a whole turn of the ring later.
+__device__ inline void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
+// Four values of a lane (one tile, or one operand of four K steps), the MFMA
+// on them, and their place in memory: a piece of 256 reals per tile, read 16
+// bytes a lane at a time.
+template <typename real> struct Net;
+template <> struct Net<double> {
+    using v4 = d4v;
+    static __host__ __device__ constexpr int col(int i, int q) { return 4 * i + q; }
+    static __device__ inline v4 mfma(double a, double b, const v4 &c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ inline v4 get(const double *p, int lane)
+    {
+        const d2v a = reinterpret_cast<const d2v *>(p)[lane], b = reinterpret_cast<const d2v *>(p)[lane + 64];
+        return v4{a[0], a[1], b[0], b[1]};
+    }
+    static __device__ inline void put(double *p, int lane, const v4 &v)
+    {
+        reinterpret_cast<d2v *>(p)[lane] = d2v{v[0], v[1]};
+        reinterpret_cast<d2v *>(p)[lane + 64] = d2v{v[2], v[3]};
+    }
+};
+template <> struct Net<float> {
+    using v4 = f4v;
+    static __host__ __device__ constexpr int col(int i, int q) { return 4 * q + i; }
+    static __device__ inline v4 mfma(float a, float b, const v4 &c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ inline v4 get(const float *p, int lane) { return reinterpret_cast<const v4 *>(p)[lane]; }
+    static __device__ inline void put(float *p, int lane, const v4 &v) { reinterpret_cast<v4 *>(p)[lane] = v; }
+};
+constexpr int kPiece = 256;   // reals of a tile
+
+// ------------------------------------------------------------ first layer
+// One wave: RT row tiles x CT column tiles, one part of K.  K step (b, s):
+// a = col(s, q) in lane group q.  The weights and T columns of the next PD
+// values of b are in flight.
+template <int RT, int CT, int PD>
+__global__ void __launch_bounds__(256, 2) k_fit_in(FitRows fr, int nrt, int nt, int nparts,
+                                                   const double *__restrict__ T, const double *__restrict__ W,
+                                                   double *__restrict__ z)
+{
+    using real = double;
+    using N = Net<real>;
+    using v4 = typename N::v4;
+    constexpr int kSegB = kM / kFitSegs;   // columns b of a segment of K
+    static_assert(kSegB % PD == 0, "a segment is a whole number of turns of the ring");
+    const int wave = wave_id(), lane = threadIdx.x & 63;
+    const int r = lane & 15, q = lane >> 4;
+    const int ncg = (nt + CT - 1) / CT, nrg = (nrt + RT - 1) / RT, nrb = (nrg + 3) / 4;
+    // the column groups of one row block on consecutive slots of one XCD
+    int item = xcd_item(blockIdx.x, gridDim.x);
+    if (item >= nrb * ncg * nparts) return;
+    const int t0 = item % ncg * CT;
+    item /= ncg;
+    const int part = item % nparts, rg = item / nparts * 4 + wave;
+    if (rg >= nrg) return;
+
+    const v4 *Trow[RT];
+    real tl[RT][4][4];   // T<[k][col(s, q)]
+    bool any = false;
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        const int tile = rg * RT + rt;
+        const int atom = tile < nrt ? row_atom(fr, tile * 16 + r) : -1;
+        any = any || atom >= 0;
+        Trow[rt] = reinterpret_cast<const v4 *>(T) + (long)(atom >= 0 ? atom : 0) * kM;
+#pragma unroll
+        for (int s = 0; s < 4; s++) {
+            v4 t = Trow[rt][N::col(s, q)];
+#pragma unroll
+            for (int k = 0; k < 4; k++) tl[rt][s][k] = atom >= 0 ? t[k] : (real)0;
+        }
+    }
+    if (__ballot(any) == 0) return;   // tiles of padding rows only
+    const real *Wl = W + (long)row_type(fr, rg * RT * 16) * fr.w_in;   // [b][tile][piece]
+    v4 w[PD][CT], tb[PD][RT];
+    auto load = [&](int b, int u) {
+#pragma unroll
+        for (int c = 0; c < CT; c++)   // tiles past the last are computed on the last one and not stored
+            w[u][c] = N::get(Wl + ((long)b * nt + min(t0 + c, nt - 1)) * kPiece, lane);
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++) tb[u][rt] = Trow[rt][b];
+    };
+    v4 acc[RT][CT], tot[RT][CT];
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int c = 0; c < CT; c++) acc[rt][c] = tot[rt][c] = v4{0, 0, 0, 0};
+    const int b0 = part * (kM / nparts), b1 = b0 + kM / nparts;
+#pragma unroll
+    for (int u = 0; u < PD; u++) load(b0 + u, u);
+    for (int b = b0; b < b1; b += PD) {
+#pragma unroll
+        for (int u = 0; u < PD; u++) {
+#pragma unroll
+            for (int s = 0; s < 4; s++) {
+                real d[RT];
+#pragma unroll
+                for (int rt = 0; rt < RT; rt++) {
+                    real x = tl[rt][s][0] * tb[u][rt][0];
+#pragma unroll
+                    for (int k = 1; k < 4; k++) x = fma(tl[rt][s][k], tb[u][rt][k], x);
+                    d[rt] = x;
+                }
+#pragma unroll
+                for (int c = 0; c < CT; c++)
+#pragma unroll
+                    for (int rt = 0; rt < RT; rt++) acc[rt][c] = N::mfma(w[u][c][s], d[rt], acc[rt][c]);
+            }
+            load(min(b + u + PD, b1 - 1), u);
+            keep_order();
+        }
+        if ((b + PD) % kSegB == 0) {
+#pragma unroll
+            for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+                for (int c = 0; c < CT; c++) {
+                    tot[rt][c] += acc[rt][c];
+                    acc[rt][c] = v4{0, 0, 0, 0};
+                }
+        }
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        const int tile = rg * RT + rt;
+        if (tile >= nrt) break;
+#pragma unroll
+        for (int c = 0; c < CT; c++)
+            if (t0 + c < nt)
+                N::put(z + ((long)(part * nrt + tile) * nt + t0 + c) * kPiece, lane, tot[rt][c]);
+    }
+}
+
+// --------------------------------------------------- the 256-wide layers
+// One block per RT row tiles; wave w owns output tile w of every layer, so
+// what a later product needs of an earlier one (y1, t2, dy2) stays in its
+// lanes' registers.  Two LDS buffers of one operand (a piece per row and
+// column tile) alternate between the products: one barrier per product.  The
+// weights are PD k tiles ahead of the products: the four products read one
+// stream (matrix after matrix), so a product's first tiles are in flight while
+// the previous one ends and its results pass the barrier.
+template <typename real, int RT, int PD>
+struct MidRing {
+    using N = Net<real>;
+    using v4 = typename N::v4;
+    const real *W;   // the wave's tile in the first matrix
+    long wm;         // from one matrix to the next
+    int nt, lane;
+    v4 w[PD];
+    __device__ inline void load(int mat, int kt, int u)
+    {
+        w[u] = N::get(W + mat * wm + (long)min(kt, nt - 1) * kPiece, lane);
+    }
+    __device__ inline void start(const real *Wt, int nt_, int wave, int lane_)
+    {
+        nt = nt_;
+        lane = lane_;
+        wm = (long)nt * nt * kPiece;
+        W = Wt + (long)wave * nt * kPiece;
+#pragma unroll
+        for (int u = 0; u < PD; u++) load(0, u, u);
+    }
+    // acc = (matrix mat's tile of the wave) x (the operand in B)
+    __device__ inline void product(int mat, const real *B, v4 (&acc)[RT])
+    {
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++) acc[rt] = v4{0, 0, 0, 0};
+        const int nr = (nt + PD - 1) / PD * PD;
+        v4 n[RT];   // the operand of the next k tile
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++) n[rt] = N::get(B + rt * kPiece, lane);
+        for (int k0 = 0; k0 < nr; k0 += PD) {
+#pragma unroll
+            for (int u = 0; u < PD; u++) {
+                if (k0 + u < nt) {
+                    v4 x[RT];
+#pragma unroll
+                    for (int rt = 0; rt < RT; rt++) {
+                        x[rt] = n[rt];
+                        n[rt] = N::get(B + (min(k0 + u + 1, nt - 1) * RT + rt) * kPiece, lane);
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+#pragma unroll
+                        for (int rt = 0; rt < RT; rt++) acc[rt] = N::mfma(w[u][i], x[rt][i], acc[rt]);
+                }
+                const int kn = k0 + u + PD;
+                if (kn < nr) load(mat, kn, u);
+                else load(min(mat + 1, 3), kn - nr, u);
+                keep_order();
+            }
+        }
+    }
+};
+
+template <typename real, int RT, int PD, bool TAB>
+__global__ void __launch_bounds__(1024) k_fit_mid(FitRows fr, int nrt, int nt, int zt, int parts,
+                                                  const real *__restrict__ z, const real *__restrict__ W,
+                                                  const real *__restrict__ fb, const real *__restrict__ tanh_tab,
+                                                  double *__restrict__ e_atom, real *__restrict__ dz1)
+{
+    using N = Net<real>;
+    using v4 = typename N::v4;
+    HIP_DYNAMIC_SHARED(uint4, smem_raw)
+    __shared__ real Ep[16][RT * 16];
+    const int wave = wave_id(), lane = threadIdx.x & 63;   // wave < nt <= 16
+    const int r = lane & 15, q = lane >> 4;
+    const int tile0 = blockIdx.x * RT;
+    real *A = reinterpret_cast<real *>(smem_raw), *B = A + nt * RT * kPiece;
+    // rows of padding follow the atoms of their type: nothing to do from the first on
+    if (row_atom(fr, tile0 * 16) < 0) return;
+    const int ty = row_type(fr, tile0 * 16);
+    MidRing<real, RT, PD> ring;   // V2t, V3t, V3, V2
+    ring.start(W + (long)ty * fr.w_mid, nt, wave, lane);
+    const real *c1 = fb + (long)ty * kFitB + 16 * wave, *c2 = c1 + kFitPad, *c3 = c2 + kFitPad, *w4 = c3 + kFitPad;
+    const real *tab = TAB ? tanh_tab : nullptr;
+    auto put = [&](real *buf, const v4 (&v)[RT]) {
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++) N::put(buf + (wave * RT + rt) * kPiece, lane, v[rt]);
+    };
+
+    v4 y1[RT], t2[RT], dy2[RT], acc[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        const real *p = z + ((long)min(tile0 + rt, nrt - 1) * zt + wave) * kPiece;
+        v4 v = N::get(p, lane);
+        for (int s = 1; s < parts; s++) v += N::get(p + (long)s * nrt * zt * kPiece, lane);
+#pragma unroll
+        for (int i = 0; i < 4; i++) y1[rt][i] = tanh_e(v[i] + c1[N::col(i, q)], tab);
+    }
+    put(A, y1);
+    __syncthreads();
+    ring.product(0, A, acc);
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            t2[rt][i] = tanh_e(acc[rt][i] + c2[N::col(i, q)], tab);
+            dy2[rt][i] = y1[rt][i] + t2[rt][i];   // y2, until dy2 is known
+        }
+    put(B, dy2);
+    __syncthreads();
+    ring.product(1, B, acc);
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        real es = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const real t3 = tanh_e(acc[rt][i] + c3[N::col(i, q)], tab), w = w4[N::col(i, q)];
+            es += (dy2[rt][i] + t3) * w;
+            acc[rt][i] = w * ((real)1 - t3 * t3);   // dz3
+        }
+        es += __shfl_xor(es, 16);
+        es += __shfl_xor(es, 32);
+        if (q == 0) Ep[wave][rt * 16 + r] = es;
+    }
+    put(A, acc);
+    __syncthreads();
+    if (threadIdx.x < RT * 16) {
+        real e = Ep[0][threadIdx.x];
+        for (int w = 1; w < nt; w++) e += Ep[w][threadIdx.x];
+        const int row = tile0 * 16 + threadIdx.x;
+        const int atom = row < nrt * 16 ? row_atom(fr, row) : -1;
+        if (atom >= 0) e_atom[atom] = (double)e + fr.b4[ty];
+    }
+    ring.product(2, A, acc);
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            dy2[rt][i] = w4[N::col(i, q)] + acc[rt][i];
+            acc[rt][i] = dy2[rt][i] * ((real)1 - t2[rt][i] * t2[rt][i]);   // dz2
+        }
+    put(B, acc);
+    __syncthreads();
+    ring.product(3, B, acc);
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        v4 o;
+#pragma unroll
+        for (int i = 0; i < 4; i++) o[i] = (dy2[rt][i] + acc[rt][i]) * ((real)1 - y1[rt][i] * y1[rt][i]);
+        if (tile0 + rt < nrt) N::put(dz1 + ((long)(tile0 + rt) * nt + wave) * kPiece, lane, o);
+    }
+}
+
+// ---------------------------------------------- input gradient and dE/dT
+// dE/dD[a][b] of 16 atoms and one b is one tile: rows a = col(i, q), columns
+// the atoms.  With T of the lane's atom it gives
+//   dT1[k][b]  = sum_a dD[a][b] T<[k][a]   (4 FMA per k in the lane, then a
+//                transposing sum over the four lane groups: group q keeps k = q)
+//   dT2[k][a] += dD[a][b] T[k][b]          (16 sums in the lane, over all b)
+// and dE/dT[k][c] = dT1[k][c] + [c < M<] dT2[k][c].  A wave takes consecutive
+// b, two at a time; the block's rows of dz1 sit in LDS.
+template <bool UP>
+__device__ inline float swap_add(float a, float b)
+{
+    // UP false: even rows of 16 lanes get a + a of the odd row beside, odd rows
+    // b + b of the even row; UP true: the same between the halves of 32 lanes
+    const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    auto s = UP ? __builtin_amdgcn_permlane32_swap(x, y, false, false) : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
+}
+template <bool UP>
+__device__ inline double swap_add(double a, double b)
+{
+    const int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
+    auto s = UP ? __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false) : __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+    auto t = UP ? __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false) : __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    return __builtin_bit_cast(double, int2{(int)s[0], (int)t[0]}) + __builtin_bit_cast(double, int2{(int)s[1], (int)t[1]});
+}
+
+constexpr int kOutB0 = 4;    // b of the innermost sums of dT2
+constexpr int kOutB1 = 16;   // b of the middle ones
+
+// SPLIT: a wave takes kOutB0 columns and writes its dT2 to part[b / 4] of
+// kOutParts; else a wave takes kOutB1, the block (8 waves) all 128, and part
+// holds the one sum.  part: [part][atom][16 a][4 k].  The weights of the next
+// PD k tiles are in flight, across the pairs of b.
+template <bool SPLIT>
+constexpr int out_waves = SPLIT ? 4 : 8;
+
+template <typename real, bool SPLIT, int PD>
+__global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr, int nrt, int nt, long natoms,
+                                                                      const real *__restrict__ dz1,
+                                                                      const real *__restrict__ T,
+                                                                      const real *__restrict__ W, real *__restrict__ dT,
+                                                                      real *__restrict__ part)
+{
+    using N = Net<real>;
+    using v4 = typename N::v4;
+    HIP_DYNAMIC_SHARED(uint4, smem_raw)
+    constexpr int RT = 1;
+    constexpr int NW = out_waves<SPLIT>, NBW = SPLIT ? kOutB0 : kOutB1, BPT = kM / (NBW * NW);   // blocks per RT row tiles
+    const int wave = wave_id(), lane = threadIdx.x & 63;
+    const int r = lane & 15, q = lane >> 4;
+    const int tile0 = blockIdx.x / BPT * RT, b0 = (blockIdx.x % BPT * NW + wave) * NBW;
+    if (row_atom(fr, tile0 * 16) < 0) return;   // padding rows only
+    const real *Wl = W + (long)row_type(fr, tile0 * 16) * fr.w_out;   // [b][tile][piece]
+    real *S = reinterpret_cast<real *>(smem_raw);                     // [tile][row tile][piece]
+    for (int k = wave; k < nt * RT; k += NW)
+        N::put(S + k * kPiece, lane, N::get(dz1 + ((long)min(tile0 + k % RT, nrt - 1) * nt + k / RT) * kPiece, lane));
+    int atom[RT];
+    const v4 *Ta[RT];
+    v4 tl[RT][4];   // T<[.][col(i, q)]
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        atom[rt] = tile0 + rt < nrt ? row_atom(fr, (tile0 + rt) * 16 + r) : -1;
+        Ta[rt] = reinterpret_cast<const v4 *>(T) + (long)(atom[rt] >= 0 ? atom[rt] : 0) * kM;
+#pragma unroll
+        for (int i = 0; i < 4; i++) tl[rt][i] = Ta[rt][N::col(i, q)];
+    }
+    const int nr = (nt + PD - 1) / PD * PD;
+    v4 w[PD][2];
+    auto load = [&](int b, int kt, int u) {
+        const real *p = Wl + ((long)b * nt + min(kt, nt - 1)) * kPiece;
+        w[u][0] = N::get(p, lane);
+        w[u][1] = N::get(p + nt * kPiece, lane);
+    };
+#pragma unroll
+    for (int u = 0; u < PD; u++) load(b0, u, u);
+    __syncthreads();
+    v4 n[RT];   // the operand of the next k tile
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) n[rt] = N::get(S + rt * kPiece, lane);
+    v4 acc2[RT][4], tot2[RT][4];   // dT2[.][col(i, q)]
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) tot2[rt][i] = v4{0, 0, 0, 0};
+    for (int g = 0; g < NBW; g += kOutB0) {
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) acc2[rt][i] = v4{0, 0, 0, 0};
+        for (int h = 0; h < kOutB0; h += 2) {
+            const int b = b0 + g + h;
+            v4 c[2][RT], tb[2][RT];
+#pragma unroll
+            for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    tb[u][rt] = Ta[rt][b + u];
+                    c[u][rt] = v4{0, 0, 0, 0};
+                }
+            for (int k0 = 0; k0 < nr; k0 += PD) {
+#pragma unroll
+                for (int u = 0; u < PD; u++) {
+                            if (k0 + u < nt) {
+                        v4 x[RT];
+#pragma unroll
+                        for (int rt = 0; rt < RT; rt++) {
+                            x[rt] = n[rt];
+                            n[rt] = N::get(S + ((k0 + u + 1 < nt ? k0 + u + 1 : 0) * RT + rt) * kPiece, lane);
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; i++)
+#pragma unroll
+                            for (int rt = 0; rt < RT; rt++) {
+                                c[0][rt] = N::mfma(w[u][0][i], x[rt][i], c[0][rt]);
+                                c[1][rt] = N::mfma(w[u][1][i], x[rt][i], c[1][rt]);
+                            }
+                    }
+                    const int kn = k0 + u + PD;
+                    if (kn < nr) load(b, kn, u);
+                    else load(min(b + 2, b0 + NBW - 2), kn - nr, u);
+                    keep_order();
+                }
+            }
+#pragma unroll
+            for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    const v4 cc = c[u][rt];
+                    real p[4];
+#pragma unroll
+                    for (int k = 0; k < 4; k++) {
+                        real s = cc[0] * tl[rt][0][k];
+#pragma unroll
+                        for (int i = 1; i < 4; i++) s = fma(cc[i], tl[rt][i][k], s);
+                        p[k] = s;
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+#pragma unroll
+                        for (int k = 0; k < 4; k++) acc2[rt][i][k] = fma(cc[i], tb[u][rt][k], acc2[rt][i][k]);
+                    const real v = swap_add<true>(swap_add<false>(p[0], p[1]), swap_add<false>(p[2], p[3]));
+                    if (atom[rt] >= 0) dT[((long)atom[rt] * kM + b + u) * 4 + q] = v;
+                }
+        }
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                if (!SPLIT) tot2[rt][i] += acc2[rt][i];
+                else if (atom[rt] >= 0)
+                    reinterpret_cast<v4 *>(part)[((long)((b0 + g) / kOutB0) * natoms + atom[rt]) * 16 + N::col(i, q)] =
+                        acc2[rt][i];
+            }
+    }
+    if (SPLIT) return;
+    // the eight waves' sums in wave order, through LDS, a quarter of them at a time
+    v4 *X = reinterpret_cast<v4 *>(smem_raw);
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            __syncthreads();
+            X[wave * 64 + lane] = tot2[rt][i];
+            __syncthreads();
+            if (wave == i) {
+                v4 s = X[lane];
+#pragma unroll
+                for (int w = 1; w < NW; w++) s += X[w * 64 + lane];
+                if (atom[rt] >= 0) reinterpret_cast<v4 *>(part)[(long)atom[rt] * 16 + N::col(i, q)] = s;
+            }
+        }
+}
+
+// Rows of 16 that a launch covers.
+int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
+
+// Row tiles up to which the input gradient's innermost column groups go to
+// waves of their own, their sums added by the kernel that reads dE/dT.
+constexpr int kOutSplitTiles = 256;
+// The same for the first layer's segments of K (FP64).
+constexpr int kInSplitTiles = 1250;
+
+}  // namespace
+
+// ----------------------------------------------------------- launchers
+int fit_in_parts(const FitRows &fr) { return row_tiles(fr) <= kInSplitTiles ? kFitSegs : 1; }
+
+void launch_fit_in(const FitRows &fr, int nt, const double *T, const void *W, double *z, hipStream_t st)
+{
+    const int nrt = row_tiles(fr), parts = fit_in_parts(fr);
+    auto go = [&](auto kern, int RT, int CT) {
+        int items = div_up(div_up(nrt, RT), 4) * div_up(nt, CT) * parts;
+        hipLaunchKernelGGL(kern, dim3(xcd_grid(items)), dim3(256), 0, st, fr, nrt, nt, parts, T, (const double *)W, z);
+    };
+    // single tiles while they are fewer than two waves for every SIMD
+    if (nrt * div_up(nt, 3) * parts < 2048) go(k_fit_in<1, 1, 4>, 1, 1);
+    else go(k_fit_in<2, 3, 2>, 2, 3);
+}
+
+template <typename real>
+void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z, const void *W, const real *fb,
+                    const real *tanh_tab, double *e_atom, real *dz1, hipStream_t st)
+{
+    const int nrt = row_tiles(fr);
+    auto go = [&](auto kern, int RT) {
+        hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT)), dim3(64 * nt), (size_t)2 * nt * RT * kPiece * sizeof(real), st, fr,
+                           nrt, nt, zt, parts, z, (const real *)W, fb, tanh_tab, e_atom, dz1);
+    };
+    if (nrt <= 512) {   // two row tiles to a block once there are two blocks for every CU
+        if (tanh_tab) go(k_fit_mid<real, 1, 5, true>, 1);
+        else go(k_fit_mid<real, 1, 5, false>, 1);
+    } else {
+        if (tanh_tab) go(k_fit_mid<real, 2, 3, true>, 2);
+        else go(k_fit_mid<real, 2, 3, false>, 2);
+    }
+}
+template void launch_fit_mid<double>(const FitRows &, int, int, int, const double *, const void *, const double *,
+                                     const double *, double *, double *, hipStream_t);
+template void launch_fit_mid<float>(const FitRows &, int, int, int, const float *, const void *, const float *,
+                                    const float *, double *, float *, hipStream_t);
+
+int fit_out_parts(const FitRows &fr) { return row_tiles(fr) <= kOutSplitTiles ? kOutParts : 1; }
+
+template <typename real>
+void launch_fit_out(const FitRows &fr, int nt, long natoms, const real *dz1, const real *T, const void *W, real *dT,
+                    real *part, hipStream_t st)
+{
+    const int nrt = row_tiles(fr);
+    auto go = [&](auto kern, int bpt, int waves) {
+        // the combination of the waves' sums takes 8 pieces, dz1 one per tile
+        const size_t lds = (size_t)std::max(nt, 8) * kPiece * sizeof(real);
+        hipLaunchKernelGGL(kern, dim3(nrt * bpt), dim3(64 * waves), lds, st, fr, nrt, nt, natoms, dz1, T, (const real *)W,
+                           dT, part);
+    };
+    if (fit_out_parts(fr) > 1) go(k_fit_out<real, true, 3>, kM / (kOutB0 * out_waves<true>), out_waves<true>);
+    else go(k_fit_out<real, false, 3>, 1, out_waves<false>);
+}
+template void launch_fit_out<double>(const FitRows &, int, long, const double *, const double *, const void *, double *,
+                                     double *, hipStream_t);
+template void launch_fit_out<float>(const FitRows &, int, long, const float *, const float *, const void *, float *,
+                                    float *, hipStream_t);
+
+}  // namespace dp
