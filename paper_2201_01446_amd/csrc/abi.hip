@@ -392,6 +392,13 @@ dp_status prepare_nlist(const dp_model *m, int natoms, const double *box, double
     return DP_OK;
 }
 
+// Cells of all the requests of a batch that are binned together (64 MB of
+// slots at a cell capacity of 32).
+constexpr long kBatchCells = 1 << 16;
+
+// Bytes of a batch's request table: the cells and the atom offsets.
+size_t request_table_bytes(int max_req) { return sizeof(BatchCell) * max_req + sizeof(int) * ((size_t)max_req + 1); }
+
 dp_status read_flags(dp_nlist *nl, int *f, hipStream_t st)
 {
     DP_HIP(hipStreamSynchronize(st));
@@ -457,12 +464,14 @@ dp_status check_compute_args(const dp_model *m, const dp_nlist *nl, int natoms, 
 
 // The list's build at coordinates x: types first (several types group the
 // candidates by them), then the candidates and reverse slots.
-dp_status build_all(const dp_model *m, dp_nlist *nl, const double *x, const int *types, hipStream_t st)
+dp_status build_all(dp_nlist *nl, const double *x, const int *types, hipStream_t st)
 {
-    launch_fill_zero_int(nl->flags, kNumFlags, st);
+    // several types: their check comes first, so the flags are cleared before it
+    const bool typed = nl->ntypes > 1;
+    if (typed) launch_fill_zero_int(nl->flags, kNumFlags, st);
     dp_status s = build_type_layout(nl, types, st);
     if (s != DP_OK) return s;
-    return launch_build_nlist(m, nl, x, types, false, st);
+    return launch_build_nlist(nl, x, types, !typed, st);
 }
 
 }  // namespace
@@ -692,7 +701,7 @@ dp_status dp_build_nlist(dp_model *m, int natoms, const double *coords_d, const 
         dp_status s = prepare_nlist(m, natoms, box_h, skin, inout);
         if (s != DP_OK) return s;
         dp_nlist *nl = *inout;
-        s = build_all(m, nl, coords_d, types_d, st);
+        s = build_all(nl, coords_d, types_d, st);
         if (s != DP_OK) return s;
         if ((s = step_check("build_nlist", st)) != DP_OK) return s;
         int f[kNumFlags];
@@ -844,7 +853,7 @@ static dp_status nve_steps(dp_model *m, dp_nlist **nlp, int natoms, double *x, d
             if ((s = prepare_nlist(m, natoms, box_h, skin, nlp)) != DP_OK) return s;
             nl = *nlp;
             if ((s = check_compute_args(m, nl, natoms, x, mode, precision)) != DP_OK) return s;
-            if ((s = build_all(m, nl, x, types, st)) != DP_OK) return s;
+            if ((s = build_all(nl, x, types, st)) != DP_OK) return s;
             if ((s = step_check("build_nlist", st)) != DP_OK) return s;
             int f[kNumFlags];
             if ((s = read_flags(nl, f, st)) != DP_OK) return s;
@@ -887,7 +896,7 @@ static dp_status nve_steps(dp_model *m, dp_nlist **nlp, int natoms, double *x, d
             // last one flagged, and the build's capacities (grown and built
             // again on an overflow, as in dp_build_nlist).
             for (int attempt = 0;; attempt++) {
-                DP_TIMED("nlist", st, s = launch_build_nlist(m, nl, x, tl, false, st));
+                DP_TIMED("nlist", st, s = launch_build_nlist(nl, x, tl, false, st));
                 if (s != DP_OK) return s;
                 if ((s = step_check("build_nlist", st)) != DP_OK) return s;
                 int f[kNumFlags];
@@ -979,7 +988,7 @@ dp_status dp_footprint_bytes(const dp_model *m, int natoms, size_t *bytes)
 {
     if (!m || natoms < 0 || !bytes) return fail(DP_ERR_ARG, "bad argument");
     // candidates (index, shift, distance, reverse slot, pair gradient), positions, boxes, counts
-    size_t per = (size_t)kCapMax * (4 + 4 + 4 + 2 + 24) + 3 * 8 + 3 * 8 + 4 * 4 + 3 * 8 + 3 * 8 + 4 * kMaxTypes;
+    size_t per = (size_t)kCapMax * (4 + 4 + 4 + 2 + 24) + 3 * 8 + 3 * 8 + 4 * 4 + 3 * 8 + 3 * 8 + 4 * kMaxTypes + 4;
     size_t ws = std::max(ws_bytes_for_atoms(natoms, DP_FP64, m->cfg.sel, m->cfg.ntypes),
                          ws_bytes_for_atoms(natoms, DP_MIXED_BF16, m->cfg.sel, m->cfg.ntypes));
     if (m->cfg.ntypes > 1) per += 4 * (2 + kMaxTypes) + 4;   // type, row, per-type counts, row map
@@ -1018,10 +1027,15 @@ dp_status dp_batch_create(dp_model *m, int max_atoms, int max_requests, double s
     DP_HIP(hipMalloc(&nl->flags, sizeof(int) * kNumFlags));
     DP_HIP(hipMemset(nl->flags, 0, sizeof(int) * kNumFlags));
     DP_HIP(hipMalloc(&nl->scal, sizeof(double) * 512));
-    DP_HIP(hipMalloc(&b->off_d, sizeof(int) * (max_requests + 1)));
-    DP_HIP(hipMalloc(&b->Lreq_d, sizeof(double) * 3 * max_requests));
-    DP_HIP(hipHostMalloc((void **)&b->off_h, sizeof(int) * (max_requests + 1), hipHostMallocDefault));
-    DP_HIP(hipHostMalloc((void **)&b->Lreq_h, sizeof(double) * 3 * max_requests, hipHostMallocDefault));
+    // positions do not move between a batch's build and its evaluation
+    DP_HIP(hipMalloc(&nl->inner, sizeof(int) * kMaxTypes * A));
+    DP_HIP(hipMalloc(&nl->disp, sizeof(unsigned long long)));
+    DP_HIP(hipMemset(nl->disp, 0, sizeof(unsigned long long)));
+    nl->margin = 0.25 * skin;
+    const size_t table = request_table_bytes(max_requests);
+    DP_HIP(hipMalloc((void **)&b->req_d, table));
+    DP_HIP(hipHostMalloc((void **)&b->req_h, table, hipHostMallocDefault));
+    DP_HIP(hipMalloc(&b->ireq, sizeof(int) * A));
     DP_HIP(hipEventCreateWithFlags(&b->staged, hipEventDisableTiming));
     dp_status s = ensure_ws(nl, DP_FP64, m->cfg.sel);
     if (s != DP_OK) return s;
@@ -1037,10 +1051,9 @@ dp_status dp_batch_destroy(dp_batch *b)
         b->nl->atomL = nullptr;
         dp_nlist_destroy(b->nl);
     }
-    (void)hipFree(b->off_d);
-    (void)hipFree(b->Lreq_d);
-    (void)hipHostFree(b->off_h);
-    (void)hipHostFree(b->Lreq_h);
+    (void)hipFree(b->req_d);
+    (void)hipFree(b->ireq);
+    (void)hipHostFree(b->req_h);
     if (b->staged) (void)hipEventDestroy(b->staged);
     delete b;
     return DP_OK;
@@ -1059,68 +1072,93 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
     dp_nlist *nl = b->nl;
     double rcs = nl->rc_build;
     long total = 0;
-    size_t cells_needed = 0;
     int cellcap = 0;
+    bool uniq = true;   // no list holds two images of one atom
+    // the requests are binned together, in as many groups as keep the cells of
+    // a group within kBatchCells (a larger single request is a group of its own)
+    struct Group {
+        int r0, nmax;
+        long cells;
+    };
+    std::vector<Group> groups;
     for (int r = 0; r < nreq; r++) {
         const dp_request &q = reqs[r];
         if (q.natoms < 1 || q.offset != total) return fail(DP_ERR_ARG, "requests must be contiguous and non-empty");
         total += q.natoms;
+        long ncell = 0;
         if (q.periodic) {
             double L[3];
+            int nc[3], R[3];
             if (!box_ok(q.box, L)) return fail(DP_ERR_UNSUPPORTED, "box must be orthorhombic");
-            long ncell = 1;
             for (int a = 0; a < 3; a++) {
                 if (L[a] < 0.5 * rcs) return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
-                int nc = (int)std::floor(L[a] / (0.5 * rcs));
-                ncell *= nc < 1 ? 1 : nc;
+                uniq = uniq && L[a] >= 2 * rcs;
             }
-            int per = (int)std::ceil((double)q.natoms / ncell);
-            int cc = (int)round_up(3 * per + 8, 8);
-            cellcap = std::max(cellcap, cc);
-            cells_needed = std::max(cells_needed, (size_t)ncell);
+            if (!cell_axes(L, rcs, nc, R)) return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
+            ncell = (long)nc[0] * nc[1] * nc[2];
+            const int per = (int)std::ceil((double)q.natoms / ncell);
+            cellcap = std::max(cellcap, (int)round_up(3 * per + 8, 8));
         } else if (q.natoms > kCapMax) {
             return fail(DP_ERR_UNSUPPORTED, "open clusters in a batch hold at most 1024 atoms");
         }
+        if (groups.empty() || groups.back().cells + ncell > kBatchCells) groups.push_back({r, 0, 0});
+        groups.back().cells += ncell;
+        groups.back().nmax = std::max(groups.back().nmax, q.natoms);
     }
     if (total > b->max_atoms) return fail(DP_ERR_CAPACITY, "batch exceeds max_atoms");
+    long cells = 0;
+    for (const Group &g : groups) cells = std::max(cells, g.cells);
     cellcap = std::max(cellcap, nl->cellcap);
-    if (cells_needed * cellcap > nl->ncell_alloc || (cells_needed && !nl->cell_cnt)) {
-        // grow the shared cell grid (rare: only for a larger cell than seen before)
+    if ((size_t)cells * cellcap > nl->ncell_alloc || (cells && !nl->cell_cnt)) {
+        // grow the cell grids (rare: only for more cells than seen before)
         DP_HIP(hipStreamSynchronize(st));
         if (nl->cell_atoms) DP_HIP(hipFree(nl->cell_atoms));
         if (nl->cell_cnt) DP_HIP(hipFree(nl->cell_cnt));
-        size_t nc = std::max(cells_needed, (size_t)1);
+        nl->cell_atoms = nullptr;
+        nl->cell_cnt = nullptr;
+        nl->ncell_alloc = 0;
+        const size_t nc = std::max((size_t)cells, (size_t)1);
         DP_HIP(hipMalloc(&nl->cell_atoms, sizeof(CellAtom) * nc * cellcap));
-        DP_HIP(hipMalloc(&nl->cell_cnt, sizeof(int) * nc));
+        DP_HIP(hipMalloc(&nl->cell_cnt, sizeof(int) * nc * cellcap));
         nl->ncell_alloc = nc * cellcap;
     }
     nl->cellcap = cellcap ? cellcap : nl->cellcap;
-    // request table: staging buffers are reused, so wait for the last upload
+    // request table: the staging buffer is reused, so wait for the last upload
     DP_HIP(hipEventSynchronize(b->staged));
+    int *off_h = reinterpret_cast<int *>(b->req_h + b->max_req);
+    int *off_d = reinterpret_cast<int *>(b->req_d + b->max_req);
+    size_t gi = 0;
+    int cell0 = 0;
     for (int r = 0; r < nreq; r++) {
-        b->off_h[r] = reqs[r].offset;
-        for (int a = 0; a < 3; a++) b->Lreq_h[3 * r + a] = reqs[r].periodic ? reqs[r].box[4 * a] : 0.0;
-    }
-    b->off_h[nreq] = (int)total;
-    DP_HIP(hipMemcpyAsync(b->off_d, b->off_h, sizeof(int) * (nreq + 1), hipMemcpyHostToDevice, st));
-    DP_HIP(hipMemcpyAsync(b->Lreq_d, b->Lreq_h, sizeof(double) * 3 * nreq, hipMemcpyHostToDevice, st));
-    DP_HIP(hipEventRecord(b->staged, st));
-    launch_expand_boxes(nreq, b->off_d, b->Lreq_d, nl->atomL, st);
-    launch_fill_zero_int(nl->flags, kNumFlags, st);
-    for (int r = 0; r < nreq; r++) {
-        double L[3];
-        const double *Lp = nullptr;
-        if (reqs[r].periodic) {
-            box_ok(reqs[r].box, L);
-            Lp = L;
+        if (gi < groups.size() && groups[gi].r0 == r) {
+            gi++;
+            cell0 = 0;
         }
-        dp_status s = launch_build_nlist_range(nl, coords_d, reqs[r].offset, reqs[r].natoms, Lp, st);
-        if (s != DP_OK) return s;
+        BatchCell c{};
+        c.off = reqs[r].offset;
+        c.n = reqs[r].natoms;
+        if (reqs[r].periodic) {
+            box_ok(reqs[r].box, c.L);
+            cell_axes(c.L, rcs, c.nc, c.R);
+            c.cell0 = cell0;
+            cell0 += c.nc[0] * c.nc[1] * c.nc[2];
+        }
+        b->req_h[r] = c;
+        off_h[r] = c.off;
     }
-    launch_reverse(nl, 0, (int)total, st);
+    off_h[nreq] = (int)total;
+    DP_HIP(hipMemcpyAsync(b->req_d, b->req_h, sizeof(BatchCell) * nreq, hipMemcpyHostToDevice, st));
+    DP_HIP(hipMemcpyAsync(off_d, off_h, sizeof(int) * (nreq + 1), hipMemcpyHostToDevice, st));
+    DP_HIP(hipEventRecord(b->staged, st));
+    nl->natoms = (int)total;
+    for (size_t g = 0; g < groups.size(); g++) {
+        const int r0 = groups[g].r0, r1 = g + 1 < groups.size() ? groups[g + 1].r0 : nreq;
+        launch_build_batch(nl, b->req_d + r0, r1 - r0, off_h[r0], off_h[r1] - off_h[r0], groups[g].nmax, groups[g].cells,
+                           g == 0, coords_d, b->ireq, st);
+    }
+    launch_reverse(nl, 0, (int)total, st, uniq);
     dp_status s = step_check("batch_nlist", st);
     if (s != DP_OK) return s;
-    nl->natoms = (int)total;
     nl->fwd_token = 0;
     ComputeArgs a{};
     a.m = m;
@@ -1135,7 +1173,7 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
     a.force = force_d ? force_d : nl->force_tmp;
     a.phase = 0;
     a.nseg = nreq;
-    a.seg_off = b->off_d;
+    a.seg_off = off_d;
     return run_compressed(a, st);
 }
 

@@ -158,16 +158,24 @@ struct dp_nlist {
     int nve_natoms = 0, nve_mode = -1, nve_prec = -1, nve_since_build = 0;
 };
 
+namespace dp {
+// One request of a batch as the list build reads it: its atoms, box edges, cell
+// grid (nc[0] == 0: open) and its first cell in the shared arrays.
+struct BatchCell {
+    double L[3];
+    int off, n, nc[3], R[3], cell0, pad;
+};
+}  // namespace dp
+
 // A batch of independent cells (serving): one combined neighbor list and
 // scratch sized for max_atoms, resident across calls.
 struct dp_batch {
     dp_nlist *nl = nullptr;
     int max_atoms = 0, max_req = 0;
     double skin = 2.0;
-    int *off_d = nullptr;        // [max_req + 1]
-    double *Lreq_d = nullptr;    // [max_req][3]
-    int *off_h = nullptr;        // pinned staging of the request table
-    double *Lreq_h = nullptr;
+    // the request table: max_req cells, then max_req + 1 atom offsets, and its pinned staging
+    dp::BatchCell *req_d = nullptr, *req_h = nullptr;
+    int *ireq = nullptr;         // [max_atoms] the request of each atom
     hipEvent_t staged = nullptr; // the last upload from the staging buffers has run
 };
 
@@ -242,15 +250,18 @@ void launch_displacement(const dp_nlist *nl, int n, const double *x, double lim,
 dp_status launch_tabulate(dp_model *m, hipStream_t st);
 constexpr int kTanhN = 1024;   // tanh table intervals of width 1/128 on [0, 8)
 void launch_tanh_table(double *tab64, float *tab32, hipStream_t st);
-dp_status launch_build_nlist(const dp_model *m, dp_nlist *nl, const double *x, const int *types,
-                             bool reset_flags, hipStream_t st);
-// Candidates of the atoms [off, off + n) of a batch, all inside one cell with
-// box edges L (NULL: open); neighbor indices are global (j + off).
-dp_status launch_build_nlist_range(dp_nlist *nl, const double *x, int off, int n, const double *L,
-                                   hipStream_t st);
+// The candidates, reverse slots, build positions and scan prefixes of a list.
+dp_status launch_build_nlist(dp_nlist *nl, const double *x, const int *types, bool reset_flags, hipStream_t st);
+// Cells and scanned cell offsets per axis of a box; false: an edge is too short.
+bool cell_axes(const double *L, double rc, int *nc, int *R);
+// The same, but for the reverse slots, for nreq consecutive requests of a batch
+// (req on the device: atoms [i0, i0 + n), nmax in the largest, ncell cells in
+// all) in one chain of launches whatever nreq.  first: the flags are reset.
+// ireq: scratch, the request of each atom.
+void launch_build_batch(dp_nlist *nl, const BatchCell *req, int nreq, int i0, int n, int nmax, long ncell, bool first,
+                        const double *x, int *ireq, hipStream_t st);
 void launch_segment_reduce(int nreq, const int *offsets, const double *e_atom, const double *w_atom,
                            double *energy, double *virial, int *flags, hipStream_t st);
-void launch_expand_boxes(int nreq, const int *offsets, const double *Lreq, double *atomL, hipStream_t st);
 
 // BF16 operands of the fitting net are kept as an exact-ish split
 // x = hi + lo (hi = bf16(x), lo = bf16(x - hi)) laid out along K as

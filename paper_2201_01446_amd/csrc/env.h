@@ -477,7 +477,7 @@ inline EnvArgs make_env_args(const dp_model *m, const dp_nlist *nl, const double
     A.tcnt = nl->ntypes > 1 ? nl->tcnt : nullptr;
     A.n_int = m->tab.n_int();
     // the prefixes were taken at the build's cut-off: another model's reads everything
-    A.inner = (nl->x0 && m->cfg.rcut == nl->rcut_build) ? nl->inner : nullptr;
+    A.inner = m->cfg.rcut == nl->rcut_build ? nl->inner : nullptr;
     A.disp = nl->disp;
     A.margin = nl->margin;
     A.row = nl->ntypes > 1 ? nl->row : nullptr;

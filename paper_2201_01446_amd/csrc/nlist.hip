@@ -22,12 +22,15 @@
 #include "dp_internal.h"
 #include "env.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 
 namespace dp {
 
 namespace {
+
+constexpr int kRevWindow = 32;   // entries the reverse search loads at once
 
 __device__ inline int pack_shift(int a, int b, int c)
 {
@@ -44,61 +47,130 @@ __device__ inline unsigned long long make_key(int ty, float r, int j, int code)
 }
 __device__ inline int key_type(unsigned long long k) { return (int)(k >> 62); }
 
-__global__ void k_zero_int(int *p, long n)
+// Clears p[0, n) and q[0, m).
+__global__ void k_zero_int(int *p, long n, int *q, long m)
 {
     long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0;
+    else if (i - n < m) q[i - n] = 0;
 }
 
-// Wrap every atom into the box, record its image index and cell, and store
-// it (wrapped position, index, type) in its cell's slot.
-__global__ void k_bin(int n, const double *__restrict__ x, const int *__restrict__ types,
-                      const int *__restrict__ key_types, double Lx, double Ly, double Lz, int ncx, int ncy,
-                      int ncz, int cellcap, double *__restrict__ wpos, int *__restrict__ wrap,
-                      int *__restrict__ cell_cnt, CellAtom *__restrict__ cell_atoms, int *__restrict__ flags)
+// The box and cell grid of one periodic cell (a request of a batch, or the
+// one cell of a list); open: none.
+struct CellGrid {
+    double L[3];
+    int nc[3], R[3];   // cells and scanned cell offsets per axis
+    int cell0;         // its first cell in the list's arrays
+};
+
+// Wrap atom i into its box, record its image index and cell, and store it
+// (wrapped position, index, type) in its cell's slot.
+__device__ inline void bin_atom(int i, int j, int type, const double *x, const CellGrid &g, int cellcap, double *wpos,
+                                int *wrap, int *cell_cnt, CellAtom *cell_atoms, int *flags)
 {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    if (types && types[i] != 0) atomicAdd(&flags[kFlagBadType], 1);   // one-type lists only
     if (!isfinite(x[3 * i]) || !isfinite(x[3 * i + 1]) || !isfinite(x[3 * i + 2])) atomicOr(&flags[kFlagBadCoord], 1);
-    double L[3] = {Lx, Ly, Lz};
-    int nc[3] = {ncx, ncy, ncz};
     int k[3], c[3];
     double w3[3];
     for (int a = 0; a < 3; a++) {
+        const double L = g.L[a];
         double xa = x[3 * i + a];
-        double fk = floor(xa / L[a]);
-        double w = xa - fk * L[a];
-        if (w >= L[a]) { w -= L[a]; fk += 1.0; }
-        if (w < 0.0) { w += L[a]; fk -= 1.0; }
+        double fk = floor(xa / L);
+        double w = xa - fk * L;
+        if (w >= L) { w -= L; fk += 1.0; }
+        if (w < 0.0) { w += L; fk -= 1.0; }
         // image index must fit the int8 shift encoding with room to spare
         if (fk > 60.0 || fk < -60.0) { atomicAdd(&flags[kFlagCapOverflow], 1); fk = 0.0; }
         k[a] = (int)fk;
         wpos[3 * i + a] = w;
         w3[a] = w;
-        int ci = (int)(w * nc[a] / L[a]);
-        c[a] = ci < 0 ? 0 : (ci >= nc[a] ? nc[a] - 1 : ci);
+        int ci = (int)(w * g.nc[a] / L);
+        c[a] = ci < 0 ? 0 : (ci >= g.nc[a] ? g.nc[a] - 1 : ci);
     }
     wrap[i] = pack_shift(k[0], k[1], k[2]);
-    int cell = (c[0] * ncy + c[1]) * ncz + c[2];
+    int cell = g.cell0 + (c[0] * g.nc[1] + c[1]) * g.nc[2] + c[2];
     int slot = atomicAdd(&cell_cnt[cell], 1);
     if (slot < cellcap) {
         CellAtom e;
         e.x = w3[0];
         e.y = w3[1];
         e.z = w3[2];
-        e.j = i;
-        e.type = key_types ? key_types[i] : 0;
+        e.j = j;
+        e.type = type;
         cell_atoms[(long)cell * cellcap + slot] = e;
     } else {
         atomicAdd(&flags[kFlagCellOverflow], 1);
     }
 }
 
+// One periodic cell; x0 receives the positions.
+__global__ void k_bin(int n, const double *__restrict__ x, const int *__restrict__ types,
+                      const int *__restrict__ key_types, CellGrid g, int cellcap, double *__restrict__ x0,
+                      double *__restrict__ wpos, int *__restrict__ wrap, int *__restrict__ cell_cnt,
+                      CellAtom *__restrict__ cell_atoms, int *__restrict__ flags)
+{
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    if (types && types[i] != 0) atomicAdd(&flags[kFlagBadType], 1);   // one-type lists only
+    for (int a = 0; a < 3; a++) x0[3 * i + a] = x[3 * i + a];
+    bin_atom(i, i, key_types ? key_types[i] : 0, x, g, cellcap, wpos, wrap, cell_cnt, cell_atoms, flags);
+}
+
+// A batch: the request of each atom, its box edges, and (periodic requests)
+// its cell.  One block per request.
+__global__ void __launch_bounds__(256) k_batch_bin(const BatchCell *__restrict__ req, const double *__restrict__ x,
+                                                   int cellcap, int *__restrict__ ireq, double *__restrict__ atomL,
+                                                   double *__restrict__ wpos, int *__restrict__ wrap,
+                                                   int *__restrict__ cell_cnt, CellAtom *__restrict__ cell_atoms,
+                                                   int *__restrict__ flags)
+{
+    const BatchCell q = req[blockIdx.x];
+    CellGrid g;
+    for (int a = 0; a < 3; a++) {
+        g.L[a] = q.L[a];
+        g.nc[a] = q.nc[a];
+    }
+    g.cell0 = q.cell0;
+    for (int i = q.off + blockIdx.y * 256 + threadIdx.x; i < q.off + q.n; i += 256 * gridDim.y) {
+        ireq[i] = blockIdx.x;   // within this launch's requests
+        for (int a = 0; a < 3; a++) atomL[3L * i + a] = q.L[a];
+        if (q.nc[0] > 0) {
+            bin_atom(i, i, 0, x, g, cellcap, wpos, wrap, cell_cnt, cell_atoms, flags);
+        } else if (!isfinite(x[3 * i]) || !isfinite(x[3 * i + 1]) || !isfinite(x[3 * i + 2])) {
+            atomicOr(&flags[kFlagBadCoord], 1);
+        }
+    }
+}
+
+// The value of lane ^ m (m a power of two, known at compile time where it is
+// inlined): moves between lanes of the vector ALU, no LDS traffic.
+__device__ inline unsigned lane_xor(unsigned v, int m)
+{
+    switch (m) {
+    case 1: return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);    // quad_perm [1,0,3,2]
+    case 2: return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);    // quad_perm [2,3,0,1]
+    case 4:   // 7 - i in each eight, then 3 - i in each four
+        return __builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false), 0x1B, 0xF, 0xF,
+                                           false);
+    case 8: return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);   // row_ror:8
+    case 16: {
+        auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return threadIdx.x & 16 ? s[0] : s[1];
+    }
+    default: {
+        auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return threadIdx.x & 32 ? s[0] : s[1];
+    }
+    }
+}
+__device__ inline unsigned long long lane_xor64(unsigned long long v, int m)
+{
+    return ((unsigned long long)lane_xor((unsigned)(v >> 32), m) << 32) | lane_xor((unsigned)v, m);
+}
+
 // Sorts keys[0, 64 KPL) ascending with one wave: a bitonic network over
 // the wave's registers, element e = lane KPL + r in register r of its lane.
 // Exchanges between elements fewer than KPL apart stay in the lane; the
-// others pair lane with lane ^ (distance / KPL) through a shuffle, each lane
+// others pair lane with lane ^ (distance / KPL) through lane moves, each lane
 // keeping the minimum or the maximum of the two.  keys is read once and
 // written once (LDS); the caller synchronises around it.
 template <int KPL>
@@ -118,7 +190,7 @@ __device__ void wave_sort(unsigned long long *keys)
 #pragma unroll
                 for (int r = 0; r < KPL; r++) {
                     const bool up = ((lane * KPL + r) & k) == 0;   // ascending run
-                    const unsigned long long o = __shfl_xor(v[r], m);
+                    const unsigned long long o = lane_xor64(v[r], m);
                     const bool keep_min = up == lower;
                     v[r] = (v[r] < o) == keep_min ? v[r] : o;
                 }
@@ -174,14 +246,27 @@ __device__ void sort_keys(unsigned long long *keys, int P)
     }
 }
 
-__device__ void finish_atom(int i, int cnt, int cap, unsigned long long *keys, const int *wrap,
-                            int ki_packed, int *out_cnt, int *out_nei, int *out_shift, float *out_dist,
-                            int *out_tcnt, int *flags, int joff)
+// What a list keeps of one atom's candidates.
+struct ListOut {
+    int cap;
+    int *cnt, *nei, *shift;
+    float *dist;
+    short *rev;
+    int *tcnt;    // several types: candidates per type (or NULL)
+    int *inner;   // per type run, how many have a distance <= inner_lim
+    float inner_lim;
+    int *flags;
+};
+
+// Sorts the atom's cnt keys and writes its row: index, image shift, distance,
+// no reverse slot yet, and the counts per type run.  wrap: image index of the
+// atoms (NULL: open).
+__device__ void finish_atom(int i, int cnt, unsigned long long *keys, const int *wrap, int ki_packed, const ListOut &o)
 {
     int lane = threadIdx.x;
-    if (cnt > cap) {
-        if (lane == 0) atomicAdd(&flags[kFlagCapOverflow], 1);
-        cnt = cap;
+    if (cnt > o.cap) {
+        if (lane == 0) atomicAdd(&o.flags[kFlagCapOverflow], 1);
+        cnt = o.cap;
     }
     int P = 64;   // <= the LDS array (the capacity rounded up to a power of two, >= 64)
     while (P < cnt) P <<= 1;
@@ -191,52 +276,60 @@ __device__ void finish_atom(int i, int cnt, int cap, unsigned long long *keys, c
     __syncthreads();
     int kix = (int)(signed char)(ki_packed & 0xFF), kiy = (int)(signed char)((ki_packed >> 8) & 0xFF),
         kiz = (int)(signed char)((ki_packed >> 16) & 0xFF);
-    for (int t = lane; t < cnt; t += 64) {
-        unsigned long long key = keys[t];
-        int lo = (int)(key & 0x7FFFFFFFu);
-        int j = lo >> 7;
-        int code = lo & 127;
-        int sx = code / 25 - 2, sy = (code / 5) % 5 - 2, sz = code % 5 - 2;
-        int kj = wrap ? wrap[j] : 0;
-        int kjx = (int)(signed char)(kj & 0xFF), kjy = (int)(signed char)((kj >> 8) & 0xFF),
-            kjz = (int)(signed char)((kj >> 16) & 0xFF);
-        out_nei[(long)i * cap + t] = j + joff;
-        out_shift[(long)i * cap + t] = pack_shift(sx + kix - kjx, sy + kiy - kjy, sz + kiz - kjz);
-        out_dist[(long)i * cap + t] = __uint_as_float((unsigned)((key >> 31) & 0x7FFFFFFFu));
-    }
-    // the rest of the row reads as beyond every candidate (the reverse
-    // search loads a fixed window that may reach past the count)
-    for (int t = cnt + lane; t < cap; t += 64) out_dist[(long)i * cap + t] = __builtin_huge_valf();
-    if (out_tcnt) {
-        int c[kMaxTypes] = {0, 0, 0, 0};
-        for (int b = 0; b < cnt; b += 64) {
-            int ty = b + lane < cnt ? key_type(keys[b + lane]) : -1;
-            for (int q = 0; q < kMaxTypes; q++) c[q] += __popcll(__ballot(ty == q));
+    const long row = (long)i * o.cap;
+    int c[kMaxTypes] = {0, 0, 0, 0}, in[kMaxTypes] = {0, 0, 0, 0};
+    for (int b = 0; b < cnt; b += 64) {
+        const int t = b + lane;
+        const bool on = t < cnt;
+        const unsigned long long key = on ? keys[t] : ~0ull;
+        const float d = __uint_as_float((unsigned)((key >> 31) & 0x7FFFFFFFu));
+        if (on) {
+            int lo = (int)(key & 0x7FFFFFFFu);
+            int j = lo >> 7;
+            int code = lo & 127;
+            int sx = code / 25 - 2, sy = (code / 5) % 5 - 2, sz = code % 5 - 2;
+            int kj = wrap ? wrap[j] : 0;
+            int kjx = (int)(signed char)(kj & 0xFF), kjy = (int)(signed char)((kj >> 8) & 0xFF),
+                kjz = (int)(signed char)((kj >> 16) & 0xFF);
+            o.nei[row + t] = j;
+            o.shift[row + t] = pack_shift(sx + kix - kjx, sy + kiy - kjy, sz + kiz - kjz);
+            o.dist[row + t] = d;
+            // a pair is searched from one side only: a slot that no search
+            // writes (j's list lacks i) must already read -1
+            o.rev[row + t] = -1;
         }
-        if (lane == 0)
-            for (int q = 0; q < kMaxTypes; q++) out_tcnt[(long)i * kMaxTypes + q] = c[q];
+        if (o.tcnt) {
+            const int ty = on ? key_type(key) : -1;
+            for (int q = 0; q < kMaxTypes; q++) {
+                c[q] += __popcll(__ballot(ty == q));
+                in[q] += __popcll(__ballot(ty == q && d <= o.inner_lim));
+            }
+        } else {
+            in[0] += __popcll(__ballot(on && d <= o.inner_lim));
+        }
     }
-    if (lane == 0) out_cnt[i] = cnt;
+    // past the row reads as beyond every candidate, as far as the reverse
+    // search's fixed window reaches
+    if (cnt + lane < o.cap && lane < kRevWindow) o.dist[row + cnt + lane] = __builtin_huge_valf();
+    if (lane == 0) {
+        o.cnt[i] = cnt;
+        for (int q = 0; q < (o.tcnt ? kMaxTypes : 1); q++) {
+            if (o.tcnt) o.tcnt[(long)i * kMaxTypes + q] = c[q];
+            o.inner[(long)i * kMaxTypes + q] = in[q];
+        }
+    }
 }
 
-// Candidates of one atom per 64-thread block: each lane takes cell offsets
-// of the (2R+1)^3 window (two at most, R <= 2) and scans the atoms of that
-// cell, whose positions sit in the cell's own slots (no gather through an
+// Candidates of one atom per 64-thread block.  Periodic: each lane takes cell
+// offsets of the (2R+1)^3 window (two at most, R <= 2) and scans the atoms of
+// that cell, whose positions sit in the cell's own slots (no gather through an
 // index), four loads in flight at a time.
-__global__ void __launch_bounds__(64) k_candidates_cells(
-    int n, const double *__restrict__ wpos, const int *__restrict__ wrap, double Lx, double Ly,
-    double Lz, int ncx, int ncy, int ncz, int Rx, int Ry, int Rz, int cellcap,
-    const int *__restrict__ cell_cnt, const CellAtom *__restrict__ cell_atoms, double rcs2, int cap,
-    int *__restrict__ out_cnt, int *__restrict__ out_nei, int *__restrict__ out_shift,
-    float *__restrict__ out_dist, int *__restrict__ out_tcnt, int *__restrict__ flags, int joff)
+__device__ void scan_cells(int i, const double *wpos, const CellGrid &g, int cellcap, const int *cell_cnt,
+                           const CellAtom *cell_atoms, double rcs2, int cap, unsigned long long *keys, int *count)
 {
-    HIP_DYNAMIC_SHARED(unsigned long long, keys)
-    __shared__ int count;
-    int i = xcd_item(blockIdx.x, gridDim.x);
-    if (i >= n) return;   // the whole (one-wave) block
     const int lane = threadIdx.x;
-    if (lane == 0) count = 0;
-    __syncthreads();
+    const double Lx = g.L[0], Ly = g.L[1], Lz = g.L[2];
+    const int ncx = g.nc[0], ncy = g.nc[1], ncz = g.nc[2], Rx = g.R[0], Ry = g.R[1], Rz = g.R[2];
     const double wi0 = wpos[3 * i], wi1 = wpos[3 * i + 1], wi2 = wpos[3 * i + 2];
     const int ci0 = min((int)(wi0 * ncx / Lx), ncx - 1), ci1 = min((int)(wi1 * ncy / Ly), ncy - 1),
               ci2 = min((int)(wi2 * ncz / Lz), ncz - 1);
@@ -252,7 +345,7 @@ __global__ void __launch_bounds__(64) k_candidates_cells(
         cx -= sx * ncx;
         cy -= sy * ncy;
         cz -= sz * ncz;
-        const int cell = (cx * ncy + cy) * ncz + cz;
+        const int cell = g.cell0 + (cx * ncy + cy) * ncz + cz;
         const int m = min(cell_cnt[cell], cellcap);
         const double ox = sx * Lx - wi0, oy = sy * Ly - wi1, oz = sz * Lz - wi2;
         const int code = (sx + 2) * 25 + (sy + 2) * 5 + (sz + 2);
@@ -268,75 +361,101 @@ __global__ void __launch_bounds__(64) k_candidates_cells(
                 const double d0 = q[u].x + ox, d1 = q[u].y + oy, d2 = q[u].z + oz;
                 const double r2 = d0 * d0 + d1 * d1 + d2 * d2;
                 if (r2 < rcs2 && !(q[u].j == i && code == 62 /* image (0, 0, 0) */)) {
-                    int slot = atomicAdd(&count, 1);
+                    int slot = atomicAdd(count, 1);
                     if (slot < cap) keys[slot] = make_key(q[u].type, (float)sqrt(r2), q[u].j, code);
                 }
             }
         }
     }
-    __syncthreads();
-    finish_atom(i, count, cap, keys, wrap, wrap[i], out_cnt, out_nei, out_shift, out_dist, out_tcnt, flags,
-                joff);
 }
 
-// Open boundary: brute force over all atoms (for clusters of modest size).
-// check_types: one-type lists flag any type other than 0; key_types: the
-// types that group a several-type list (NULL: one type).
-__global__ void __launch_bounds__(64) k_candidates_open(int n, const double *__restrict__ x,
-                                                        const int *__restrict__ check_types,
-                                                        const int *__restrict__ key_types, double rcs2,
-                                                        int cap, int *__restrict__ out_cnt,
-                                                        int *__restrict__ out_nei,
-                                                        int *__restrict__ out_shift,
-                                                        float *__restrict__ out_dist,
-                                                        int *__restrict__ out_tcnt,
-                                                        int *__restrict__ flags, int joff)
+// Open boundary: brute force over the atoms [j0, j1) (for clusters of modest
+// size).  key_types: the types that group a several-type list (NULL: one type).
+__device__ void scan_open(int i, int j0, int j1, const double *x, const int *key_types, double rcs2, int cap,
+                          unsigned long long *keys, int *count)
+{
+    double xi0 = x[3 * i], xi1 = x[3 * i + 1], xi2 = x[3 * i + 2];
+    for (int j = j0 + (int)threadIdx.x; j < j1; j += 64) {
+        if (j == i) continue;
+        double d0 = x[3 * j] - xi0, d1 = x[3 * j + 1] - xi1, d2 = x[3 * j + 2] - xi2;
+        double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+        if (r2 < rcs2) {
+            int slot = atomicAdd(count, 1);
+            if (slot < cap)
+                keys[slot] = make_key(key_types ? key_types[j] : 0, (float)sqrt(r2), j, 62 /* image (0,0,0) */);
+        }
+    }
+}
+
+__global__ void __launch_bounds__(64) k_candidates_cells(int n, const double *__restrict__ wpos,
+                                                         const int *__restrict__ wrap, CellGrid g, int cellcap,
+                                                         const int *__restrict__ cell_cnt,
+                                                         const CellAtom *__restrict__ cell_atoms, double rcs2, ListOut o)
 {
     HIP_DYNAMIC_SHARED(unsigned long long, keys)
     __shared__ int count;
     int i = xcd_item(blockIdx.x, gridDim.x);
     if (i >= n) return;   // the whole (one-wave) block
-    int lane = threadIdx.x;
-    if (lane == 0) {
-        count = 0;
-        if (check_types && check_types[i] != 0) atomicAdd(&flags[kFlagBadType], 1);
-        if (!isfinite(x[3 * i]) || !isfinite(x[3 * i + 1]) || !isfinite(x[3 * i + 2]))
-            atomicOr(&flags[kFlagBadCoord], 1);
-    }
+    if (threadIdx.x == 0) count = 0;
     __syncthreads();
-    double xi0 = x[3 * i], xi1 = x[3 * i + 1], xi2 = x[3 * i + 2];
-    for (int j = lane; j < n; j += 64) {
-        if (j == i) continue;
-        double d0 = x[3 * j] - xi0, d1 = x[3 * j + 1] - xi1, d2 = x[3 * j + 2] - xi2;
-        double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-        if (r2 < rcs2) {
-            int slot = atomicAdd(&count, 1);
-            if (slot < cap)
-                keys[slot] = make_key(key_types ? key_types[j] : 0, (float)sqrt(r2), j, 62 /* image (0,0,0) */);
-        }
-    }
+    scan_cells(i, wpos, g, cellcap, cell_cnt, cell_atoms, rcs2, o.cap, keys, &count);
     __syncthreads();
-    finish_atom(i, count, cap, keys, nullptr, 0, out_cnt, out_nei, out_shift, out_dist, out_tcnt, flags, joff);
+    finish_atom(i, count, keys, wrap, wrap[i], o);
 }
 
-// Per atom (one wave) and type run: how many candidates have a build
-// distance <= lim.  The runs are sorted by distance, so these are a prefix.
-__global__ void __launch_bounds__(256) k_inner(int n, int cap, int ntypes, const int *__restrict__ cnt,
-                                               const int *__restrict__ tcnt, const float *__restrict__ dist,
-                                               float lim, int *__restrict__ inner)
+// Atoms [i0, i0 + n) of a batch, each in its request's cell grid or open cluster.
+__global__ void __launch_bounds__(64) k_candidates_batch(int i0, int n, const BatchCell *__restrict__ req,
+                                                         const int *__restrict__ ireq, const double *__restrict__ x,
+                                                         const double *__restrict__ wpos, const int *__restrict__ wrap,
+                                                         int cellcap, const int *__restrict__ cell_cnt,
+                                                         const CellAtom *__restrict__ cell_atoms, double rcs2, ListOut o)
 {
-    int lane = threadIdx.x & 63;
-    int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n) return;   // the whole wave
-    const float *d = dist + (long)i * cap;
-    int c0 = 0;
-    for (int ty = 0; ty < ntypes; ty++) {
-        int ct = tcnt ? tcnt[(long)i * kMaxTypes + ty] : cnt[i];
-        int m = 0;
-        for (int b = 0; b < ct; b += 64) m += __popcll(__ballot(b + lane < ct && d[c0 + b + lane] <= lim));
-        if (lane == 0) inner[(long)i * kMaxTypes + ty] = m;
-        c0 += ct;
+    HIP_DYNAMIC_SHARED(unsigned long long, keys)
+    __shared__ int count;
+    int i = xcd_item(blockIdx.x, gridDim.x);
+    if (i >= n) return;   // the whole (one-wave) block
+    i += i0;
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    const BatchCell *q = req + ireq[i];
+    const bool open = q->nc[0] == 0;
+    if (open) {
+        scan_open(i, q->off, q->off + q->n, x, nullptr, rcs2, o.cap, keys, &count);
+    } else {
+        CellGrid g;
+        for (int a = 0; a < 3; a++) {
+            g.L[a] = q->L[a];
+            g.nc[a] = q->nc[a];
+            g.R[a] = q->R[a];
+        }
+        g.cell0 = q->cell0;
+        scan_cells(i, wpos, g, cellcap, cell_cnt, cell_atoms, rcs2, o.cap, keys, &count);
     }
+    __syncthreads();
+    finish_atom(i, count, keys, open ? nullptr : wrap, open ? 0 : wrap[i], o);
+}
+
+// check_types: one-type lists flag any type other than 0.
+__global__ void __launch_bounds__(64) k_candidates_open(int n, const double *__restrict__ x,
+                                                        const int *__restrict__ check_types,
+                                                        const int *__restrict__ key_types, double *__restrict__ x0,
+                                                        double rcs2, ListOut o)
+{
+    HIP_DYNAMIC_SHARED(unsigned long long, keys)
+    __shared__ int count;
+    int i = xcd_item(blockIdx.x, gridDim.x);
+    if (i >= n) return;   // the whole (one-wave) block
+    if (threadIdx.x < 3) x0[3 * i + threadIdx.x] = x[3 * i + threadIdx.x];
+    if (threadIdx.x == 0) {
+        count = 0;
+        if (check_types && check_types[i] != 0) atomicAdd(&o.flags[kFlagBadType], 1);
+        if (!isfinite(x[3 * i]) || !isfinite(x[3 * i + 1]) || !isfinite(x[3 * i + 2]))
+            atomicOr(&o.flags[kFlagBadCoord], 1);
+    }
+    __syncthreads();
+    scan_open(i, 0, n, x, key_types, rcs2, o.cap, keys, &count);
+    __syncthreads();
+    finish_atom(i, count, keys, nullptr, 0, o);
 }
 
 // Largest |x_i - x0_i|: per block a maximum, then one atomicMax on the bits
@@ -383,112 +502,97 @@ void launch_displacement(const dp_nlist *nl, int n, const double *x, double lim,
 
 void launch_fill_zero_int(int *p, long n, hipStream_t st)
 {
-    if (n > 0) hipLaunchKernelGGL(k_zero_int, dim3(div_up(n, 256)), dim3(256), 0, st, p, n);
+    if (n > 0) hipLaunchKernelGGL(k_zero_int, dim3(div_up(n, 256)), dim3(256), 0, st, p, n, (int *)nullptr, 0L);
 }
 
-// The positions of the build and each atom's candidate prefixes within
-// rcut + margin (lists that carry them).
-static dp_status launch_prefix(const dp_model *m, dp_nlist *nl, const double *x, hipStream_t st)
+static ListOut list_out(const dp_nlist *nl)
 {
-    if (!nl->x0) return DP_OK;
-    int n = nl->natoms;
-    DP_HIP(hipMemcpyAsync(nl->x0, x, sizeof(double) * 3 * (size_t)n, hipMemcpyDeviceToDevice, st));
-    const bool typed = nl->ntypes > 1;
-    hipLaunchKernelGGL(k_inner, dim3(div_up(n, 4)), dim3(256), 0, st, n, nl->cap, typed ? nl->ntypes : 1, nl->cnt,
-                       typed ? nl->tcnt : nullptr, nl->dist, (float)(m->cfg.rcut + nl->margin), nl->inner);
-    return DP_OK;
+    ListOut o;
+    o.cap = nl->cap;
+    o.cnt = nl->cnt;
+    o.nei = nl->nei;
+    o.shift = nl->shift;
+    o.dist = nl->dist;
+    o.rev = nl->rev;
+    o.tcnt = nl->ntypes > 1 ? nl->tcnt : nullptr;
+    o.inner = nl->inner;
+    o.inner_lim = (float)(nl->rcut_build + nl->margin);
+    o.flags = nl->flags;
+    return o;
 }
 
-dp_status launch_build_nlist(const dp_model *m, dp_nlist *nl, const double *x, const int *types,
-                             bool reset_flags, hipStream_t st)
+// Bytes of LDS for one atom's keys: the sort pads the candidate count up to a
+// power of two <= that of the capacity.
+static size_t key_bytes(int cap)
+{
+    int cap2 = 1;
+    while (cap2 < cap) cap2 <<= 1;
+    return sizeof(unsigned long long) * cap2;
+}
+
+// Cells and scanned offsets per axis of a box for cells of edge >= rc / 2;
+// false when an axis is shorter than that.
+bool cell_axes(const double *L, double rc, int *nc, int *R)
+{
+    for (int a = 0; a < 3; a++) {
+        nc[a] = (int)floor(L[a] / (0.5 * rc));
+        if (nc[a] < 1) nc[a] = 1;
+        R[a] = (int)ceil(rc / (L[a] / nc[a]) - 1e-12);
+        if (R[a] > 2) return false;
+    }
+    return true;
+}
+
+dp_status launch_build_nlist(dp_nlist *nl, const double *x, const int *types, bool reset_flags, hipStream_t st)
 {
     int n = nl->natoms;
     double rcs2 = nl->rc_build * nl->rc_build;
-    // the sort pads the candidate count up to a power of two <= that of cap
-    int cap2 = 1;
-    while (cap2 < nl->cap) cap2 <<= 1;
-    size_t lds = sizeof(unsigned long long) * cap2;
+    const size_t lds = key_bytes(nl->cap);
     // several types: the list's own copy (checked by build_type_layout) groups the candidates
     const bool typed = nl->ntypes > 1;
     const int *check = typed ? nullptr : types;
     const int *ktypes = typed ? nl->type : nullptr;
-    int *tcnt = typed ? nl->tcnt : nullptr;
-    if (reset_flags) launch_fill_zero_int(nl->flags, kNumFlags, st);
+    const ListOut o = list_out(nl);
     if (!nl->periodic) {
-        hipLaunchKernelGGL(k_candidates_open, dim3(xcd_grid(n)), dim3(64), lds, st, n, x, check, ktypes, rcs2,
-                           nl->cap, nl->cnt, nl->nei, nl->shift, nl->dist, tcnt, nl->flags, 0);
+        if (reset_flags) launch_fill_zero_int(nl->flags, kNumFlags, st);
+        hipLaunchKernelGGL(k_candidates_open, dim3(xcd_grid(n)), dim3(64), lds, st, n, x, check, ktypes, nl->x0, rcs2, o);
         launch_reverse(nl, 0, n, st, true);   // open: every image shift is zero
-        return launch_prefix(m, nl, x, st);
+        return DP_OK;
     }
-    long ncell = (long)nl->nc[0] * nl->nc[1] * nl->nc[2];
-    launch_fill_zero_int(nl->cell_cnt, ncell, st);
-    hipLaunchKernelGGL(k_bin, dim3(div_up(n, 256)), dim3(256), 0, st, n, x, check, ktypes, nl->L[0], nl->L[1],
-                       nl->L[2], nl->nc[0], nl->nc[1], nl->nc[2], nl->cellcap, nl->wpos, nl->wrap, nl->cell_cnt,
-                       nl->cell_atoms, nl->flags);
-    int R[3];
-    for (int a = 0; a < 3; a++) {
-        double c = nl->L[a] / nl->nc[a];
-        R[a] = (int)ceil(nl->rc_build / c - 1e-12);
-        if (R[a] > 2) return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
-    }
-    hipLaunchKernelGGL(k_candidates_cells, dim3(xcd_grid(n)), dim3(64), lds, st, n,
-                       nl->wpos, nl->wrap, nl->L[0], nl->L[1],
-                       nl->L[2], nl->nc[0], nl->nc[1], nl->nc[2], R[0], R[1], R[2], nl->cellcap,
-                       nl->cell_cnt, nl->cell_atoms, rcs2, nl->cap, nl->cnt, nl->nei, nl->shift, nl->dist, tcnt,
-                       nl->flags, 0);
+    CellGrid g;
+    for (int a = 0; a < 3; a++) g.L[a] = nl->L[a];
+    g.cell0 = 0;
+    if (!cell_axes(nl->L, nl->rc_build, g.nc, g.R))
+        return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
+    const long ncell = (long)g.nc[0] * g.nc[1] * g.nc[2], nflag = reset_flags ? kNumFlags : 0;
+    hipLaunchKernelGGL(k_zero_int, dim3(div_up(ncell + nflag, 256)), dim3(256), 0, st, nl->cell_cnt, ncell, nl->flags, nflag);
+    hipLaunchKernelGGL(k_bin, dim3(div_up(n, 256)), dim3(256), 0, st, n, x, check, ktypes, g, nl->cellcap, nl->x0,
+                       nl->wpos, nl->wrap, nl->cell_cnt, nl->cell_atoms, nl->flags);
+    hipLaunchKernelGGL(k_candidates_cells, dim3(xcd_grid(n)), dim3(64), lds, st, n, nl->wpos, nl->wrap, g, nl->cellcap,
+                       nl->cell_cnt, nl->cell_atoms, rcs2, o);
     // edges of at least 2 (rcut + skin): a list holds at most one image of
     // any atom, so j's slot for i is the one whose index is i
     const bool uniq = nl->L[0] >= 2 * nl->rc_build && nl->L[1] >= 2 * nl->rc_build && nl->L[2] >= 2 * nl->rc_build;
     launch_reverse(nl, 0, n, st, uniq);
-    return launch_prefix(m, nl, x, st);
-}
-
-dp_status launch_build_nlist_range(dp_nlist *nl, const double *x, int off, int n, const double *L,
-                                   hipStream_t st)
-{
-    double rcs = nl->rc_build, rcs2 = rcs * rcs;
-    int cap2 = 1;
-    while (cap2 < nl->cap) cap2 <<= 1;
-    size_t lds = sizeof(unsigned long long) * cap2;
-    long cap = nl->cap;
-    const double *xr = x + 3L * off;
-    int *cnt = nl->cnt + off, *nei = nl->nei + off * cap, *shift = nl->shift + off * cap;
-    float *dist = nl->dist + off * cap;
-    if (!L) {
-        hipLaunchKernelGGL(k_candidates_open, dim3(xcd_grid(n)), dim3(64), lds, st, n, xr, (const int *)nullptr,
-                           (const int *)nullptr, rcs2, nl->cap, cnt, nei, shift, dist, (int *)nullptr, nl->flags,
-                           off);
-        return DP_OK;
-    }
-    int nc[3], R[3];
-    for (int a = 0; a < 3; a++) {
-        nc[a] = (int)floor(L[a] / (0.5 * rcs));
-        if (nc[a] < 1) nc[a] = 1;
-        R[a] = (int)ceil(rcs / (L[a] / nc[a]) - 1e-12);
-        if (R[a] > 2) return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
-    }
-    long ncell = (long)nc[0] * nc[1] * nc[2];
-    if ((size_t)(ncell * nl->cellcap) > nl->ncell_alloc) return fail(DP_ERR_STATE, "cell grid too small");
-    launch_fill_zero_int(nl->cell_cnt, ncell, st);
-    hipLaunchKernelGGL(k_bin, dim3(div_up(n, 256)), dim3(256), 0, st, n, xr, (const int *)nullptr,
-                       (const int *)nullptr, L[0], L[1], L[2], nc[0], nc[1], nc[2], nl->cellcap, nl->wpos + 3L * off,
-                       nl->wrap + off, nl->cell_cnt, nl->cell_atoms, nl->flags);
-    hipLaunchKernelGGL(k_candidates_cells, dim3(xcd_grid(n)), dim3(64), lds, st, n, nl->wpos + 3L * off, nl->wrap + off, L[0],
-                       L[1], L[2], nc[0], nc[1], nc[2], R[0], R[1], R[2], nl->cellcap, nl->cell_cnt, nl->cell_atoms,
-                       rcs2, nl->cap, cnt, nei, shift, dist, (int *)nullptr, nl->flags, off);
     return DP_OK;
 }
 
-namespace {
-
-// Expands per-request box edges to per-atom ones; one block per request.
-__global__ void k_expand_boxes(const int *__restrict__ off, const double *__restrict__ Lreq,
-                               double *__restrict__ atomL)
+void launch_build_batch(dp_nlist *nl, const BatchCell *req, int nreq, int i0, int n, int nmax, long ncell, bool first,
+                        const double *x, int *ireq, hipStream_t st)
 {
-    int r = blockIdx.x;
-    for (int i = off[r] + threadIdx.x; i < off[r + 1]; i += blockDim.x)
-        for (int a = 0; a < 3; a++) atomL[3L * i + a] = Lreq[3 * r + a];
+    const long nflag = first ? kNumFlags : 0;
+    if (ncell + nflag > 0)
+        hipLaunchKernelGGL(k_zero_int, dim3(div_up(ncell + nflag, 256)), dim3(256), 0, st, nl->flags, nflag, nl->cell_cnt,
+                           ncell);
+    // blocks for the largest request; the smaller ones' later blocks find no atoms
+    hipLaunchKernelGGL(k_batch_bin, dim3(nreq, std::min(64, div_up(nmax, 256))), dim3(256), 0, st, req, x, nl->cellcap, ireq,
+                       nl->atomL, nl->wpos, nl->wrap, nl->cell_cnt, nl->cell_atoms, nl->flags);
+    hipLaunchKernelGGL(k_candidates_batch, dim3(xcd_grid(n)), dim3(64), key_bytes(nl->cap), st, i0, n, req, ireq, x,
+                       nl->wpos, nl->wrap, nl->cellcap, nl->cell_cnt, nl->cell_atoms, nl->rc_build * nl->rc_build,
+                       list_out(nl));
 }
+
+namespace {
 
 // Per request (block): E = sum of E_i and W = sum of W_i over its atoms, in
 // an order fixed relative to the request's first atom (so the result does
@@ -528,19 +632,7 @@ void launch_segment_reduce(int nreq, const int *offsets, const double *e_atom, c
                        flags);
 }
 
-void launch_expand_boxes(int nreq, const int *offsets, const double *Lreq, double *atomL, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_expand_boxes, dim3(nreq), dim3(256), 0, st, offsets, Lreq, atomL);
-}
-
-
 namespace {
-
-__global__ void k_fill_short(short *p, long n, short v)
-{
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
 
 __device__ inline int neg_shift(int v)
 {
@@ -566,8 +658,6 @@ __device__ inline int neg_shift(int v)
 // of at least 2 (rcut + skin), or no box): a list holds at most one image of
 // any atom, so an entry of the window is i's slot when its index is i (the
 // image shift is not read).  One 64-thread block per atom.
-constexpr int kRevWindow = 32;
-
 __device__ inline int run_start(const int *tcnt, int a, int ty)
 {
     int s = 0;
@@ -789,11 +879,6 @@ __global__ void __launch_bounds__(256) k_force_gather(int n, EnvArgs A, const sh
 void launch_reverse(dp_nlist *nl, int off, int n, hipStream_t st, bool uniq)
 {
     if (n <= 0) return;
-    // every slot starts at -1: a pair is searched from one side only, so a
-    // slot that no search writes (j's list lacks i) must already read -1
-    long m = (long)n * nl->cap;
-    hipLaunchKernelGGL(k_fill_short, dim3(div_up(m, 256)), dim3(256), 0, st, nl->rev + (long)off * nl->cap, m,
-                       (short)-1);
     const bool typed = nl->ntypes > 1;
     if (typed)
         hipLaunchKernelGGL(k_reverse<true>, dim3(xcd_grid(n)), dim3(64), 0, st, off, n, nl->cap, nl->cnt, nl->nei,
