@@ -211,7 +211,9 @@ __global__ void __launch_bounds__(256, 2) k_fit_in(FitRows fr, int nrt, int nt, 
 // weights are PD k tiles ahead of the products: the four products read one
 // stream (matrix after matrix), so a product's first tiles are in flight while
 // the previous one ends and its results pass the barrier.
-template <typename real, int RT, int PD>
+// NTC: nt when it is known at compile time (the loops then unroll whole, and an
+// operand of the next k tile is in flight without a copy), else 0.
+template <typename real, int RT, int PD, int NTC>
 struct MidRing {
     using N = Net<real>;
     using v4 = typename N::v4;
@@ -237,35 +239,40 @@ struct MidRing {
     {
 #pragma unroll
         for (int rt = 0; rt < RT; rt++) acc[rt] = v4{0, 0, 0, 0};
-        const int nr = (nt + PD - 1) / PD * PD;
-        v4 n[RT];   // the operand of the next k tile
+        const int n = NTC ? NTC : nt, nr = (n + PD - 1) / PD * PD;
+        v4 x[RT], xn[RT];   // the operand of this and of the next k tile
+        auto fetch = [&](int kt) {
 #pragma unroll
-        for (int rt = 0; rt < RT; rt++) n[rt] = N::get(B + rt * kPiece, lane);
-        for (int k0 = 0; k0 < nr; k0 += PD) {
+            for (int rt = 0; rt < RT; rt++) xn[rt] = N::get(B + (kt * RT + rt) * kPiece, lane);
+        };
+        auto step = [&](int kt, int u) {
+            if (NTC || kt < n) {
 #pragma unroll
-            for (int u = 0; u < PD; u++) {
-                if (k0 + u < nt) {
-                    v4 x[RT];
+                for (int rt = 0; rt < RT; rt++) x[rt] = xn[rt];
+                if (kt + 1 < n) fetch(kt + 1);
 #pragma unroll
-                    for (int rt = 0; rt < RT; rt++) {
-                        x[rt] = n[rt];
-                        n[rt] = N::get(B + (min(k0 + u + 1, nt - 1) * RT + rt) * kPiece, lane);
-                    }
+                for (int i = 0; i < 4; i++)
 #pragma unroll
-                    for (int i = 0; i < 4; i++)
-#pragma unroll
-                        for (int rt = 0; rt < RT; rt++) acc[rt] = N::mfma(w[u][i], x[rt][i], acc[rt]);
-                }
-                const int kn = k0 + u + PD;
-                if (kn < nr) load(mat, kn, u);
-                else load(min(mat + 1, 3), kn - nr, u);
-                keep_order();
+                    for (int rt = 0; rt < RT; rt++) acc[rt] = N::mfma(w[u][i], x[rt][i], acc[rt]);
             }
+            if (kt + PD < nr) load(mat, kt + PD, u);
+            else load(min(mat + 1, 3), kt + PD - nr, u);
+            keep_order();
+        };
+        fetch(0);
+        if constexpr (NTC) {
+            static_assert(NTC % PD == 0, "whole turns of the ring");
+#pragma unroll
+            for (int kt = 0; kt < NTC; kt++) step(kt, kt % PD);
+        } else {
+            for (int k0 = 0; k0 < nr; k0 += PD)
+#pragma unroll
+                for (int u = 0; u < PD; u++) step(k0 + u, u);
         }
     }
 };
 
-template <typename real, int RT, int PD, bool TAB>
+template <typename real, int RT, int PD, int NTC, bool TAB>
 __global__ void __launch_bounds__(1024) k_fit_mid(FitRows fr, int nrt, int nt, int zt, int parts,
                                                   const real *__restrict__ z, const real *__restrict__ W,
                                                   const real *__restrict__ fb, const real *__restrict__ tanh_tab,
@@ -282,7 +289,7 @@ __global__ void __launch_bounds__(1024) k_fit_mid(FitRows fr, int nrt, int nt, i
     // rows of padding follow the atoms of their type: nothing to do from the first on
     if (row_atom(fr, tile0 * 16) < 0) return;
     const int ty = row_type(fr, tile0 * 16);
-    MidRing<real, RT, PD> ring;   // V2t, V3t, V3, V2
+    MidRing<real, RT, PD, NTC> ring;   // V2t, V3t, V3, V2
     ring.start(W + (long)ty * fr.w_mid, nt, wave, lane);
     const real *c1 = fb + (long)ty * kFitB + 16 * wave, *c2 = c1 + kFitPad, *c3 = c2 + kFitPad, *w4 = c3 + kFitPad;
     const real *tab = TAB ? tanh_tab : nullptr;
@@ -391,7 +398,7 @@ constexpr int kOutB1 = 16;   // b of the middle ones
 template <bool SPLIT>
 constexpr int out_waves = SPLIT ? 4 : 8;
 
-template <typename real, bool SPLIT, int PD>
+template <typename real, bool SPLIT, int PD, int NTC>
 __global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr, int nrt, int nt, long natoms,
                                                                       const real *__restrict__ dz1,
                                                                       const real *__restrict__ T,
@@ -401,27 +408,20 @@ __global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr
     using N = Net<real>;
     using v4 = typename N::v4;
     HIP_DYNAMIC_SHARED(uint4, smem_raw)
-    constexpr int RT = 1;
-    constexpr int NW = out_waves<SPLIT>, NBW = SPLIT ? kOutB0 : kOutB1, BPT = kM / (NBW * NW);   // blocks per RT row tiles
+    constexpr int NW = out_waves<SPLIT>, NBW = SPLIT ? kOutB0 : kOutB1, BPT = kM / (NBW * NW);   // blocks per row tile
     const int wave = wave_id(), lane = threadIdx.x & 63;
     const int r = lane & 15, q = lane >> 4;
-    const int tile0 = blockIdx.x / BPT * RT, b0 = (blockIdx.x % BPT * NW + wave) * NBW;
-    if (row_atom(fr, tile0 * 16) < 0) return;   // padding rows only
-    const real *Wl = W + (long)row_type(fr, tile0 * 16) * fr.w_out;   // [b][tile][piece]
-    real *S = reinterpret_cast<real *>(smem_raw);                     // [tile][row tile][piece]
-    for (int k = wave; k < nt * RT; k += NW)
-        N::put(S + k * kPiece, lane, N::get(dz1 + ((long)min(tile0 + k % RT, nrt - 1) * nt + k / RT) * kPiece, lane));
-    int atom[RT];
-    const v4 *Ta[RT];
-    v4 tl[RT][4];   // T<[.][col(i, q)]
+    const int tile = blockIdx.x / BPT, b0 = (blockIdx.x % BPT * NW + wave) * NBW;
+    if (row_atom(fr, tile * 16) < 0) return;   // padding rows only
+    const real *Wl = W + (long)row_type(fr, tile * 16) * fr.w_out;   // [b][tile][piece]
+    real *S = reinterpret_cast<real *>(smem_raw);                     // [tile][piece]
+    for (int k = wave; k < nt; k += NW) N::put(S + k * kPiece, lane, N::get(dz1 + ((long)tile * nt + k) * kPiece, lane));
+    const int atom = row_atom(fr, tile * 16 + r);
+    const v4 *Ta = reinterpret_cast<const v4 *>(T) + (long)(atom >= 0 ? atom : 0) * kM;
+    v4 tl[4];   // T<[.][col(i, q)]
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++) {
-        atom[rt] = tile0 + rt < nrt ? row_atom(fr, (tile0 + rt) * 16 + r) : -1;
-        Ta[rt] = reinterpret_cast<const v4 *>(T) + (long)(atom[rt] >= 0 ? atom[rt] : 0) * kM;
-#pragma unroll
-        for (int i = 0; i < 4; i++) tl[rt][i] = Ta[rt][N::col(i, q)];
-    }
-    const int nr = (nt + PD - 1) / PD * PD;
+    for (int i = 0; i < 4; i++) tl[i] = Ta[N::col(i, q)];
+    const int nk = NTC ? NTC : nt, nr = (nk + PD - 1) / PD * PD;
     v4 w[PD][2];
     auto load = [&](int b, int kt, int u) {
         const real *p = Wl + ((long)b * nt + min(kt, nt - 1)) * kPiece;
@@ -430,102 +430,84 @@ __global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr
     };
 #pragma unroll
     for (int u = 0; u < PD; u++) load(b0, u, u);
+    // (everything read so far has arrived: no wait for it is left in the loops)
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    v4 n[RT];   // the operand of the next k tile
+    v4 x, xn = N::get(S, lane);   // the operand of this and of the next k tile
+    v4 acc2[4], tot2[4];   // dT2[.][col(i, q)]
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++) n[rt] = N::get(S + rt * kPiece, lane);
-    v4 acc2[RT][4], tot2[RT][4];   // dT2[.][col(i, q)]
-#pragma unroll
-    for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) tot2[rt][i] = v4{0, 0, 0, 0};
+    for (int i = 0; i < 4; i++) tot2[i] = v4{0, 0, 0, 0};
     for (int g = 0; g < NBW; g += kOutB0) {
 #pragma unroll
-        for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) acc2[rt][i] = v4{0, 0, 0, 0};
+        for (int i = 0; i < 4; i++) acc2[i] = v4{0, 0, 0, 0};
         for (int h = 0; h < kOutB0; h += 2) {
             const int b = b0 + g + h;
-            v4 c[2][RT], tb[2][RT];
+            const v4 tb[2] = {Ta[b], Ta[b + 1]};
+            v4 c[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
+            auto step = [&](int kt, int u) {
+                if (NTC || kt < nk) {
+                    x = xn;
+                    xn = N::get(S + (kt + 1 < nk ? kt + 1 : 0) * kPiece, lane);
 #pragma unroll
-            for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    tb[u][rt] = Ta[rt][b + u];
-                    c[u][rt] = v4{0, 0, 0, 0};
-                }
-            for (int k0 = 0; k0 < nr; k0 += PD) {
-#pragma unroll
-                for (int u = 0; u < PD; u++) {
-                            if (k0 + u < nt) {
-                        v4 x[RT];
-#pragma unroll
-                        for (int rt = 0; rt < RT; rt++) {
-                            x[rt] = n[rt];
-                            n[rt] = N::get(S + ((k0 + u + 1 < nt ? k0 + u + 1 : 0) * RT + rt) * kPiece, lane);
-                        }
-#pragma unroll
-                        for (int i = 0; i < 4; i++)
-#pragma unroll
-                            for (int rt = 0; rt < RT; rt++) {
-                                c[0][rt] = N::mfma(w[u][0][i], x[rt][i], c[0][rt]);
-                                c[1][rt] = N::mfma(w[u][1][i], x[rt][i], c[1][rt]);
-                            }
+                    for (int i = 0; i < 4; i++) {
+                        c[0] = N::mfma(w[u][0][i], x[i], c[0]);
+                        c[1] = N::mfma(w[u][1][i], x[i], c[1]);
                     }
-                    const int kn = k0 + u + PD;
-                    if (kn < nr) load(b, kn, u);
-                    else load(min(b + 2, b0 + NBW - 2), kn - nr, u);
-                    keep_order();
                 }
+                if (kt + PD < nr) load(b, kt + PD, u);
+                else load(min(b + 2, b0 + NBW - 2), kt + PD - nr, u);
+                keep_order();
+            };
+            if constexpr (NTC) {
+                static_assert(NTC % PD == 0, "whole turns of the ring");
+#pragma unroll
+                for (int kt = 0; kt < NTC; kt++) step(kt, kt % PD);
+            } else {
+                for (int k0 = 0; k0 < nr; k0 += PD)
+#pragma unroll
+                    for (int u = 0; u < PD; u++) step(k0 + u, u);
             }
 #pragma unroll
-            for (int rt = 0; rt < RT; rt++)
+            for (int u = 0; u < 2; u++) {
+                const v4 cc = c[u];
+                real p[4];
 #pragma unroll
-                for (int u = 0; u < 2; u++) {
-                    const v4 cc = c[u][rt];
-                    real p[4];
+                for (int k = 0; k < 4; k++) {
+                    real s = cc[0] * tl[0][k];
 #pragma unroll
-                    for (int k = 0; k < 4; k++) {
-                        real s = cc[0] * tl[rt][0][k];
-#pragma unroll
-                        for (int i = 1; i < 4; i++) s = fma(cc[i], tl[rt][i][k], s);
-                        p[k] = s;
-                    }
-#pragma unroll
-                    for (int i = 0; i < 4; i++)
-#pragma unroll
-                        for (int k = 0; k < 4; k++) acc2[rt][i][k] = fma(cc[i], tb[u][rt][k], acc2[rt][i][k]);
-                    const real v = swap_add<true>(swap_add<false>(p[0], p[1]), swap_add<false>(p[2], p[3]));
-                    if (atom[rt] >= 0) dT[((long)atom[rt] * kM + b + u) * 4 + q] = v;
+                    for (int i = 1; i < 4; i++) s = fma(cc[i], tl[i][k], s);
+                    p[k] = s;
                 }
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+#pragma unroll
+                    for (int k = 0; k < 4; k++) acc2[i][k] = fma(cc[i], tb[u][k], acc2[i][k]);
+                const real v = swap_add<true>(swap_add<false>(p[0], p[1]), swap_add<false>(p[2], p[3]));
+                if (atom >= 0) dT[((long)atom * kM + b + u) * 4 + q] = v;
+            }
         }
 #pragma unroll
-        for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                if (!SPLIT) tot2[rt][i] += acc2[rt][i];
-                else if (atom[rt] >= 0)
-                    reinterpret_cast<v4 *>(part)[((long)((b0 + g) / kOutB0) * natoms + atom[rt]) * 16 + N::col(i, q)] =
-                        acc2[rt][i];
-            }
+        for (int i = 0; i < 4; i++) {
+            if (!SPLIT) tot2[i] += acc2[i];
+            else if (atom >= 0)
+                reinterpret_cast<v4 *>(part)[((long)((b0 + g) / kOutB0) * natoms + atom) * 16 + N::col(i, q)] = acc2[i];
+        }
     }
     if (SPLIT) return;
     // the eight waves' sums in wave order, through LDS, a quarter of them at a time
     v4 *X = reinterpret_cast<v4 *>(smem_raw);
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++)
+    for (int i = 0; i < 4; i++) {
+        __syncthreads();
+        X[wave * 64 + lane] = tot2[i];
+        __syncthreads();
+        if (wave == i) {
+            v4 s = X[lane];
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            __syncthreads();
-            X[wave * 64 + lane] = tot2[rt][i];
-            __syncthreads();
-            if (wave == i) {
-                v4 s = X[lane];
-#pragma unroll
-                for (int w = 1; w < NW; w++) s += X[w * 64 + lane];
-                if (atom[rt] >= 0) reinterpret_cast<v4 *>(part)[(long)atom[rt] * 16 + N::col(i, q)] = s;
-            }
+            for (int w = 1; w < NW; w++) s += X[w * 64 + lane];
+            if (atom >= 0) reinterpret_cast<v4 *>(part)[(long)atom * 16 + N::col(i, q)] = s;
         }
+    }
 }
 
 // Rows of 16 that a launch covers.
@@ -563,12 +545,18 @@ void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z,
         hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT)), dim3(64 * nt), (size_t)2 * nt * RT * kPiece * sizeof(real), st, fr,
                            nrt, nt, zt, parts, z, (const real *)W, fb, tanh_tab, e_atom, dz1);
     };
-    if (nrt <= 512) {   // two row tiles to a block once there are two blocks for every CU
-        if (tanh_tab) go(k_fit_mid<real, 1, 5, true>, 1);
-        else go(k_fit_mid<real, 1, 5, false>, 1);
+    // two row tiles to a block once there are two blocks for every CU; widths
+    // of 15 tiles (225 to 240, the paper's 240 among them) have loops of their own
+    const int RT = nrt <= 512 ? 1 : 2;
+    if (nt == 15 && !tanh_tab) {
+        if (RT == 1) go(k_fit_mid<real, 1, 5, 15, false>, 1);
+        else go(k_fit_mid<real, 2, 3, 15, false>, 2);
+    } else if (!tanh_tab) {
+        if (RT == 1) go(k_fit_mid<real, 1, 5, 0, false>, 1);
+        else go(k_fit_mid<real, 2, 3, 0, false>, 2);
     } else {
-        if (tanh_tab) go(k_fit_mid<real, 2, 3, true>, 2);
-        else go(k_fit_mid<real, 2, 3, false>, 2);
+        if (RT == 1) go(k_fit_mid<real, 1, 5, 0, true>, 1);
+        else go(k_fit_mid<real, 2, 3, 0, true>, 2);
     }
 }
 template void launch_fit_mid<double>(const FitRows &, int, int, int, const double *, const void *, const double *,
@@ -589,8 +577,14 @@ void launch_fit_out(const FitRows &fr, int nt, long natoms, const real *dz1, con
         hipLaunchKernelGGL(kern, dim3(nrt * bpt), dim3(64 * waves), lds, st, fr, nrt, nt, natoms, dz1, T, (const real *)W,
                            dT, part);
     };
-    if (fit_out_parts(fr) > 1) go(k_fit_out<real, true, 3>, kM / (kOutB0 * out_waves<true>), out_waves<true>);
-    else go(k_fit_out<real, false, 3>, 1, out_waves<false>);
+    constexpr int bpt = kM / (kOutB0 * out_waves<true>);
+    if (fit_out_parts(fr) > 1) {
+        if (nt == 15) go(k_fit_out<real, true, 3, 15>, bpt, out_waves<true>);
+        else go(k_fit_out<real, true, 3, 0>, bpt, out_waves<true>);
+    } else {
+        if (nt == 15) go(k_fit_out<real, false, 3, 15>, 1, out_waves<false>);
+        else go(k_fit_out<real, false, 3, 0>, 1, out_waves<false>);
+    }
 }
 template void launch_fit_out<double>(const FitRows &, int, long, const double *, const double *, const void *, double *,
                                      double *, hipStream_t);
