@@ -351,7 +351,6 @@ struct FitRows {
     long w_in = 0, w_mid = 0, w_out = 0;
 };
 constexpr int kFitSegs = 4;      // segments of K of the first layer, summed in order (FP64, FP32)
-constexpr int kOutParts = 32;    // innermost sums of the part of dE/dT that runs over all columns
 // FP64: z [fit_in_parts][row tile][nt][256], the first layer's sums before bias and tanh
 int fit_in_parts(const FitRows &fr);
 void launch_fit_in(const FitRows &fr, int nt, const double *T, const void *W, double *z, hipStream_t st);

@@ -102,105 +102,158 @@ template <> struct Net<float> {
 };
 constexpr int kPiece = 256;   // reals of a tile
 
-// ------------------------------------------------------------ first layer
-// One wave: RT row tiles x CT column tiles, one part of K.  K step (b, s):
-// a = col(s, q) in lane group q.  The weights and T columns of the next PD
-// values of b are in flight.
-template <int RT, int CT, int PD>
-__global__ void __launch_bounds__(256, 2) k_fit_in(FitRows fr, int nrt, int nt, int nparts,
-                                                   const double *__restrict__ T, const double *__restrict__ W,
-                                                   double *__restrict__ z)
-{
-    using real = double;
-    using N = Net<real>;
-    using v4 = typename N::v4;
-    constexpr int kSegB = kM / kFitSegs;   // columns b of a segment of K
-    static_assert(kSegB % PD == 0, "a segment is a whole number of turns of the ring");
-    const int wave = wave_id(), lane = threadIdx.x & 63;
-    const int r = lane & 15, q = lane >> 4;
-    const int ncg = (nt + CT - 1) / CT, nrg = (nrt + RT - 1) / RT, nrb = (nrg + 3) / 4;
-    // the column groups of one row block on consecutive slots of one XCD
-    int item = xcd_item(blockIdx.x, gridDim.x);
-    if (item >= nrb * ncg * nparts) return;
-    const int t0 = item % ncg * CT;
-    item /= ncg;
-    const int part = item % nparts, rg = item / nparts * 4 + wave;
-    if (rg >= nrg) return;
+// ------------------------------------------------------ first layer, FP64
+// One block per RT row tiles and part of K, wave w owns output tile w.  K step
+// (b, s): a = col(s, q) in lane group q.  D of the chunk's kInItems (row tile,
+// b) pairs is formed once per block, for the next chunk while the products of
+// the present one run, and read by all waves from LDS: formed by every wave for
+// its own columns, as FP64 vector and matrix instructions share a pipe, it cost
+// 8 % of the products (five groups of three column tiles).  The weights of the
+// next PD values of b are in flight.  WHOLE: all of K in one block, segment
+// after segment; else the block's part is one segment.
+constexpr int kInItems = 16;
 
-    const v4 *Trow[RT];
-    real tl[RT][4][4];   // T<[k][col(s, q)]
-    bool any = false;
+template <int RT, bool WHOLE>
+__global__ void __launch_bounds__(1024) k_fit_in(FitRows fr, int nrt, int nt, const double *__restrict__ T,
+                                                 const double *__restrict__ W, double *__restrict__ z)
+{
+    using N = Net<double>;
+    using v4 = N::v4;
+    HIP_DYNAMIC_SHARED(uint4, smem_raw)
+    constexpr int KC = kInItems / RT;                       // b of a chunk
+    constexpr int kSegB = kM / kFitSegs;                    // b of a segment
+    constexpr int PD = RT == 4 ? 2 : 4, NB = WHOLE ? kM : kSegB, NP = WHOLE ? 1 : kFitSegs;
+    static_assert(kSegB % KC == 0 && KC % PD == 0, "whole chunks, whole turns of the ring");
+    const int wave = wave_id(), lane = threadIdx.x & 63;   // wave < nt <= 16
+    const int r = lane & 15, q = lane >> 4;
+    const int part = blockIdx.x % NP, tile0 = blockIdx.x / NP * RT;
+    if (row_atom(fr, tile0 * 16) < 0) return;   // padding rows only
+    double *Db = reinterpret_cast<double *>(smem_raw);         // [2][item][piece]
+    v4 *Tl = reinterpret_cast<v4 *>(Db + 2 * kInItems * kPiece);   // [RT][4][64]: T(a = col(s, q))
+    const v4 *Tg = reinterpret_cast<const v4 *>(T);
+    auto atom_of = [&](int t) { return tile0 + t < nrt ? row_atom(fr, (tile0 + t) * 16 + r) : -1; };
+    const double *Wl = W + (long)row_type(fr, tile0 * 16) * fr.w_in + (long)wave * kPiece;   // [b][tile][piece]
+    const int b0 = part * NB;
+    v4 w[PD];
+    auto load_w = [&](int b, int u) { w[u] = N::get(Wl + (long)b * nt * kPiece, lane); };
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++) {
-        const int tile = rg * RT + rt;
-        const int atom = tile < nrt ? row_atom(fr, tile * 16 + r) : -1;
-        any = any || atom >= 0;
-        Trow[rt] = reinterpret_cast<const v4 *>(T) + (long)(atom >= 0 ? atom : 0) * kM;
+    for (int u = 0; u < PD; u++) load_w(b0 + u, u);
+    // item it: row tile it % RT, b = chunk's first + it / RT; this wave forms it0 and it0 + nt, ..
+    auto load_t = [&](int it, int b) {
+        const int at = atom_of(it % RT);
+        return Tg[(long)(at >= 0 ? at : 0) * kM + b + it / RT];
+    };
+    auto put_d = [&](int it, const v4 &tb, double *buf) {
+        v4 d;
 #pragma unroll
         for (int s = 0; s < 4; s++) {
-            v4 t = Trow[rt][N::col(s, q)];
+            const v4 t = Tl[((it % RT) * 4 + s) * 64 + lane];
+            double x = t[0] * tb[0];
 #pragma unroll
-            for (int k = 0; k < 4; k++) tl[rt][s][k] = atom >= 0 ? t[k] : (real)0;
+            for (int k = 1; k < 4; k++) x = fma(t[k], tb[k], x);
+            d[s] = x;
         }
-    }
-    if (__ballot(any) == 0) return;   // tiles of padding rows only
-    const real *Wl = W + (long)row_type(fr, rg * RT * 16) * fr.w_in;   // [b][tile][piece]
-    v4 w[PD][CT], tb[PD][RT];
-    auto load = [&](int b, int u) {
-#pragma unroll
-        for (int c = 0; c < CT; c++)   // tiles past the last are computed on the last one and not stored
-            w[u][c] = N::get(Wl + ((long)b * nt + min(t0 + c, nt - 1)) * kPiece, lane);
-#pragma unroll
-        for (int rt = 0; rt < RT; rt++) tb[u][rt] = Trow[rt][b];
+        N::put(buf + it * kPiece, lane, d);
     };
-    v4 acc[RT][CT], tot[RT][CT];
+    v4 tb = load_t(wave, b0);
+    // the chunk at b into buf; then the load of the one after it
+    auto put_chunk = [&](int b, double *buf) {
+        put_d(wave, tb, buf);
+        for (int it = wave + nt; it < kInItems; it += nt) put_d(it, load_t(it, b), buf);
+        if (b + KC < b0 + NB) tb = load_t(wave, b + KC);
+    };
+    // the four waves of a SIMD do that at different times, so that the others'
+    // products go on (all at once, at the barrier, left the matrix cores idle)
+    const int turn = (wave >> 2) * (KC / 4);
+    for (int k = wave; k < RT * 4; k += nt) {
+        const int at = atom_of(k >> 2);
+        const v4 v = Tg[(long)(at >= 0 ? at : 0) * kM + N::col(k & 3, q)];
+        Tl[k * 64 + lane] = at >= 0 ? v : v4{0, 0, 0, 0};   // rows without an atom: D = 0
+    }
+    v4 acc[RT], tot[RT];
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++)
+    for (int t = 0; t < RT; t++) acc[t] = tot[t] = v4{0, 0, 0, 0};
+    __syncthreads();
+    put_chunk(b0, Db);
+    __syncthreads();
+    for (int b = b0; b < b0 + NB; b += KC) {
+        const int buf = ((b - b0) / KC) & 1;
+        const bool more = b + KC < b0 + NB;
+        const double *D = Db + buf * kInItems * kPiece;
 #pragma unroll
-        for (int c = 0; c < CT; c++) acc[rt][c] = tot[rt][c] = v4{0, 0, 0, 0};
-    const int b0 = part * (kM / nparts), b1 = b0 + kM / nparts;
+        for (int k = 0; k < KC; k++) {
+            if (k % (KC / 4) == 0 && more && k == turn) put_chunk(b + KC, Db + (buf ^ 1) * kInItems * kPiece);
+            v4 x[RT];
+#pragma unroll
+            for (int t = 0; t < RT; t++) x[t] = N::get(D + (k * RT + t) * kPiece, lane);
+#pragma unroll
+            for (int s = 0; s < 4; s++)
+#pragma unroll
+                for (int t = 0; t < RT; t++) acc[t] = N::mfma(w[k % PD][s], x[t][s], acc[t]);
+            load_w(min(b + k + PD, b0 + NB - 1), k % PD);
+            keep_order();
+        }
+        if (WHOLE && (b + KC) % kSegB == 0) {
+#pragma unroll
+            for (int t = 0; t < RT; t++) {
+                tot[t] += acc[t];
+                acc[t] = v4{0, 0, 0, 0};
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < RT; t++)
+        if (tile0 + t < nrt)
+            N::put(z + ((long)(part * nrt + tile0 + t) * nt + wave) * kPiece, lane, WHOLE ? tot[t] : acc[t]);
+}
+
+// The same for few rows: one wave per row tile, output tile and segment of K,
+// D formed in its registers (four waves of a block share the weights).
+__global__ void __launch_bounds__(256) k_fit_in_few(FitRows fr, int nrt, int nt, const double *__restrict__ T,
+                                                    const double *__restrict__ W, double *__restrict__ z)
+{
+    using N = Net<double>;
+    using v4 = N::v4;
+    constexpr int PD = 4, NB = kM / kFitSegs;
+    const int wave = wave_id(), lane = threadIdx.x & 63;
+    const int r = lane & 15, q = lane >> 4;
+    int item = xcd_item(blockIdx.x, gridDim.x);   // the column tiles of one row block on one XCD
+    if (item >= (nrt + 3) / 4 * nt * kFitSegs) return;
+    const int ct = item % nt;
+    item /= nt;
+    const int part = item % kFitSegs, tile = item / kFitSegs * 4 + wave;
+    if (tile >= nrt || row_atom(fr, tile * 16) < 0) return;   // beyond the rows, or padding
+    const int atom = row_atom(fr, tile * 16 + r);
+    const v4 *Trow = reinterpret_cast<const v4 *>(T) + (long)(atom >= 0 ? atom : 0) * kM;
+    const double *Wl = W + (long)row_type(fr, tile * 16) * fr.w_in + (long)ct * kPiece;
+    const int b0 = part * NB, b1 = b0 + NB;
+    v4 tl[4], w[PD], tb[PD], acc = v4{0, 0, 0, 0};
+    auto load = [&](int b, int u) {
+        w[u] = N::get(Wl + (long)b * nt * kPiece, lane);
+        tb[u] = Trow[b];
+    };
 #pragma unroll
     for (int u = 0; u < PD; u++) load(b0 + u, u);
-    for (int b = b0; b < b1; b += PD) {
+#pragma unroll
+    for (int s = 0; s < 4; s++) {
+        tl[s] = Trow[N::col(s, q)];
+        if (atom < 0) tl[s] = v4{0, 0, 0, 0};
+    }
+    for (int b = b0; b < b1; b += PD)
 #pragma unroll
         for (int u = 0; u < PD; u++) {
 #pragma unroll
             for (int s = 0; s < 4; s++) {
-                real d[RT];
+                double x = tl[s][0] * tb[u][0];
 #pragma unroll
-                for (int rt = 0; rt < RT; rt++) {
-                    real x = tl[rt][s][0] * tb[u][rt][0];
-#pragma unroll
-                    for (int k = 1; k < 4; k++) x = fma(tl[rt][s][k], tb[u][rt][k], x);
-                    d[rt] = x;
-                }
-#pragma unroll
-                for (int c = 0; c < CT; c++)
-#pragma unroll
-                    for (int rt = 0; rt < RT; rt++) acc[rt][c] = N::mfma(w[u][c][s], d[rt], acc[rt][c]);
+                for (int k = 1; k < 4; k++) x = fma(tl[s][k], tb[u][k], x);
+                acc = N::mfma(w[u][s], x, acc);
             }
             load(min(b + u + PD, b1 - 1), u);
             keep_order();
         }
-        if ((b + PD) % kSegB == 0) {
-#pragma unroll
-            for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-                for (int c = 0; c < CT; c++) {
-                    tot[rt][c] += acc[rt][c];
-                    acc[rt][c] = v4{0, 0, 0, 0};
-                }
-        }
-    }
-#pragma unroll
-    for (int rt = 0; rt < RT; rt++) {
-        const int tile = rg * RT + rt;
-        if (tile >= nrt) break;
-#pragma unroll
-        for (int c = 0; c < CT; c++)
-            if (t0 + c < nt)
-                N::put(z + ((long)(part * nrt + tile) * nt + t0 + c) * kPiece, lane, tot[rt][c]);
-    }
+    N::put(z + ((long)(part * nrt + tile) * nt + ct) * kPiece, lane, acc);
 }
 
 // --------------------------------------------------- the 256-wide layers
@@ -391,15 +444,15 @@ __device__ inline double swap_add(double a, double b)
 constexpr int kOutB0 = 4;    // b of the innermost sums of dT2
 constexpr int kOutB1 = 16;   // b of the middle ones
 
-// SPLIT: a wave takes kOutB0 columns and writes its dT2 to part[b / 4] of
-// kOutParts; else a wave takes kOutB1, the block (8 waves) all 128, and part
-// holds the one sum.  part: [part][atom][16 a][4 k].  The weights of the next
-// PD k tiles are in flight, across the pairs of b.
-template <bool SPLIT>
-constexpr int out_waves = SPLIT ? 4 : 8;
+// A wave takes NBW columns.  LEVEL 0: it writes the sums over kOutB0 of them
+// (32 parts); 1: over kOutB1 (8 parts, NBW = kOutB1); 2: the block's eight waves
+// cover all 128 and add theirs (one part, NBW = kOutB1).  part: [part][atom][16
+// a][4 k].  The weights of the next PD k tiles are in flight, across the pairs
+// of b.
+constexpr int out_waves(int level) { return level == 2 ? 8 : 4; }
 
-template <typename real, bool SPLIT, int PD, int NTC>
-__global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr, int nrt, int nt, long natoms,
+template <typename real, int LEVEL, int NBW, int NTC>
+__global__ void __launch_bounds__(64 * out_waves(LEVEL), 2) k_fit_out(FitRows fr, int nrt, int nt, long natoms,
                                                                       const real *__restrict__ dz1,
                                                                       const real *__restrict__ T,
                                                                       const real *__restrict__ W, real *__restrict__ dT,
@@ -408,7 +461,7 @@ __global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr
     using N = Net<real>;
     using v4 = typename N::v4;
     HIP_DYNAMIC_SHARED(uint4, smem_raw)
-    constexpr int NW = out_waves<SPLIT>, NBW = SPLIT ? kOutB0 : kOutB1, BPT = kM / (NBW * NW);   // blocks per row tile
+    constexpr int NW = out_waves(LEVEL), BPT = kM / (NBW * NW), PD = 3;   // blocks per row tile
     const int wave = wave_id(), lane = threadIdx.x & 63;
     const int r = lane & 15, q = lane >> 4;
     const int tile = blockIdx.x / BPT, b0 = (blockIdx.x % BPT * NW + wave) * NBW;
@@ -488,12 +541,19 @@ __global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr
         }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            if (!SPLIT) tot2[i] += acc2[i];
+            if (LEVEL > 0) tot2[i] += acc2[i];
             else if (atom >= 0)
                 reinterpret_cast<v4 *>(part)[((long)((b0 + g) / kOutB0) * natoms + atom) * 16 + N::col(i, q)] = acc2[i];
         }
     }
-    if (SPLIT) return;
+    if (LEVEL == 0) return;
+    if (LEVEL == 1) {
+        if (atom >= 0)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                reinterpret_cast<v4 *>(part)[((long)(b0 / kOutB1) * natoms + atom) * 16 + N::col(i, q)] = tot2[i];
+        return;
+    }
     // the eight waves' sums in wave order, through LDS, a quarter of them at a time
     v4 *X = reinterpret_cast<v4 *>(smem_raw);
 #pragma unroll
@@ -513,27 +573,31 @@ __global__ void __launch_bounds__(64 * out_waves<SPLIT>, 2) k_fit_out(FitRows fr
 // Rows of 16 that a launch covers.
 int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
 
-// Row tiles up to which the input gradient's innermost column groups go to
-// waves of their own, their sums added by the kernel that reads dE/dT.
-constexpr int kOutSplitTiles = 256;
-// The same for the first layer's segments of K (FP64).
-constexpr int kInSplitTiles = 1250;
+// Row tiles from which on the first layer's (FP64) K stays whole, and up to
+// which it is left to single waves.
+constexpr int kInWholeTiles = 1250, kInFewTiles = 48;
+// Row tiles up to which the input gradient's sums over all columns are left
+// in 32 parts (a wave has 4 columns, then 8), and in 8 parts.
+constexpr int kOut4Tiles = 64, kOut32Tiles = 256, kOut8Tiles = 1024;
 
 }  // namespace
 
 // ----------------------------------------------------------- launchers
-int fit_in_parts(const FitRows &fr) { return row_tiles(fr) <= kInSplitTiles ? kFitSegs : 1; }
+int fit_in_parts(const FitRows &fr) { return row_tiles(fr) < kInWholeTiles ? kFitSegs : 1; }
 
 void launch_fit_in(const FitRows &fr, int nt, const double *T, const void *W, double *z, hipStream_t st)
 {
-    const int nrt = row_tiles(fr), parts = fit_in_parts(fr);
-    auto go = [&](auto kern, int RT, int CT) {
-        int items = div_up(div_up(nrt, RT), 4) * div_up(nt, CT) * parts;
-        hipLaunchKernelGGL(kern, dim3(xcd_grid(items)), dim3(256), 0, st, fr, nrt, nt, parts, T, (const double *)W, z);
+    const int nrt = row_tiles(fr);
+    auto go = [&](auto kern, int RT, int parts) {
+        const size_t lds = (size_t)(2 * kInItems + 4 * RT) * kPiece * sizeof(double);
+        hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT) * parts), dim3(64 * nt), lds, st, fr, nrt, nt, T, (const double *)W, z);
     };
-    // single tiles while they are fewer than two waves for every SIMD
-    if (nrt * div_up(nt, 3) * parts < 2048) go(k_fit_in<1, 1, 4>, 1, 1);
-    else go(k_fit_in<2, 3, 2>, 2, 3);
+    if (nrt <= kInFewTiles)
+        hipLaunchKernelGGL(k_fit_in_few, dim3(xcd_grid(div_up(nrt, 4) * nt * kFitSegs)), dim3(256), 0, st, fr, nrt, nt, T,
+                           (const double *)W, z);
+    else if (nrt < 512) go(k_fit_in<1, false>, 1, kFitSegs);
+    else if (nrt < kInWholeTiles) go(k_fit_in<2, false>, 2, kFitSegs);
+    else go(k_fit_in<4, true>, 4, 1);
 }
 
 template <typename real>
@@ -564,27 +628,33 @@ template void launch_fit_mid<double>(const FitRows &, int, int, int, const doubl
 template void launch_fit_mid<float>(const FitRows &, int, int, int, const float *, const void *, const float *,
                                     const float *, double *, float *, hipStream_t);
 
-int fit_out_parts(const FitRows &fr) { return row_tiles(fr) <= kOutSplitTiles ? kOutParts : 1; }
+int fit_out_parts(const FitRows &fr)
+{
+    const int nrt = row_tiles(fr);
+    return nrt <= kOut32Tiles ? kM / kOutB0 : nrt <= kOut8Tiles ? kM / kOutB1 : 1;
+}
 
 template <typename real>
 void launch_fit_out(const FitRows &fr, int nt, long natoms, const real *dz1, const real *T, const void *W, real *dT,
                     real *part, hipStream_t st)
 {
     const int nrt = row_tiles(fr);
-    auto go = [&](auto kern, int bpt, int waves) {
+    auto go = [&](auto kern, int level, int nbw) {
         // the combination of the waves' sums takes 8 pieces, dz1 one per tile
         const size_t lds = (size_t)std::max(nt, 8) * kPiece * sizeof(real);
-        hipLaunchKernelGGL(kern, dim3(nrt * bpt), dim3(64 * waves), lds, st, fr, nrt, nt, natoms, dz1, T, (const real *)W,
-                           dT, part);
+        const int waves = out_waves(level);
+        hipLaunchKernelGGL(kern, dim3(nrt * (kM / (nbw * waves))), dim3(64 * waves), lds, st, fr, nrt, nt, natoms, dz1, T,
+                           (const real *)W, dT, part);
     };
-    constexpr int bpt = kM / (kOutB0 * out_waves<true>);
-    if (fit_out_parts(fr) > 1) {
-        if (nt == 15) go(k_fit_out<real, true, 3, 15>, bpt, out_waves<true>);
-        else go(k_fit_out<real, true, 3, 0>, bpt, out_waves<true>);
-    } else {
-        if (nt == 15) go(k_fit_out<real, false, 3, 15>, 1, out_waves<false>);
-        else go(k_fit_out<real, false, 3, 0>, 1, out_waves<false>);
-    }
+    auto pick = [&](auto ntc) {
+        constexpr int NTC = decltype(ntc)::value;
+        if (nrt <= kOut4Tiles) go(k_fit_out<real, 0, 4, NTC>, 0, 4);
+        else if (nrt <= kOut32Tiles) go(k_fit_out<real, 0, 8, NTC>, 0, 8);
+        else if (nrt <= kOut8Tiles) go(k_fit_out<real, 1, 16, NTC>, 1, 16);
+        else go(k_fit_out<real, 2, 16, NTC>, 2, 16);
+    };
+    if (nt == 15) pick(std::integral_constant<int, 15>());
+    else pick(std::integral_constant<int, 0>());
 }
 template void launch_fit_out<double>(const FitRows &, int, long, const double *, const double *, const void *, double *,
                                      double *, hipStream_t);

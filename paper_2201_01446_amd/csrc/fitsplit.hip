@@ -163,7 +163,11 @@ __global__ void __launch_bounds__(512) k_split_in(FitRows fr, int nrt, int ks, i
             load_t(it, bp, tb);
             put_d(it, tb, buf);
         }
+        if (bp + KC < s1) load_chunk(bp + KC);
     };
+    // the two waves of a SIMD do that at different times, so that the other's
+    // products go on
+    const int turn = (wave >> 2) * (KC / 2);
     // weights [K step][tile][part][lane], two K steps ahead
     const bf8v *Wl = W + (long)ty * fr.w_in + (long)wave * 2 * NP * 64;
     bf8v w[2][2][NP];
@@ -191,10 +195,10 @@ __global__ void __launch_bounds__(512) k_split_in(FitRows fr, int nrt, int ks, i
     for (int s = s0; s < s1; s += KC) {
         const int buf = ((s - s0) / KC) & 1;
         const bool more = s + KC < s1;
-        if (more) load_chunk(s + KC);
         const bf8v *D = Db + buf * kInItems * NP * 64;
 #pragma unroll 2
         for (int k = 0; k < KC; k += 2) {
+            if (more && k == turn) put_chunk(s + KC, Db + (buf ^ 1) * kInItems * NP * 64);
 #pragma unroll
             for (int u = 0; u < 2; u++) {
                 bf8v x[RT][NP];
@@ -216,7 +220,6 @@ __global__ void __launch_bounds__(512) k_split_in(FitRows fr, int nrt, int ks, i
                     acc[c][t] = f4v{0, 0, 0, 0};
                 }
         }
-        if (more) put_chunk(s + KC, Db + (buf ^ 1) * kInItems * NP * 64);
         __syncthreads();
     }
 #pragma unroll
@@ -329,12 +332,19 @@ __global__ void __launch_bounds__(512) k_mix_in(FitRows fr, int nrt, int ks, con
     __syncthreads();
     put_chunk(0, false, Db);
     __syncthreads();
+    // the two waves of a SIMD form the next chunk at different times, so that the
+    // other's products go on
+    const int turn = (wave >> 2) * (KC / 2);
     constexpr int NCH = 3 * kMixSteps / KC, CPP = kMixSteps / KC;   // chunks, chunks of a pass
     for (int ch = 0; ch < NCH; ch++) {
         const bf8v *D = Db + (ch & 1) * KC * RT * 64;
+        const bool more = ch + 1 < NCH;
+        auto put_next = [&] { put_chunk((ch + 1) % CPP * AC, ch + 1 >= 2 * CPP, Db + ((ch + 1) & 1) * KC * RT * 64); };
+        if (!mine && more) put_next();
         if (mine) {
 #pragma unroll
             for (int k = 0; k < KC; k++) {
+                if (k % (KC / 2) == 0 && more && k == turn) put_next();
 #pragma unroll
                 for (int t = 0; t < RT; t++) {
                     const bf8v x = D[(k * RT + t) * 64 + lane];
@@ -346,7 +356,6 @@ __global__ void __launch_bounds__(512) k_mix_in(FitRows fr, int nrt, int ks, con
                 keep_order();
             }
         }
-        if (ch + 1 < NCH) put_chunk((ch + 1) % CPP * AC, ch + 1 >= 2 * CPP, Db + ((ch + 1) & 1) * KC * RT * 64);
         __syncthreads();
     }
     if (!mine) return;
