@@ -3,6 +3,7 @@
 // kernel launches.  No arithmetic of the model lives here.
 
 #include "dp_internal.h"
+#include "env.h"
 
 #include <algorithm>
 #include <cmath>
@@ -687,7 +688,11 @@ dp_status dp_table_download(dp_model *m, double *coef_h, int *n_int)
     if (n_int) *n_int = n;
     if (coef_h) {
         DP_HIP(hipDeviceSynchronize());
-        DP_HIP(hipMemcpy(coef_h, m->tab64, sizeof(double) * (size_t)m->ntypes * n * kM * 6, hipMemcpyDeviceToHost));
+        std::vector<double> t((size_t)m->ntypes * n * kM * 6);
+        DP_HIP(hipMemcpy(t.data(), m->tab64, sizeof(double) * t.size(), hipMemcpyDeviceToHost));
+        for (size_t b = 0; b < t.size(); b += kM * 6)   // as [interval][column][6]
+            for (int c = 0; c < kM; c++)
+                for (int e = 0; e < 6; e++) coef_h[b + c * 6 + e] = t[b + coef_pos(0.0, e, c)];
     }
     return DP_OK;
 }

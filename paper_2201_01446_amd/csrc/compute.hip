@@ -26,6 +26,7 @@ struct WS {
     void *T, *D, *y1r, *y1o, *y2r, *y2o, *t2r, *t3r, *dz3o, *dy2r, *dz2o, *dz1o, *dDr, *dT;
     void *rec;   // the forward's compacted neighbors (r_ij, j) per atom, sel slots
     int *rcnt;   // their number per atom
+    unsigned short *slots;   // their slots alone, in y2r's place (the compressed step's net leaves it free); or NULL
     double *e_atom, *w_atom, *part;
 };
 
@@ -82,6 +83,7 @@ WS carve(void *base, int np, int precision, int sel)
     w.dT = take(np * 4 * kM * rs);
     w.rec = take((size_t)np * sel * 4 * rs);
     w.rcnt = (int *)take(np * 4);
+    w.slots = sel * sizeof(short) <= kFitPad * rs ? (unsigned short *)w.y2r : nullptr;
     w.e_atom = (double *)take(np * 8);
     w.w_atom = (double *)take(np * 72);
     w.part = (double *)take(256 * 10 * 8);
@@ -197,7 +199,7 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
             bool tab = a.mode == DP_TAB_UNFUSED;
             if ((s = plain_forward<TR, TA>(m, a.nl, n, a.x, w.T, w.D, a.nnei_out, st, tab)) != DP_OK) return s;
         } else if (a.mode == DP_COMPRESSED) {
-            DP_TIMED("emb_fwd", st, launch_emb_fwd(m, a.nl, n, a.x, a.precision, w.T, a.D_out ? w.D : nullptr, w.rec, w.rcnt, a.nnei_out, a.nseg_out, st));
+            DP_TIMED("emb_fwd", st, launch_emb_fwd(m, a.nl, n, a.x, a.precision, w.T, a.D_out ? w.D : nullptr, w.rec, w.rcnt, w.slots, a.nnei_out, a.nseg_out, st));
             if ((s = step_check("emb_fwd", st)) != DP_OK) return s;
         } else {
             bool pad = a.mode == DP_FUSED_PADDED;
@@ -295,7 +297,7 @@ dp_status run_t(const ComputeArgs &a, const WS &w, int np, const FitWeights &fw,
                 bool pad = a.mode == DP_FUSED_PADDED;
                 DP_TIMED("emb_bwd_pn", st, launch_emb_bwd_pn(m, a.nl, n, a.x, a.precision, w.T, w.dDr, w.rec, w.rcnt, pad, a.force, w.w_atom, st));
             }
-            DP_TIMED("force_gather", st, launch_force_gather(m, a.nl, n, a.x, a.precision, w.rec, w.rcnt, a.force, st));
+            DP_TIMED("force_gather", st, launch_force_gather(m, a.nl, n, a.x, a.precision, w.rec, w.rcnt, a.mode == DP_COMPRESSED ? w.slots : nullptr, a.force, st));
             if ((s = step_check("emb_bwd", st)) != DP_OK) return s;
         }
     }

@@ -81,8 +81,8 @@ struct dp_model {
     void *embg32 = nullptr;      // the same in FP32
     // table
     dp::TableInfo tab;
-    double *tab64 = nullptr;     // [ntypes * n_int][M][6]: type t's table at interval t * n_int
-    float *tab32 = nullptr;      // [ntypes * n_int][M][6]
+    double *tab64 = nullptr;     // [ntypes * n_int] blocks of M x 6 (coef_pos): type t's table at interval t * n_int
+    float *tab32 = nullptr;      // the same in FP32
     double *nodes = nullptr;     // scratch [ntypes][n_int+1][M][3] of node values g, g', g''
     // tanh of the fitting net: native, or the second-order table
     // [kTanhN][a0, a1, a2, 0] on [0, 8), in FP64 (FP64 epilogues) and FP32
@@ -396,7 +396,7 @@ void launch_emb_bwd_pn(const dp_model *m, const dp_nlist *nl, int n, const doubl
 // rec/rcnt: the forward's compacted neighbor records (sel slots per atom) and
 // their counts, written by launch_emb_fwd and read by launch_emb_bwd
 void launch_emb_fwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, void *T,
-                    void *D, void *rec, int *rcnt, int *nnei, int *nseg, hipStream_t st);
+                    void *D, void *rec, int *rcnt, unsigned short *slots, int *nnei, int *nseg, hipStream_t st);
 void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, const void *dT,
                     const void *dTp, int nparts, const void *rec, const int *rcnt, double *force, double *w_atom,
                     hipStream_t st);
@@ -439,7 +439,7 @@ void launch_reverse(dp_nlist *nl, int off, int n, hipStream_t st, bool uniq = fa
 // reverse slot (rec / rcnt: the forward's neighbor records); deterministic
 // (fixed order), no atomics.
 void launch_force_gather(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision,
-                         const void *rec, const int *rcnt, double *force, hipStream_t st);
+                         const void *rec, const int *rcnt, const unsigned short *slots, double *force, hipStream_t st);
 size_t ws_bytes_for_atoms(int natoms, int precision, int sel, int ntypes);
 // The static scratch of dp_compute_noalloc: its size in bytes (fixed at
 // build time) and the calling thread's switch that keeps the kernel timers

@@ -38,7 +38,9 @@
 // (the backward's B, computed by the segments' quads in parallel, gains
 // nothing from sharing).
 //
-// Work distribution (one 64-lane wavefront per atom, neighbor data in LDS):
+// Work distribution (one 64-lane wavefront per atom, a block of its own:
+// nothing is shared, and a block of four held its LDS until its slowest wave
+// was done; neighbor data in LDS):
 //   moments and B: quad q of the wave owns one segment per round; for the
 //   moments lane l of the quad takes environment column k = l of every
 //   neighbor of the segment, for B the four lanes split the 128 columns and
@@ -63,20 +65,6 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// The 6 coefficients of column c of interval th (24 bytes, 8-byte aligned).
-__device__ inline void coef_col(const float *tab, int th, int c, float (&a)[6])
-{
-    const float2 *p = reinterpret_cast<const float2 *>(tab + ((long)th * kM + c) * 6);
-    float2 u = p[0], v = p[1], w = p[2];
-    a[0] = u.x; a[1] = u.y; a[2] = v.x; a[3] = v.y; a[4] = w.x; a[5] = w.y;
-}
-__device__ inline void coef_col(const double *tab, int th, int c, double (&a)[6])
-{
-    const double2 *p = reinterpret_cast<const double2 *>(tab + ((long)th * kM + c) * 6);
-    double2 u = p[0], v = p[1], w = p[2];
-    a[0] = u.x; a[1] = u.y; a[2] = v.x; a[3] = v.y; a[4] = w.x; a[5] = w.y;
 }
 
 // f = sum_e a[e] t^e and its derivative.
@@ -123,11 +111,16 @@ __device__ inline int round_reps(const NbrLDS<real> &L, const int *seg, int s0, 
 {
     int thu = lane < ns ? (L.th[seg[s0 + lane]] & ~kOobBit) : -1;
     int rep = lane;
-    for (int v = 0; v < ns; v++) {
-        int thv = __shfl(thu, v);
-        if (v < lane && thv == thu && rep == lane) rep = v;
+    // from the last to the first, so that the first match stays; past ns no
+    // lane matches (-1) but those, which keep themselves below.  Lane reads:
+    // as shuffles these were 32 dependent trips through the LDS a round (the
+    // forward at 108,000 atoms 670 us against 600, FP32).
+#pragma unroll
+    for (int v = kSegRound - 2; v >= 0; v--) {
+        const int thv = __builtin_amdgcn_readlane(thu, v);
+        if (v < lane && thv == thu) rep = v;
     }
-    return rep;
+    return lane < ns ? rep : lane;
 }
 
 // Starts of the runs of equal interval in the neighbor list: seg[0..nseg-1],
@@ -192,28 +185,30 @@ constexpr int bwd_lds_bytes(int sel)
 }
 
 // -------------------------------------------------------------- forward
+// At 108,000 atoms 570 us (FP32) and 960 (FP64), 670 and 1,110 before the
+// lane reads, the blocks of one wave and the coalesced table: the scan with
+// the stores of records and T takes 40-45 %, the contraction 40 %; bound by
+// the instructions of the wave (FP32) and by latency at 3 waves a SIMD (FP64).
 template <typename real, typename TD>
-__global__ void __launch_bounds__(256) k_emb_fwd(int natoms, EnvArgs A, const real *__restrict__ tab,
+__global__ void __launch_bounds__(64) k_emb_fwd(int natoms, EnvArgs A, const real *__restrict__ tab,
                                                  real sigma, real *__restrict__ T_out,
                                                  TD *__restrict__ D_out, int *__restrict__ nnei_out,
                                                  int *__restrict__ nseg_out)
 {
     HIP_DYNAMIC_SHARED(uint4, smem_raw)   // 16-byte aligned
     char *base = reinterpret_cast<char *>(smem_raw);
-    int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int i = xcd_item(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + wave;
-    base += wave * fwd_lds_bytes<real>(A.sel);
+    int lane = threadIdx.x;
+    int i = xcd_item(blockIdx.x, gridDim.x);
+    if (i >= natoms) return;
     NbrLDS<real> L = carve<real>(base, A.sel, ENV_FWD);
     char *p = base + nbr_lds_bytes<real>(A.sel, ENV_FWD);
     real *Tl = reinterpret_cast<real *>(base);   // 4 x M, after the rounds
     real *Ms = reinterpret_cast<real *>(p);   // kSegRound x 24
     p += kSegRound * 24 * sizeof(real);
     int *seg = reinterpret_cast<int *>(p);
-    bool live = i < natoms;
-    int nn = 0, n_in = 0, over = 0, oob = 0;
-    if (live) nn = build_env<real, ENV_FWD>(i, A, L, lane, n_in, over, oob);
-    __syncthreads();
-    if (!live) return;
+    int n_in = 0, over = 0, oob = 0;
+    const int nn = build_env<real, ENV_FWD>(i, A, L, lane, n_in, over, oob);
+    wave_sync();
     int nruns = 0;
     int nseg = find_segments<real, kFwdMaxRun>(L, nn, lane, seg, &nruns);
 
@@ -245,16 +240,15 @@ __global__ void __launch_bounds__(256) k_emb_fwd(int natoms, EnvArgs A, const re
         const unsigned long long reps = __ballot(lane < ns && rep == lane);
         if (reps != ((1ull << ns) - 1ull)) {
             wave_sync();
-            const bool qrep = q < ns && __shfl(rep, q) == q;   // quad q holds a representative
             real add[6] = {0, 0, 0, 0, 0, 0};
-            for (int u = 0; u < ns; u++) {
-                int ru = __shfl(rep, u);
-                if (qrep && ru == q && u != q) {
+            for (unsigned long long rest = ((1ull << ns) - 1ull) & ~reps; rest; rest &= rest - 1) {
+                const int u = __builtin_ctzll(rest);
+                if (__builtin_amdgcn_readlane(rep, u) == q) {
 #pragma unroll
                     for (int e = 0; e < 6; e++) add[e] += Ms[u * 24 + ql * 6 + e];
                 }
             }
-            if (qrep) {
+            if (reps >> q & 1) {   // quad q holds a representative
 #pragma unroll
                 for (int e = 0; e < 6; e++) Ms[q * 24 + ql * 6 + e] += add[e];
             }
@@ -442,18 +436,20 @@ struct DTRegs {
     }
 };
 
+// The registers are those of 2 (FP64) and 4 waves a SIMD: with the 3 that it
+// would choose in FP64 the compiler keeps fewer coefficient loads in flight
+// (1,155 us against 1,010 at 108,000 atoms; 555 in FP32).
 template <typename real>
-__global__ void __launch_bounds__(256) k_emb_bwd(int natoms, EnvArgs A, const real *__restrict__ tab,
-                                                 real sigma, const real *__restrict__ dT,
-                                                 const real *__restrict__ dTp, int nparts,
-                                                 double *__restrict__ force,
-                                                 double *__restrict__ w_atom)
+__global__ void __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(sizeof(real) == 8 ? 2 : 4, sizeof(real) == 8 ? 2 : 4)))
+k_emb_bwd(int natoms, EnvArgs A, const real *__restrict__ tab, real sigma, const real *__restrict__ dT,
+          const real *__restrict__ dTp, int nparts, double *__restrict__ force, double *__restrict__ w_atom)
 {
     HIP_DYNAMIC_SHARED(uint4, smem_raw)   // 16-byte aligned
     char *base = reinterpret_cast<char *>(smem_raw);
-    int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    int i = xcd_item(blockIdx.x, gridDim.x) * (blockDim.x >> 6) + wave;
-    base += wave * bwd_lds_bytes<real>(A.sel);
+    int lane = threadIdx.x;
+    int i = xcd_item(blockIdx.x, gridDim.x);
+    if (i >= natoms) return;
     NbrLDS<real> L = carve<real>(base, A.sel, ENV_BWD);
     char *p = base + nbr_lds_bytes<real>(A.sel, ENV_BWD);
     V4<real> *dTl = reinterpret_cast<V4<real> *>(p);   // per column
@@ -461,15 +457,12 @@ __global__ void __launch_bounds__(256) k_emb_bwd(int natoms, EnvArgs A, const re
     real *Bs = reinterpret_cast<real *>(p);             // kSegRound x 24
     p += kSegRound * 24 * sizeof(real);
     int *seg = reinterpret_cast<int *>(p);
-    bool live = i < natoms;
     // dE/dT into registers first: its loads stream from HBM while the
     // neighbor scan runs
     DTRegs<real> dt;
-    if (live) dt.load(i, natoms, lane, dT, dTp, nparts);
-    int nn = 0;
-    if (live) nn = load_env<real>(i, A, L, lane);
-    __syncthreads();
-    if (!live) return;
+    dt.load(i, natoms, lane, dT, dTp, nparts);
+    const int nn = load_env<real>(i, A, L, lane);
+    wave_sync();
 
     dt.finish(lane, sigma, dTl);
     int nseg = find_segments(L, nn, lane, seg);   // its wave barrier also publishes dT
@@ -555,16 +548,16 @@ __global__ void __launch_bounds__(256) k_emb_bwd(int natoms, EnvArgs A, const re
 // ---------------------------------------------------------- launchers
 template <typename real, typename TD>
 static void launch_fwd_t(const dp_model *m, const dp_nlist *nl, int n, const double *x, void *T,
-                         void *D, void *rec, int *rcnt, int *nnei, int *nseg, hipStream_t st)
+                         void *D, void *rec, int *rcnt, unsigned short *slots, int *nnei, int *nseg,
+                         hipStream_t st)
 {
     EnvArgs A = make_env_args(m, nl, x);
     A.rec = rec;
     A.rcnt = rcnt;
+    A.slots = slots;
     A.pg = nl->pg;
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
-    int wpb = lds_wpb(fwd_lds_bytes<real>(A.sel));
-    size_t lds = (size_t)wpb * fwd_lds_bytes<real>(A.sel);
-    hipLaunchKernelGGL((k_emb_fwd<real, TD>), dim3(xcd_grid(div_up(n, wpb))), dim3(64 * wpb), lds, st, n, A, tab,
+    hipLaunchKernelGGL((k_emb_fwd<real, TD>), dim3(xcd_grid(n)), dim3(64), fwd_lds_bytes<real>(A.sel), st, n, A, tab,
                        (real)m->cfg.desc_scale, (real *)T, (TD *)D, nnei, nseg);
 }
 
@@ -578,19 +571,18 @@ static void launch_bwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
     A.rcnt = const_cast<int *>(rcnt);
     A.pg = nl->pg;
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
-    int wpb = lds_wpb(bwd_lds_bytes<real>(A.sel));
-    size_t lds = (size_t)wpb * bwd_lds_bytes<real>(A.sel);
-    hipLaunchKernelGGL((k_emb_bwd<real>), dim3(xcd_grid(div_up(n, wpb))), dim3(64 * wpb), lds, st, n, A, tab,
+    hipLaunchKernelGGL((k_emb_bwd<real>), dim3(xcd_grid(n)), dim3(64), bwd_lds_bytes<real>(A.sel), st, n, A, tab,
                        (real)m->cfg.desc_scale, (const real *)dT, (const real *)dTp, nparts,
                        force, w_atom);
 }
 
 void launch_emb_fwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision,
-                    void *T, void *D, void *rec, int *rcnt, int *nnei, int *nseg, hipStream_t st)
+                    void *T, void *D, void *rec, int *rcnt, unsigned short *slots, int *nnei, int *nseg,
+                         hipStream_t st)
 {
-    if (precision == DP_FP64) launch_fwd_t<double, double>(m, nl, n, x, T, D, rec, rcnt, nnei, nseg, st);
-    else if (precision == DP_FP32) launch_fwd_t<float, float>(m, nl, n, x, T, D, rec, rcnt, nnei, nseg, st);
-    else launch_fwd_t<float, __bf16>(m, nl, n, x, T, D, rec, rcnt, nnei, nseg, st);
+    if (precision == DP_FP64) launch_fwd_t<double, double>(m, nl, n, x, T, D, rec, rcnt, slots, nnei, nseg, st);
+    else if (precision == DP_FP32) launch_fwd_t<float, float>(m, nl, n, x, T, D, rec, rcnt, slots, nnei, nseg, st);
+    else launch_fwd_t<float, __bf16>(m, nl, n, x, T, D, rec, rcnt, slots, nnei, nseg, st);
 }
 
 void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, const void *dT,

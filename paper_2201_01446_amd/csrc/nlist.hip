@@ -818,6 +818,7 @@ __global__ void __launch_bounds__(256) k_force_gather(int n, EnvArgs A, const sh
     if (!(code & kTruncBit)) {
         int nn = code;
         const V4<real> *rec = reinterpret_cast<const V4<real> *>(A.rec) + (long)i * A.sel;
+        const unsigned short *slots = A.slots ? A.slots + (long)i * A.sel : nullptr;
         for (int k0 = 0; k0 < nn; k0 += 256) {
             long off[4];
 #pragma unroll
@@ -825,7 +826,7 @@ __global__ void __launch_bounds__(256) k_force_gather(int n, EnvArgs A, const sh
                 int k = k0 + 64 * u + lane;
                 off[u] = -1;
                 if (k < nn) {
-                    int c = record_slot(rec[k].w) & 0xFFFFFF;
+                    int c = slots ? (int)slots[k] : record_slot(rec[k].w) & 0xFFFFFF;
                     int r = ri[c];
                     off[u] = r < 0 ? -1 : ((long)ni[c] * cap + r) * ST;
                 }
@@ -889,12 +890,13 @@ void launch_reverse(dp_nlist *nl, int off, int n, hipStream_t st, bool uniq)
 }
 
 void launch_force_gather(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision,
-                         const void *rec, const int *rcnt, double *force, hipStream_t st)
+                         const void *rec, const int *rcnt, const unsigned short *slots, double *force, hipStream_t st)
 {
     if (n <= 0) return;
     EnvArgs A = make_env_args(m, nl, x);
     A.rec = const_cast<void *>(rec);
     A.rcnt = const_cast<int *>(rcnt);
+    A.slots = const_cast<unsigned short *>(slots);
     A.pg = nl->pg;
     if (precision == DP_FP64)
         hipLaunchKernelGGL(k_force_gather<double>, dim3(xcd_grid(div_up(n, 4))), dim3(256), 0, st, n, A, nl->rev,

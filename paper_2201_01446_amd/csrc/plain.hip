@@ -159,13 +159,6 @@ __global__ void k_plain_dG(long rows, int sel, real sigma, const V4<real> *__res
 // fused paths): G and G' = dG/ds of every row, padded rows included, written
 // to memory from the table (Sec. 3.2), one thread per (row, column).
 template <typename real>
-__device__ inline void tab_coef(const real *tab, int th, int c, real (&a)[6])
-{
-    const real *p = tab + ((long)th * kM + c) * 6;
-    for (int e = 0; e < 6; e++) a[e] = p[e];
-}
-
-template <typename real>
 __global__ void k_tab_eval(long rows, EnvArgs A, const real *__restrict__ tab, const real *__restrict__ s,
                            real *__restrict__ G, real *__restrict__ Gp)
 {
@@ -177,7 +170,7 @@ __global__ void k_tab_eval(long rows, EnvArgs A, const real *__restrict__ tab, c
     real t;
     int oob = table_interval<real>(A, s[row], th, t);
     real a[6];
-    tab_coef<real>(tab, th & ~kOobBit, c, a);
+    coef_col(tab, th & ~kOobBit, c, a);
     real f = a[5], fp = a[5];
     for (int e = 4; e >= 1; e--) {
         f = fma(f, t, a[e]);
