@@ -234,6 +234,10 @@ inline int lds_wpb(size_t per_wave)
         if ((size_t)w * per_wave <= 65536) return w;
     return 0;
 }
+// Sums and maxima over at most this many atoms are one block's work: a second
+// launch (or the zeroing of an atomic's target) costs more than the other
+// blocks save.
+constexpr int kOneBlockAtoms = 4096;
 inline int xcd_grid(long nblocks) { return (int)round_up(nblocks, kXcd); }
 __device__ inline int xcd_item(int b, int grid) { return (b % kXcd) * (grid / kXcd) + b / kXcd; }
 

@@ -128,7 +128,7 @@ __device__ inline int round_reps(const NbrLDS<real> &L, const int *seg, int s0, 
 // than X is cut into pieces of X neighbors (and a last shorter one), which
 // become segments of their own; nruns then receives the number of whole runs.
 template <typename real, int X = 0>
-__device__ int find_segments(const NbrLDS<real> &L, int nn, int lane, int *seg, int *nruns = nullptr)
+__device__ __forceinline__ int find_segments(const NbrLDS<real> &L, int nn, int lane, int *seg, int *nruns = nullptr)
 {
     int nseg = 0, runs = 0;
     int open = 0;   // start of the run that continues into the next chunk
@@ -185,6 +185,54 @@ constexpr int bwd_lds_bytes(int sel)
 }
 
 // -------------------------------------------------------------- forward
+// One round of the forward: the moments of the ns segments from s0 on, those of
+// segments that share an interval added up in the first of them; returns which
+// segments those are (bit u: segment s0 + u).
+template <typename real>
+__device__ __forceinline__ unsigned long long round_moments(const NbrLDS<real> &L, const int *seg, int s0, int ns, real *Ms, int lane)
+{
+    const int q = lane >> 2, ql = lane & 3;
+    // moments of segment s0 + q: lane ql of the quad sums column k = ql
+    // of R over the segment's neighbors, in list order
+    if (q < ns) {
+        real Mk[6] = {0, 0, 0, 0, 0, 0};
+        int e1 = seg[s0 + q + 1];
+        for (int k = seg[s0 + q]; k < e1; k++) {
+            real t = L.t[k];
+            real r = reinterpret_cast<const real *>(&L.R[k])[ql];
+            real pw = 1;
+#pragma unroll
+            for (int e = 0; e < 6; e++) {
+                Mk[e] = fma(r, pw, Mk[e]);
+                pw *= t;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 6; e++) Ms[q * 24 + ql * 6 + e] = Mk[e];
+    }
+    // segments of the round that share an interval: the representative
+    // takes the others' moments (in segment order), and only it is contracted
+    const int rep = round_reps(L, seg, s0, ns, lane);
+    const unsigned long long reps = __ballot(lane < ns && rep == lane);
+    if (reps != ((1ull << ns) - 1ull)) {
+        wave_sync();
+        real add[6] = {0, 0, 0, 0, 0, 0};
+        for (unsigned long long rest = ((1ull << ns) - 1ull) & ~reps; rest; rest &= rest - 1) {
+            const int u = __builtin_ctzll(rest);
+            if (__builtin_amdgcn_readlane(rep, u) == q) {
+#pragma unroll
+                for (int e = 0; e < 6; e++) add[e] += Ms[u * 24 + ql * 6 + e];
+            }
+        }
+        if (reps >> q & 1) {   // quad q holds a representative
+#pragma unroll
+            for (int e = 0; e < 6; e++) Ms[q * 24 + ql * 6 + e] += add[e];
+        }
+    }
+    wave_sync();
+    return reps;
+}
+
 // At 108,000 atoms 570 us (FP32) and 960 (FP64), 670 and 1,110 before the
 // lane reads, the blocks of one wave and the coalesced table: the scan with
 // the stores of records and T takes 40-45 %, the contraction 40 %; bound by
@@ -212,48 +260,10 @@ __global__ void __launch_bounds__(64) k_emb_fwd(int natoms, EnvArgs A, const rea
     int nruns = 0;
     int nseg = find_segments<real, kFwdMaxRun>(L, nn, lane, seg, &nruns);
 
-    int q = lane >> 2, ql = lane & 3;
     real T0[4] = {0, 0, 0, 0}, T1[4] = {0, 0, 0, 0};   // columns lane, lane + 64
     for (int s0 = 0; s0 < nseg; s0 += kSegRound) {
         int ns = min(kSegRound, nseg - s0);
-        // moments of segment s0 + q: lane ql of the quad sums column k = ql
-        // of R over the segment's neighbors, in list order
-        if (q < ns) {
-            real Mk[6] = {0, 0, 0, 0, 0, 0};
-            int e1 = seg[s0 + q + 1];
-            for (int k = seg[s0 + q]; k < e1; k++) {
-                real t = L.t[k];
-                real r = reinterpret_cast<const real *>(&L.R[k])[ql];
-                real pw = 1;
-#pragma unroll
-                for (int e = 0; e < 6; e++) {
-                    Mk[e] = fma(r, pw, Mk[e]);
-                    pw *= t;
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < 6; e++) Ms[q * 24 + ql * 6 + e] = Mk[e];
-        }
-        // segments of the round that share an interval: the representative
-        // takes the others' moments (in segment order), and only it is contracted
-        const int rep = round_reps(L, seg, s0, ns, lane);
-        const unsigned long long reps = __ballot(lane < ns && rep == lane);
-        if (reps != ((1ull << ns) - 1ull)) {
-            wave_sync();
-            real add[6] = {0, 0, 0, 0, 0, 0};
-            for (unsigned long long rest = ((1ull << ns) - 1ull) & ~reps; rest; rest &= rest - 1) {
-                const int u = __builtin_ctzll(rest);
-                if (__builtin_amdgcn_readlane(rep, u) == q) {
-#pragma unroll
-                    for (int e = 0; e < 6; e++) add[e] += Ms[u * 24 + ql * 6 + e];
-                }
-            }
-            if (reps >> q & 1) {   // quad q holds a representative
-#pragma unroll
-                for (int e = 0; e < 6; e++) Ms[q * 24 + ql * 6 + e] += add[e];
-            }
-        }
-        wave_sync();
+        const unsigned long long reps = round_moments(L, seg, s0, ns, Ms, lane);
         // T[k][c] += sum_e a[theta][c][e] M[k][e], lanes over columns; the
         // coefficients of up to four representatives are requested before any is used
         for (unsigned long long left = reps; left;) {
@@ -335,7 +345,7 @@ __global__ void __launch_bounds__(64) k_emb_fwd(int natoms, EnvArgs A, const rea
 // first lane stores B at Bs[(lane >> lg) * 24].  FULL: lg = 2 known at
 // compile time.
 template <typename real, bool FULL>
-__device__ inline void round_B(const NbrLDS<real> &L, const int *seg, int s0, int ns, int lg,
+__device__ __forceinline__ void round_B(const NbrLDS<real> &L, const int *seg, int s0, int ns, int lg,
                                const real *__restrict__ tab, const V4<real> *dTl, real *Bs, int lane)
 {
     if (FULL) lg = 2;
@@ -436,6 +446,66 @@ struct DTRegs {
     }
 };
 
+// B of a round: four lanes per segment in a full one; a round of at most 8, 4, 2
+// or 1 segments (the last one) gives each 8, 16, 32 or 64 lanes, so its lanes
+// still share the columns.
+template <typename real>
+__device__ __forceinline__ void round_B(const NbrLDS<real> &L, const int *seg, int s0, int ns, const real *__restrict__ tab,
+                               const V4<real> *dTl, real *Bs, int lane)
+{
+    if (ns > 8) round_B<real, true>(L, seg, s0, ns, 2, tab, dTl, Bs, lane);
+    else round_B<real, false>(L, seg, s0, ns, ns > 4 ? 3 : ns > 2 ? 4 : ns > 1 ? 5 : 6, tab, dTl, Bs, lane);
+    wave_sync();
+}
+
+// f(k, segment of k relative to s0) for the neighbors k of a round, one per lane.
+template <typename real, typename Fn>
+__device__ __forceinline__ void each_neighbor(const NbrLDS<real> &L, const int *seg, int s0, int ns, int lane, Fn f)
+{
+    int kb = seg[s0], ke = seg[s0 + ns];
+    int cur = -1;   // segment (relative to s0) of the last neighbor before this chunk
+    for (int b0 = kb; b0 < ke; b0 += 64) {
+        int k = b0 + lane;
+        bool in = k < ke;
+        bool head = in && (k == kb || L.th[k] != L.th[k - 1]);
+        unsigned long long hm = __ballot(head);
+        int sidx = cur + __popcll(hm & ((2ull << lane) - 1ull));   // heads up to and including k
+        cur += __popcll(hm);
+        if (in) f(k, sidx);
+    }
+}
+
+// Neighbor k of atom i, b: B of its interval.  dE/dR_j and dE/ds_j, then the
+// chain rule through Eq. 1: g = dE_i/dr_ij, to the neighbor's pair-gradient
+// slot; d = r_ij.
+template <typename real>
+__device__ __forceinline__ void pair_grad(const EnvArgs &A, const NbrLDS<real> &L, int i, int k, const real *b, V4<real> &d,
+                                 real &g0, real &g1, real &g2)
+{
+    int th = L.th[k];
+    real t = L.t[k];
+    d = L.Dv[k];
+    int slot = L.j[k];
+    real dR[4], Q[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; kk++) horner2<real>(b + kk * 6, t, dR[kk], Q[kk]);
+    real rinv, s, sp;
+    env_geom<real>(A, d, rinv, s, sp);
+    real h0 = d.x * rinv, h1 = d.y * rinv, h2 = d.z * rinv;
+    // dE/ds through G: sum_k R_k dB_k/dt with R = s (1, h); no G' past the table end
+    real dsG = (th & kOobBit) ? (real)0 : s * (Q[0] + Q[1] * h0 + Q[2] * h1 + Q[3] * h2);
+    // R = s (1, h): dE/ds collects dR0 + dR.h; dE/dh = s dR[1..3]
+    real dEds = dsG + dR[0] + dR[1] * h0 + dR[2] * h1 + dR[3] * h2;
+    real u0 = s * dR[1], u1 = s * dR[2], u2 = s * dR[3];
+    real udh = u0 * h0 + u1 * h1 + u2 * h2;
+    real c0 = dEds * sp;
+    g0 = c0 * h0 + (u0 - udh * h0) * rinv;
+    g1 = c0 * h1 + (u1 - udh * h1) * rinv;
+    g2 = c0 * h2 + (u2 - udh * h2) * rinv;
+    // dE_i/dr_ij, gathered into F_j after the kernel (no atomics)
+    put_pg<real>(A.pg, A.cap, i, slot, g0, g1, g2);
+}
+
 // The registers are those of 2 (FP64) and 4 waves a SIMD: with the 3 that it
 // would choose in FP64 the compiler keeps fewer coefficient loads in flight
 // (1,155 us against 1,010 at 108,000 atoms; 555 in FP32).
@@ -473,54 +543,18 @@ k_emb_bwd(int natoms, EnvArgs A, const real *__restrict__ tab, real sigma, const
     for (int r = 0; r < 9; r++) W[r] = 0;
     for (int s0 = 0; s0 < nseg; s0 += kSegRound) {
         int ns = min(kSegRound, nseg - s0);
-        // B of the round's segments: four lanes per segment in a full round;
-        // a round of at most 8, 4, 2 or 1 segments (the last one) gives each
-        // 8, 16, 32 or 64 lanes, so its lanes still share the columns
-        if (ns > 8) round_B<real, true>(L, seg, s0, ns, 2, tab, dTl, Bs, lane);
-        else round_B<real, false>(L, seg, s0, ns, ns > 4 ? 3 : ns > 2 ? 4 : ns > 1 ? 5 : 6, tab, dTl, Bs, lane);
-        wave_sync();
-        // the neighbors of these segments, one per lane: dE/dR_j and dE/ds_j
-        // from B, then the chain rule through Eq. 1 and the scatter
-        int kb = seg[s0], ke = seg[s0 + ns];
-        int cur = -1;   // segment (relative to s0) of the last neighbor before this chunk
-        for (int b0 = kb; b0 < ke; b0 += 64) {
-            int k = b0 + lane;
-            bool in = k < ke;
-            bool head = in && (k == kb || L.th[k] != L.th[k - 1]);
-            unsigned long long hm = __ballot(head);
-            int sidx = cur + __popcll(hm & ((2ull << lane) - 1ull));   // heads up to and including k
-            cur += __popcll(hm);
-            if (!in) continue;
-            int th = L.th[k];
-            real t = L.t[k];
-            V4<real> d = L.Dv[k];
-            int slot = L.j[k];
-            const real *b = Bs + sidx * 24;
-            real dR[4], Q[4];
-#pragma unroll
-            for (int kk = 0; kk < 4; kk++) horner2<real>(b + kk * 6, t, dR[kk], Q[kk]);
-            real rinv, s, sp;
-            env_geom<real>(A, d, rinv, s, sp);
-            real h0 = d.x * rinv, h1 = d.y * rinv, h2 = d.z * rinv;
-            // dE/ds through G: sum_k R_k dB_k/dt with R = s (1, h); no G' past the table end
-            real dsG = (th & kOobBit) ? (real)0 : s * (Q[0] + Q[1] * h0 + Q[2] * h1 + Q[3] * h2);
-            // R = s (1, h): dE/ds collects dR0 + dR.h; dE/dh = s dR[1..3]
-            real dEds = dsG + dR[0] + dR[1] * h0 + dR[2] * h1 + dR[3] * h2;
-            real u0 = s * dR[1], u1 = s * dR[2], u2 = s * dR[3];
-            real udh = u0 * h0 + u1 * h1 + u2 * h2;
-            real c0 = dEds * sp;
-            real g0 = c0 * h0 + (u0 - udh * h0) * rinv;
-            real g1 = c0 * h1 + (u1 - udh * h1) * rinv;
-            real g2 = c0 * h2 + (u2 - udh * h2) * rinv;
-            // dE_i/dr_ij, gathered into F_j after the kernel (no atomics)
-            put_pg<real>(A.pg, A.cap, i, slot, g0, g1, g2);
+        round_B(L, seg, s0, ns, tab, dTl, Bs, lane);
+        each_neighbor(L, seg, s0, ns, lane, [&](int k, int sidx) __attribute__((always_inline)) {
+            V4<real> d;
+            real g0, g1, g2;
+            pair_grad(A, L, i, k, Bs + sidx * 24, d, g0, g1, g2);
             Fi0 += g0;
             Fi1 += g1;
             Fi2 += g2;
             W[0] -= d.x * g0; W[1] -= d.x * g1; W[2] -= d.x * g2;
             W[3] -= d.y * g0; W[4] -= d.y * g1; W[5] -= d.y * g2;
             W[6] -= d.z * g0; W[7] -= d.z * g1; W[8] -= d.z * g2;
-        }
+        });
         wave_sync();   // Bs is rewritten by the next round
     }
     for (int off = 32; off > 0; off >>= 1) {
@@ -543,9 +577,190 @@ k_emb_bwd(int natoms, EnvArgs A, const real *__restrict__ tab, real sigma, const
     }
 }
 
+// ------------------------------------------------- four waves to an atom
+// For systems of fewer atoms than the chip has SIMDs a wave per atom leaves most
+// of them idle and the step waits for one wave's chain of work.  Here a block of
+// four waves takes an atom: they share the scan and the environment, each forms
+// the moments (B) of every fourth round of segments, and the sums over segments
+// are split by column and component of R (by component of force and virial),
+// so that every sum has the order that it has in the kernels of one wave, and
+// the same bits.  Forward and backward
+// at 108 atoms, FP64: 24 and 23 us by one wave, 18 and 16 by four; forward at 500,
+// FP32: 23 and 18.
+constexpr int kWide = 4;
+
+template <typename real>
+constexpr int wide_lds_bytes(int sel, bool fwd)
+{
+    constexpr int al = (int)sizeof(V4<real>);
+    int b = (nbr_lds_bytes<real>(sel, fwd ? ENV_FWD : ENV_BWD) + (fwd ? 0 : kM * al) +
+             kWide * kSegRound * 24 * (int)sizeof(real) + kWide * seg_bytes(sel) + 31) / 32 * 32;
+    return (b + (fwd ? 512 : 3 * sel * (int)sizeof(real)) + al - 1) / al * al;
+}
+
+template <typename real>
+__global__ void __launch_bounds__(64 * kWide) k_emb_fwd_wide(int natoms, EnvArgs A, const real *__restrict__ tab,
+                                                             real sigma, real *__restrict__ T_out,
+                                                             int *__restrict__ nnei_out, int *__restrict__ nseg_out)
+{
+    HIP_DYNAMIC_SHARED(uint4, smem_raw)   // 16-byte aligned
+    char *base = reinterpret_cast<char *>(smem_raw);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = xcd_item(blockIdx.x, gridDim.x);
+    if (i >= natoms) return;   // the whole block
+    NbrLDS<real> L = carve<real>(base, A.sel, ENV_FWD);
+    char *p = base + nbr_lds_bytes<real>(A.sel, ENV_FWD);
+    real *Ms = reinterpret_cast<real *>(p);   // kWide x kSegRound x 24
+    p += kWide * kSegRound * 24 * sizeof(real);
+    int *seg = reinterpret_cast<int *>(p + wave * seg_bytes(A.sel));
+    // per round of a turn: its intervals (with their place in Ms) and their number
+    int *list = reinterpret_cast<int *>(p + kWide * seg_bytes(A.sel));
+    int *cnts = list + kWide * kSegRound;   // 2 x kWide of the scan, then kWide of the rounds
+    int *num = cnts + 2 * kWide;
+    int n_in = 0, over = 0, oob = 0;
+    const int nn = build_env_wide<real, kWide>(i, A, L, cnts, n_in, over, oob);
+    int nruns = 0;
+    const int nseg = find_segments<real, kFwdMaxRun>(L, nn, lane, seg, &nruns);
+
+    // sums: wave w has columns 64 (w mod 2) + lane, components 2 (w / 2) and the next
+    const int c = (wave & 1) * 64 + lane, kk = (wave >> 1) * 2;
+    real T0 = 0, T1 = 0;
+    for (int t0 = 0; t0 < nseg; t0 += kSegRound * kWide) {
+        const int s0 = t0 + wave * kSegRound, ns = max(0, min(kSegRound, nseg - s0));
+        unsigned long long reps = 0;
+        if (ns > 0) reps = round_moments(L, seg, s0, ns, Ms + wave * kSegRound * 24, lane);
+        if (reps >> lane & 1)
+            list[wave * kSegRound + __popcll(reps & ((1ull << lane) - 1ull))] =
+                (L.th[seg[s0 + lane]] & ~kOobBit) << 6 | (wave * kSegRound + lane);
+        if (lane == 0) num[wave] = __popcll(reps);
+        __syncthreads();
+        const int p1 = num[0], p2 = p1 + num[1], p3 = p2 + num[2], tot = p3 + num[3];
+        auto entry = [&](int u) {
+            const int r = (u >= p1) + (u >= p2) + (u >= p3);
+            return __builtin_amdgcn_readfirstlane(list[r * kSegRound + u - (r == 0 ? 0 : r == 1 ? p1 : r == 2 ? p2 : p3)]);
+        };
+        constexpr int PD = 8;   // intervals whose coefficients are in flight
+        real a[PD][6];
+        int at[PD];
+#pragma unroll
+        for (int u = 0; u < PD; u++)
+            if (u < tot) {
+                const int x = entry(u);
+                at[u] = x & 63;
+                coef_col(tab, x >> 6, c, a[u]);
+            }
+        for (int u0 = 0; u0 < tot; u0 += PD) {
+#pragma unroll
+            for (int u = 0; u < PD; u++) {
+                if (u0 + u < tot) {
+                    const real *m = Ms + at[u] * 24 + kk * 6;
+#pragma unroll
+                    for (int e = 0; e < 6; e++) {
+                        T0 = fma(m[e], a[u][e], T0);
+                        T1 = fma(m[6 + e], a[u][e], T1);
+                    }
+                    if (u0 + u + PD < tot) {
+                        const int x = entry(u0 + u + PD);
+                        at[u] = x & 63;
+                        coef_col(tab, x >> 6, c, a[u]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+        __syncthreads();   // Ms and the list are rewritten by the next turn
+    }
+    real *o = T_out + ((long)i * kM + c) * 4 + kk;
+    o[0] = T0 * sigma;
+    o[1] = T1 * sigma;
+    if (wave == 0) {
+        if (nnei_out && lane == 0) nnei_out[i] = nn;
+        if (nseg_out && lane == 0) nseg_out[i] = nruns;
+        record_flags<real>(A, lane, n_in, over, oob);
+    }
+}
+
+template <typename real>
+__global__ void __launch_bounds__(64 * kWide) k_emb_bwd_wide(int natoms, EnvArgs A, const real *__restrict__ tab,
+                                                             real sigma, const real *__restrict__ dT,
+                                                             const real *__restrict__ dTp, int nparts,
+                                                             double *__restrict__ force, double *__restrict__ w_atom)
+{
+    HIP_DYNAMIC_SHARED(uint4, smem_raw)   // 16-byte aligned
+    char *base = reinterpret_cast<char *>(smem_raw);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int i = xcd_item(blockIdx.x, gridDim.x);
+    if (i >= natoms) return;   // the whole block
+    NbrLDS<real> L = carve<real>(base, A.sel, ENV_BWD);
+    char *p = base + nbr_lds_bytes<real>(A.sel, ENV_BWD);
+    V4<real> *dTl = reinterpret_cast<V4<real> *>(p);   // per column
+    p += kM * sizeof(V4<real>);
+    real *Bs = reinterpret_cast<real *>(p) + wave * kSegRound * 24;   // kSegRound x 24 of each wave
+    p += kWide * kSegRound * 24 * sizeof(real);
+    int *seg = reinterpret_cast<int *>(p + wave * seg_bytes(A.sel));
+    p = base + (p - base + kWide * seg_bytes(A.sel) + 31) / 32 * 32;
+    real *G = reinterpret_cast<real *>(p);   // the pair gradients, sel x 3
+    DTRegs<real> dt;
+    if (wave == 0) dt.load(i, natoms, lane, dT, dTp, nparts);
+    const int nn = load_env<real, ENV_BWD, kWide>(i, A, L, threadIdx.x);
+    if (wave == 0) dt.finish(lane, sigma, dTl);
+    __syncthreads();
+    const int nseg = find_segments(L, nn, lane, seg);
+
+    for (int s0 = wave * kSegRound; s0 < nseg; s0 += kSegRound * kWide) {
+        const int ns = min(kSegRound, nseg - s0);
+        round_B(L, seg, s0, ns, tab, dTl, Bs, lane);
+        each_neighbor(L, seg, s0, ns, lane, [&](int k, int sidx) {
+            V4<real> d;
+            real g0, g1, g2;
+            pair_grad(A, L, i, k, Bs + sidx * 24, d, g0, g1, g2);
+            G[3 * k] = g0;
+            G[3 * k + 1] = g1;
+            G[3 * k + 2] = g2;
+        });
+        wave_sync();   // Bs is rewritten by the next round
+    }
+    __syncthreads();
+    // wave 0 the force, the others a row of the virial each: per lane over the
+    // rounds as in the kernel of one wave, then over the lanes
+    real v0 = 0, v1 = 0, v2 = 0;
+    for (int s0 = 0; s0 < nseg; s0 += kSegRound)
+        for (int k = seg[s0] + lane, ke = seg[min(s0 + kSegRound, nseg)]; k < ke; k += 64) {
+            const real g0 = G[3 * k], g1 = G[3 * k + 1], g2 = G[3 * k + 2];
+            if (wave == 0) {
+                v0 += g0;
+                v1 += g1;
+                v2 += g2;
+            } else {
+                const V4<real> d = L.Dv[k];
+                const real x = wave == 1 ? d.x : wave == 2 ? d.y : d.z;
+                v0 -= x * g0;
+                v1 -= x * g1;
+                v2 -= x * g2;
+            }
+        }
+    for (int off = 32; off > 0; off >>= 1) {
+        v0 += __shfl_xor(v0, off);
+        v1 += __shfl_xor(v1, off);
+        v2 += __shfl_xor(v2, off);
+    }
+    if (lane == 0) {
+        double *o = wave == 0 ? force + 3 * i : w_atom + (long)i * 9 + (wave - 1) * 3;
+        o[0] = (double)v0;
+        o[1] = (double)v1;
+        o[2] = (double)v2;
+    }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------- launchers
+// Up to this many atoms four waves take one: a wave to each SIMD of the chip.
+// Past it the redundant parts (segments, barriers) cost more than the idle SIMDs
+// did: 1,371 atoms 32 and 27 us (forward, backward; FP32) against 28 and 25 by
+// one wave, 1,536 water atoms 58 and 52 against 33 and 33 (FP64).
+constexpr int kWideAtoms = 1024;
+
 template <typename real, typename TD>
 static void launch_fwd_t(const dp_model *m, const dp_nlist *nl, int n, const double *x, void *T,
                          void *D, void *rec, int *rcnt, unsigned short *slots, int *nnei, int *nseg,
@@ -557,6 +772,11 @@ static void launch_fwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
     A.slots = slots;
     A.pg = nl->pg;
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
+    if (n <= kWideAtoms && !D && wide_lds_bytes<real>(A.sel, true) <= 65536) {
+        hipLaunchKernelGGL(k_emb_fwd_wide<real>, dim3(xcd_grid(n)), dim3(64 * kWide), wide_lds_bytes<real>(A.sel, true), st,
+                           n, A, tab, (real)m->cfg.desc_scale, (real *)T, nnei, nseg);
+        return;
+    }
     hipLaunchKernelGGL((k_emb_fwd<real, TD>), dim3(xcd_grid(n)), dim3(64), fwd_lds_bytes<real>(A.sel), st, n, A, tab,
                        (real)m->cfg.desc_scale, (real *)T, (TD *)D, nnei, nseg);
 }
@@ -571,6 +791,11 @@ static void launch_bwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
     A.rcnt = const_cast<int *>(rcnt);
     A.pg = nl->pg;
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
+    if (n <= kWideAtoms && wide_lds_bytes<real>(A.sel, false) <= 65536) {
+        hipLaunchKernelGGL(k_emb_bwd_wide<real>, dim3(xcd_grid(n)), dim3(64 * kWide), wide_lds_bytes<real>(A.sel, false), st,
+                           n, A, tab, (real)m->cfg.desc_scale, (const real *)dT, (const real *)dTp, nparts, force, w_atom);
+        return;
+    }
     hipLaunchKernelGGL((k_emb_bwd<real>), dim3(xcd_grid(n)), dim3(64), bwd_lds_bytes<real>(A.sel), st, n, A, tab,
                        (real)m->cfg.desc_scale, (const real *)dT, (const real *)dTp, nparts,
                        force, w_atom);

@@ -242,11 +242,12 @@ __device__ inline void zero_pg(const EnvArgs &A, int i, int c)
 
 // Per neighbor k < nn of the slice: s, R_j, the table interval and offset
 // (and what MODE keeps); returns this lane's count of look-ups past the table.
-template <typename real, int MODE, bool TAB>
-__device__ int finish_env(const EnvArgs &A, NbrLDS<real> L, int nn, int lane)
+// NW waves share the atom: lane is then the thread's number among them.
+template <typename real, int MODE, bool TAB, int NW = 1>
+__device__ __forceinline__ int finish_env(const EnvArgs &A, NbrLDS<real> L, int nn, int lane)
 {
     int oob = 0;
-    for (int k = lane; k < nn; k += 64) {
+    for (int k = lane; k < nn; k += 64 * NW) {
         V4<real> d = (MODE == ENV_BWD || MODE == ENV_BWDR) ? L.Dv[k] : L.R[k];
         real rinv, s, sp;
         env_geom<real>(A, d, rinv, s, sp);
@@ -265,6 +266,43 @@ __device__ int finish_env(const EnvArgs &A, NbrLDS<real> L, int nn, int lane)
         }
     }
     return oob;
+}
+
+// More than lim of the candidates [c0, c0 + ct) lie within rcut: the lim
+// nearest by (r^2, j, image shift x, y, z) to LDS positions base, base + 1, ..
+// (ranks are a permutation), the pair gradients of the others to zero.  first,
+// stride: the candidates that this thread ranks.
+template <typename real, int MODE>
+__device__ inline void rank_candidates(int i, const EnvArgs &A, NbrLDS<real> L, int first, int stride, int c0, int ct, int lim,
+                                int base, int ty, double xi0, double xi1, double xi2, double L0, double L1, double L2)
+{
+    const int *nei = A.nei + (long)i * A.cap;
+    const int *shf = A.shift + (long)i * A.cap;
+    const real rty = (real)ty;
+    for (int k = c0 + first; k < c0 + ct; k += stride) {
+        int j = nei[k], s = shf[k];
+        double d0, d1, d2;
+        if (!within_cut(A.x, j, xi0, xi1, xi2, s, L0, L1, L2, A.rc2, d0, d1, d2)) continue;
+        double r2 = d0 * d0 + d1 * d1 + d2 * d2;
+        int so = shift_order(s);
+        int rank = 0;
+        for (int q = c0; q < c0 + ct; q++) {
+            int jq = nei[q], sq = shf[q];
+            double e0, e1, e2;
+            if (!within_cut(A.x, jq, xi0, xi1, xi2, sq, L0, L1, L2, A.rc2, e0, e1, e2)) continue;
+            double rq = e0 * e0 + e1 * e1 + e2 * e2;
+            bool less = rq < r2 || (rq == r2 && (jq < j || (jq == j && shift_order(sq) < so)));
+            rank += less ? 1 : 0;
+        }
+        if (rank < lim) {
+            int pos = base + rank;
+            (MODE == ENV_BWD ? L.Dv : L.R)[pos] = V4<real>{(real)d0, (real)d1, (real)d2, rty};
+            if (MODE != ENV_FWD) L.j[pos] = j;
+            if (MODE == ENV_FWD && A.rec) put_record<real>(A, i, pos, d0, d1, d2, slot_code(k, ty));
+        } else if (MODE == ENV_FWD && A.pg) {
+            zero_pg<real>(A, i, k);   // within rcut but beyond the lim nearest
+        }
+    }
 }
 
 // The candidates [c0, c0 + ct) of atom i (one neighbor type ty): those
@@ -315,34 +353,7 @@ __device__ int scan_candidates(int i, const EnvArgs &A, NbrLDS<real> L, int lane
             n_in += __popcll(mask);
         }
     }
-    if (n_in > lim) {
-        // keep the lim nearest by (r^2, j, image shift x, y, z); ranks are a
-        // permutation
-        for (int k = c0 + lane; k < c0 + ct; k += 64) {
-            int j = nei[k], s = shf[k];
-            double d0, d1, d2;
-            if (!within_cut(A.x, j, xi0, xi1, xi2, s, L0, L1, L2, A.rc2, d0, d1, d2)) continue;
-            double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-            int so = shift_order(s);
-            int rank = 0;
-            for (int q = c0; q < c0 + ct; q++) {
-                int jq = nei[q], sq = shf[q];
-                double e0, e1, e2;
-                if (!within_cut(A.x, jq, xi0, xi1, xi2, sq, L0, L1, L2, A.rc2, e0, e1, e2)) continue;
-                double rq = e0 * e0 + e1 * e1 + e2 * e2;
-                bool less = rq < r2 || (rq == r2 && (jq < j || (jq == j && shift_order(sq) < so)));
-                rank += less ? 1 : 0;
-            }
-            if (rank < lim) {
-                int pos = base + rank;
-                (MODE == ENV_BWD ? L.Dv : L.R)[pos] = V4<real>{(real)d0, (real)d1, (real)d2, rty};
-                if (MODE != ENV_FWD) L.j[pos] = j;
-                if (MODE == ENV_FWD && A.rec) put_record<real>(A, i, pos, d0, d1, d2, slot_code(k, ty));
-            } else if (MODE == ENV_FWD && A.pg) {
-                zero_pg<real>(A, i, k);   // within rcut but beyond the lim nearest
-            }
-        }
-    }
+    if (n_in > lim) rank_candidates<real, MODE>(i, A, L, lane, 64, c0, ct, lim, base, ty, xi0, xi1, xi2, L0, L1, L2);
     return n_in;
 }
 
@@ -399,21 +410,22 @@ __device__ int build_env(int i, const EnvArgs &A, NbrLDS<real> L, int lane, int 
 
 // The backward's neighbors of atom i: read back the forward's records (no
 // scan of the skin list), then the same per-neighbor quantities.
-template <typename real, int MODE = ENV_BWD>
-__device__ int load_env(int i, const EnvArgs &A, NbrLDS<real> L, int lane)
+// NW waves share the atom: lane is then the thread's number among them.
+template <typename real, int MODE = ENV_BWD, int NW = 1>
+__device__ __forceinline__ int load_env(int i, const EnvArgs &A, NbrLDS<real> L, int lane)
 {
     int nn = A.rcnt[i] & ~kTruncBit;
     const V4<real> *rec = reinterpret_cast<const V4<real> *>(A.rec) + (long)i * A.sel;
-    // four records per lane in flight
+    constexpr int NR = NW == 1 ? 4 : 1;   // records per lane in flight
     for (int k0 = 0; k0 < nn; k0 += 256) {
-        V4<real> r[4];
+        V4<real> r[NR];
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
+        for (int u = 0; u < NR; u++) {
             int k = k0 + 64 * u + lane;
             if (k < nn) r[u] = rec[k];
         }
 #pragma unroll
-        for (int u = 0; u < 4; u++) {
+        for (int u = 0; u < NR; u++) {
             int k = k0 + 64 * u + lane;
             if (k < nn) {
                 int code = record_slot(r[u].w);
@@ -422,10 +434,83 @@ __device__ int load_env(int i, const EnvArgs &A, NbrLDS<real> L, int lane)
             }
         }
     }
+    // (several waves: a thread reads back the entries that it wrote)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    finish_env<real, MODE, true>(A, L, nn, lane);
+    finish_env<real, MODE, true, NW>(A, L, nn, lane);
+    return nn;
+}
+
+// build_env with NW waves to the atom (thread t of 64 NW; barriers across the
+// block): wave w takes chunk w of every NW chunks of 64 candidates.  The order
+// of the kept neighbors, and everything written, are those of build_env.  oob
+// counts the block's look-ups past the table end and is valid in thread 0's wave
+// (lane sums to be added up by record_flags).  cnts: NW ints of LDS, twice.
+template <typename real, int NW>
+__device__ int build_env_wide(int i, const EnvArgs &A, NbrLDS<real> L, int *cnts, int &n_in_out, int &over_out, int &oob_out)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double xi0 = A.x[3 * i], xi1 = A.x[3 * i + 1], xi2 = A.x[3 * i + 2];
+    double L0 = A.L0, L1 = A.L1, L2 = A.L2;
+    if (A.atomL) {
+        L0 = A.atomL[3 * i];
+        L1 = A.atomL[3 * i + 1];
+        L2 = A.atomL[3 * i + 2];
+    }
+    bool prefix = false;   // as in build_env
+    if (A.inner) prefix = 2.0 * __longlong_as_double((long long)*A.disp) + kScanSlack <= A.margin;
+    const int *nei = A.nei + (long)i * A.cap, *shf = A.shift + (long)i * A.cap;
+    int nn = 0, n_in = 0, over = 0, c0 = 0, pass = 0;
+    for (int ty = 0; ty < (A.ntypes <= 1 ? 1 : A.ntypes); ty++) {
+        const int ct = A.ntypes <= 1 ? A.cnt[i] : A.tcnt[(long)i * kMaxTypes + ty];
+        const int cs = prefix ? A.inner[(long)i * kMaxTypes + ty] : ct, lim = A.ntypes <= 1 ? A.sel : A.sel_t[ty];
+        int m = 0;   // of this type within rcut
+        for (int b = 0; b < cs; b += 64 * NW, pass ^= 1) {
+            const int k = b + tid, c = c0 + k;
+            const bool on = k < cs;
+            const int j = on ? nei[c] : 0, s = on ? shf[c] : 0;
+            double d0 = 0, d1 = 0, d2 = 0;
+            const bool in = on && within_cut(A.x, j, xi0, xi1, xi2, s, L0, L1, L2, A.rc2, d0, d1, d2);
+            const unsigned long long mask = __ballot(in);
+            int *cw = cnts + pass * NW;
+            if (lane == 0) cw[wave] = __popcll(mask);
+            __syncthreads();
+            int q = m + __popcll(mask & ((1ull << lane) - 1ull));
+            for (int w = 0; w < NW; w++) {
+                const int v = cw[w];
+                if (w < wave) q += v;
+                m += v;
+            }
+            if (in && q < lim) {
+                const int pos = nn + q;
+                L.R[pos] = V4<real>{(real)d0, (real)d1, (real)d2, (real)ty};
+                if (A.rec) put_record<real>(A, i, pos, d0, d1, d2, slot_code(c, ty));
+            }
+        }
+        if (m > lim) {   // uniform over the block: keep the lim nearest, as scan_candidates
+            __syncthreads();
+            rank_candidates<real, ENV_FWD>(i, A, L, tid, 64 * NW, c0, cs, lim, nn, ty, xi0, xi1, xi2, L0, L1, L2);
+        }
+        nn += m < lim ? m : lim;
+        n_in += m;
+        over |= m > lim;
+        c0 += ct;
+    }
+    if (A.rec && tid == 0) A.rcnt[i] = nn | (over ? kTruncBit : 0);
+    __syncthreads();
+    int oob = finish_env<real, ENV_FWD, true, NW>(A, L, nn, tid);
+    // the block's look-ups past the end, to lane 0 of wave 0 (its other lanes zero)
+    for (int off = 32; off > 0; off >>= 1) oob += __shfl_xor(oob, off);
+    __syncthreads();   // the environment is in; the counts of the last pass have been read
+    if (lane == 0) cnts[wave] = oob;
+    __syncthreads();
+    oob = 0;
+    if (tid == 0)
+        for (int w = 0; w < NW; w++) oob += cnts[w];
+    oob_out = oob;
+    n_in_out = n_in;
+    over_out = over;
     return nn;
 }
 

@@ -490,11 +490,45 @@ __global__ void __launch_bounds__(256) k_displacement(int n, const double *__res
     }
 }
 
+// The same by one block, for few atoms: the maximum is stored, so nothing has
+// to be zeroed first.
+__global__ void __launch_bounds__(1024) k_displacement_one(int n, const double *__restrict__ x,
+                                                           const double *__restrict__ x0, double lim,
+                                                           unsigned long long *__restrict__ disp,
+                                                           int *__restrict__ flags)
+{
+    __shared__ double wmax[16];
+    double m = 0;
+    bool bad = false;
+    for (int i = threadIdx.x; i < n; i += 1024) {
+        double d0 = x[3 * i] - x0[3 * i], d1 = x[3 * i + 1] - x0[3 * i + 1], d2 = x[3 * i + 2] - x0[3 * i + 2];
+        double d = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+        if (!isfinite(d)) {
+            bad = true;
+            d = __builtin_huge_val();
+        }
+        m = fmax(m, d);
+    }
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(&flags[kFlagBadCoord], 1);
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; w++) m = fmax(m, wmax[w]);
+        *disp = (unsigned long long)__double_as_longlong(m);
+        if (m > 0 && 2.0 * m >= lim) atomicOr(&flags[kFlagSkin], 1);
+    }
+}
+
 }  // namespace
 
 void launch_displacement(const dp_nlist *nl, int n, const double *x, double lim, hipStream_t st)
 {
     if (!nl->x0 || n <= 0) return;
+    if (n <= kOneBlockAtoms) {
+        hipLaunchKernelGGL(k_displacement_one, dim3(1), dim3(1024), 0, st, n, x, nl->x0, lim, nl->disp, nl->flags);
+        return;
+    }
     launch_fill_zero_int(reinterpret_cast<int *>(nl->disp), 2, st);
     hipLaunchKernelGGL(k_displacement, dim3(div_up(n, 256)), dim3(256), 0, st, n, x, nl->x0, lim, nl->disp,
                        nl->flags);
