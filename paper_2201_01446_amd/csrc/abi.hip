@@ -56,175 +56,6 @@ dp_status upload(T **dst, const std::vector<T> &src)
     return DP_OK;
 }
 
-// float -> bfloat16 bits, round to nearest even
-uint16_t bf16_bits(float f)
-{
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-dp_status upload_fit(FitWeights &w, const std::vector<double> *mats, int prec)
-{
-    // mats: V1 [2048][256], V1t [256][2048], V2, V2t, V3, V3t [256][256]
-    void **dst[6] = {&w.V1, &w.V1t, &w.V2, &w.V2t, &w.V3, &w.V3t};
-    // K (row length) of each matrix as a GEMM Bt operand
-    const size_t kcols[6] = {(size_t)kFitPad, (size_t)kDdim, (size_t)kFitPad, (size_t)kFitPad, (size_t)kFitPad,
-                             (size_t)kFitPad};
-    for (int k = 0; k < 6; k++) {
-        const std::vector<double> &m = mats[k];
-        size_t n = m.size();
-        if (prec == DP_FP64) {
-            DP_HIP(hipMalloc(dst[k], n * 8));
-            DP_HIP(hipMemcpy(*dst[k], m.data(), n * 8, hipMemcpyHostToDevice));
-        } else if (prec == DP_FP32) {
-            std::vector<float> f(n);
-            for (size_t i = 0; i < n; i++) f[i] = (float)m[i];
-            DP_HIP(hipMalloc(dst[k], n * 4));
-            DP_HIP(hipMemcpy(*dst[k], f.data(), n * 4, hipMemcpyHostToDevice));
-        } else {
-            // rows of Bt as [hi | lo | hi] along K (see kSplitBf16)
-            size_t K = kcols[k], rows = n / K;
-            std::vector<uint16_t> b(3 * n);
-            for (size_t r = 0; r < rows; r++)
-                for (size_t c = 0; c < K; c++) {
-                    float f = (float)m[r * K + c];
-                    uint16_t hi = bf16_bits(f);
-                    uint32_t hb = (uint32_t)hi << 16;
-                    float hf;
-                    std::memcpy(&hf, &hb, 4);
-                    uint16_t lo = bf16_bits(f - hf);
-                    b[r * 3 * K + c] = hi;
-                    b[r * 3 * K + K + c] = lo;
-                    b[r * 3 * K + 2 * K + c] = hi;
-                }
-            DP_HIP(hipMalloc(dst[k], 3 * n * 2));
-            DP_HIP(hipMemcpy(*dst[k], b.data(), 3 * n * 2, hipMemcpyHostToDevice));
-        }
-    }
-    return DP_OK;
-}
-
-// The same weights in the lane order of fitnet.hip: a piece of 256 reals per
-// tile of 16 columns (nt of them) and four K steps; lane l, K step i: row or
-// column l mod 16, k = 4 i + l / 16 (FP64) or 4 (l / 16) + i (FP32).
-template <typename real>
-dp_status upload_fitnet(FitWeights &w, const std::vector<double> *mats, int ntypes, int nt)
-{
-    constexpr bool f64 = sizeof(real) == 8;
-    std::vector<real> in(f64 ? (size_t)ntypes * kM * nt * 256 : 0), mid((size_t)ntypes * 4 * nt * nt * 256),
-        out((size_t)ntypes * kM * nt * 256);
-    // element (l, i) of a piece: FP64 stores the K steps in pairs (16 bytes a lane)
-    auto piece = [](real *p, auto val) {
-        for (int l = 0; l < 64; l++)
-            for (int i = 0; i < 4; i++)
-                p[f64 ? (i / 2) * 128 + l * 2 + i % 2 : l * 4 + i] =
-                    (real)val(l % 16, f64 ? 4 * i + l / 16 : 4 * (l / 16) + i);
-    };
-    real *pi = in.data(), *pm = mid.data(), *po = out.data();
-    for (int t = 0; t < ntypes; t++) {
-        const double *V1 = mats[0].data() + (size_t)t * kDdim * kFitPad;   // [a M + b][o]
-        for (int b = 0; b < (f64 ? kM : 0); b++)
-            for (int ot = 0; ot < nt; ot++, pi += 256)
-                piece(pi, [&](int o, int a) { return V1[(size_t)(a * kM + b) * kFitPad + 16 * ot + o]; });
-        // V2t, V3t (out by in), V3, V2 (in by out): rows are the product's outputs
-        const int order[4] = {3, 5, 4, 2};
-        for (int k = 0; k < 4; k++) {
-            const double *V = mats[order[k]].data() + (size_t)t * kFitPad * kFitPad;
-            for (int ot = 0; ot < nt; ot++)
-                for (int kt = 0; kt < nt; kt++, pm += 256)
-                    piece(pm, [&](int o, int c) { return V[(size_t)(16 * ot + o) * kFitPad + 16 * kt + c]; });
-        }
-        for (int b = 0; b < kM; b++)
-            for (int kt = 0; kt < nt; kt++, po += 256)
-                piece(po, [&](int a, int o) { return V1[(size_t)(a * kM + b) * kFitPad + 16 * kt + o]; });
-    }
-    dp_status s;
-    // (the FP32 first layer takes split products, upload_split3)
-    if (f64 && (s = upload((real **)&w.in, in)) != DP_OK) return s;
-    if ((s = upload((real **)&w.mid, mid)) != DP_OK) return s;
-    return upload((real **)&w.out, out);
-}
-
-// BF16 parts of v (as FP32): the rounded value, then what is left of it.
-void put_parts(uint16_t *base, size_t pitch, int np, double v)
-{
-    float r = (float)v;
-    for (int n = 0; n < np; n++) {
-        uint16_t h = bf16_bits(r);
-        uint32_t hb = (uint32_t)h << 16;
-        float hf;
-        std::memcpy(&hf, &hb, 4);
-        base[n * pitch] = h;
-        r -= hf;
-    }
-}
-
-// The first layer's weights as three BF16 parts in the lane order of the FP32
-// kernel of fitsplit.hip: [K step][tile][part][lane][8], element j of lane l:
-// a = 4 (l / 16) + j mod 4, b = 2 (K step) + j / 4.
-dp_status upload_split3(FitWeights &w, const std::vector<double> *mats, int ntypes, int ks)
-{
-    const size_t piece = 512;   // 64 lanes x 8
-    std::vector<uint16_t> in((size_t)ntypes * (kM / 2) * 2 * ks * 3 * piece);
-    uint16_t *p = in.data();
-    for (int t = 0; t < ntypes; t++) {
-        const double *V1 = mats[0].data() + (size_t)t * kDdim * kFitPad;   // [a M + b][o]
-        for (int bp = 0; bp < kM / 2; bp++)
-            for (int ot = 0; ot < 2 * ks; ot++, p += 3 * piece)
-                for (int l = 0; l < 64; l++)
-                    for (int j = 0; j < 8; j++) {
-                        int a = 4 * (l / 16) + j % 4, b = 2 * bp + j / 4;
-                        put_parts(p + l * 8 + j, piece, 3, V1[(size_t)(a * kM + b) * kFitPad + 16 * ot + l % 16]);
-                    }
-    }
-    return upload((uint16_t **)&w.in, in);
-}
-
-// The weights as two BF16 parts in the lane order of the mixed kernels of
-// fitsplit.hip: K in its natural order, element j of lane l of K step g: k =
-// 32 g + 8 (l / 16) + j.  in [part][K step][tile][lane][8]; mid [matrix][part]
-// [K step][tile][lane][8]; out [b][part][K step][lane][8].
-dp_status upload_mix(FitWeights &w, const std::vector<double> *mats, int ntypes, int ks)
-{
-    const size_t piece = 512;
-    std::vector<uint16_t> in((size_t)ntypes * 2 * (kDdim / 32) * 2 * ks * piece),
-        mid((size_t)ntypes * 4 * 2 * ks * 2 * ks * piece), out((size_t)ntypes * kM * 2 * ks * piece);
-    const size_t in_part = (size_t)(kDdim / 32) * 2 * ks * piece, mid_part = (size_t)ks * 2 * ks * piece,
-                 out_part = (size_t)ks * piece;
-    for (int t = 0; t < ntypes; t++) {
-        const double *V1 = mats[0].data() + (size_t)t * kDdim * kFitPad;   // [k = a M + b][o]
-        uint16_t *p = in.data() + (size_t)t * 2 * in_part;
-        for (int g = 0; g < kDdim / 32; g++)
-            for (int ot = 0; ot < 2 * ks; ot++, p += piece)
-                for (int l = 0; l < 64; l++)
-                    for (int j = 0; j < 8; j++)
-                        put_parts(p + l * 8 + j, in_part, 2, V1[(size_t)(32 * g + 8 * (l / 16) + j) * kFitPad + 16 * ot + l % 16]);
-        const int order[4] = {3, 5, 4, 2};   // V2t, V3t (out by in), V3, V2 (in by out)
-        for (int k = 0; k < 4; k++) {
-            const double *V = mats[order[k]].data() + (size_t)t * kFitPad * kFitPad;
-            p = mid.data() + ((size_t)t * 4 + k) * 2 * mid_part;
-            for (int g = 0; g < ks; g++)
-                for (int ot = 0; ot < 2 * ks; ot++, p += piece)
-                    for (int l = 0; l < 64; l++)
-                        for (int j = 0; j < 8; j++)
-                            put_parts(p + l * 8 + j, mid_part, 2, V[(size_t)(16 * ot + l % 16) * kFitPad + 32 * g + 8 * (l / 16) + j]);
-        }
-        for (int b = 0; b < kM; b++) {
-            p = out.data() + ((size_t)t * kM + b) * 2 * out_part;
-            for (int g = 0; g < ks; g++, p += piece)
-                for (int l = 0; l < 64; l++)
-                    for (int j = 0; j < 8; j++)
-                        put_parts(p + l * 8 + j, out_part, 2, V1[(size_t)(l % 16 * kM + b) * kFitPad + 32 * g + 8 * (l / 16) + j]);
-        }
-    }
-    dp_status s;
-    if ((s = upload((uint16_t **)&w.in, in)) != DP_OK) return s;
-    if ((s = upload((uint16_t **)&w.mid, mid)) != DP_OK) return s;
-    return upload((uint16_t **)&w.out, out);
-}
-
 void free_fit(FitWeights &w)
 {
     void *p[9] = {w.V1, w.V1t, w.V2, w.V2t, w.V3, w.V3t, w.in, w.mid, w.out};
@@ -523,25 +354,22 @@ dp_status dp_model_create(const dp_model_config *cfg, const double *params_h, si
     m->ntypes = T;
     size_t nemb = emb_params(c), nfit = fit_params(c);
     int F = m->f1, P = kFitPad;
-    // per center type: the GEMM operands (each matrix's copies back to back) and the vectors
-    std::vector<double> mats[6];
+    // per center type: the GEMM operands (each matrix's copies back to back) and
+    // the vectors; V1t and the other layouts are formed on the device
+    std::vector<double> mats[5];
     mats[0].assign((size_t)T * kDdim * P, 0.0);   // V1  [2048][256] per type
-    mats[1].assign((size_t)T * P * kDdim, 0.0);   // V1t [256][2048] per type
-    for (int k = 2; k < 6; k++) mats[k].assign((size_t)T * P * P, 0.0);
+    for (int k = 1; k < 5; k++) mats[k].assign((size_t)T * P * P, 0.0);   // V2, V2t, V3, V3t
     std::vector<double> fb((size_t)T * kFitB, 0.0);
     for (int t = 0; t < T; t++) {
         const double *p = params_h + (size_t)T * nemb + (size_t)t * nfit;
         const double *V1 = p, *c1 = V1 + (size_t)kDdim * F, *V2 = c1 + F, *c2 = V2 + (size_t)F * F, *V3 = c2 + F,
                      *c3 = V3 + (size_t)F * F, *w4 = c3 + F, *b4 = w4 + F;
-        double *M0 = mats[0].data() + (size_t)t * kDdim * P, *M1 = mats[1].data() + (size_t)t * P * kDdim;
+        double *M0 = mats[0].data() + (size_t)t * kDdim * P;
         for (int a = 0; a < kDdim; a++)
-            for (int o = 0; o < F; o++) {
-                M0[(size_t)a * P + o] = V1[(size_t)a * F + o];
-                M1[(size_t)o * kDdim + a] = V1[(size_t)a * F + o];
-            }
+            for (int o = 0; o < F; o++) M0[(size_t)a * P + o] = V1[(size_t)a * F + o];
         const double *Vs[2] = {V2, V3};
         for (int k = 0; k < 2; k++) {
-            double *Ma = mats[2 + 2 * k].data() + (size_t)t * P * P, *Mb = mats[3 + 2 * k].data() + (size_t)t * P * P;
+            double *Ma = mats[1 + 2 * k].data() + (size_t)t * P * P, *Mb = mats[2 + 2 * k].data() + (size_t)t * P * P;
             for (int a = 0; a < F; a++)
                 for (int o = 0; o < F; o++) {
                     Ma[(size_t)a * P + o] = Vs[k][(size_t)a * F + o];
@@ -587,12 +415,10 @@ dp_status dp_model_create(const dp_model_config *cfg, const double *params_h, si
     dp_status s;
     if ((s = upload(&m->emb_d, emb)) != DP_OK || (s = upload(&m->fitb_d, fb)) != DP_OK ||
         (s = upload(&m->fitb_f, fbf)) != DP_OK || (s = upload((double **)&m->embg64, eg)) != DP_OK ||
-        (s = upload((float **)&m->embg32, egf)) != DP_OK || (s = upload_fit(m->w64, mats, DP_FP64)) != DP_OK ||
-        (s = upload_fitnet<double>(m->w64, mats, T, div_up(F, 16))) != DP_OK ||
-        (s = upload_fitnet<float>(m->w32, mats, T, div_up(F, 16))) != DP_OK ||
-        (s = upload_split3(m->w32, mats, T, div_up(F, 32))) != DP_OK ||
-        (s = upload_mix(m->wbf, mats, T, div_up(F, 32))) != DP_OK ||
-        (s = upload_fit(m->w32, mats, DP_FP32)) != DP_OK || (s = upload_fit(m->wbf, mats, DP_MIXED_BF16)) != DP_OK) {
+        (s = upload((float **)&m->embg32, egf)) != DP_OK || (s = upload((double **)&m->w64.V1, mats[0])) != DP_OK ||
+        (s = upload((double **)&m->w64.V2, mats[1])) != DP_OK || (s = upload((double **)&m->w64.V2t, mats[2])) != DP_OK ||
+        (s = upload((double **)&m->w64.V3, mats[3])) != DP_OK || (s = upload((double **)&m->w64.V3t, mats[4])) != DP_OK ||
+        (s = pack_weights(m->w64, m->w32, m->wbf, T, F)) != DP_OK) {
         dp_model_destroy(m);
         return s;
     }

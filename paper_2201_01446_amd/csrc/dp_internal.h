@@ -250,6 +250,7 @@ void launch_fill_zero_int(int *p, long n, hipStream_t st);
 // kFlagSkin when twice it reaches `lim` (the list's reach beyond the
 // evaluating model's cut-off: a pair within that cut-off may then lack its
 // candidate) and kFlagBadCoord on a non-finite position.
+dp_status pack_weights(FitWeights &d, FitWeights &w32, FitWeights &wbf, int ntypes, int f1);
 void launch_displacement(const dp_nlist *nl, int n, const double *x, double lim, hipStream_t st);
 dp_status launch_tabulate(dp_model *m, hipStream_t st);
 constexpr int kTanhN = 1024;   // tanh table intervals of width 1/128 on [0, 8)
