@@ -326,7 +326,7 @@ struct MidRing {
 };
 
 template <typename real, int RT, int PD, int NTC, bool TAB>
-__global__ void __launch_bounds__(1024) k_fit_mid(FitRows fr, int nrt, int nt, int zt, int parts,
+__global__ void __launch_bounds__(1024, sizeof(real) == 4 ? 8 : 4) k_fit_mid(FitRows fr, int nrt, int nt, int zt, int parts,
                                                   const real *__restrict__ z, const real *__restrict__ W,
                                                   const real *__restrict__ fb, const real *__restrict__ tanh_tab,
                                                   double *__restrict__ e_atom, real *__restrict__ dz1)
@@ -612,15 +612,19 @@ void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z,
     // two row tiles to a block once there are two blocks for every CU; widths
     // of 15 tiles (225 to 240, the paper's 240 among them) have loops of their own
     const int RT = nrt <= 512 ? 1 : 2;
+    // FP32: the registers of eight waves a SIMD, so that two blocks of 15 waves
+    // share a CU (503 -> 475 us at 108,000 atoms); one tile of weights ahead is
+    // what fits
+    constexpr int PD2 = sizeof(real) == 4 ? 1 : 3;
     if (nt == 15 && !tanh_tab) {
         if (RT == 1) go(k_fit_mid<real, 1, 5, 15, false>, 1);
-        else go(k_fit_mid<real, 2, 3, 15, false>, 2);
+        else go(k_fit_mid<real, 2, PD2, 15, false>, 2);
     } else if (!tanh_tab) {
         if (RT == 1) go(k_fit_mid<real, 1, 5, 0, false>, 1);
-        else go(k_fit_mid<real, 2, 3, 0, false>, 2);
+        else go(k_fit_mid<real, 2, PD2, 0, false>, 2);
     } else {
         if (RT == 1) go(k_fit_mid<real, 1, 5, 0, true>, 1);
-        else go(k_fit_mid<real, 2, 3, 0, true>, 2);
+        else go(k_fit_mid<real, 2, PD2, 0, true>, 2);
     }
 }
 template void launch_fit_mid<double>(const FitRows &, int, int, int, const double *, const void *, const double *,
