@@ -572,7 +572,7 @@ def tanh_compare(P, cfg, params, x0, v0, box, steps):
         out["table" if tab else "native"] = {
             "atom_steps_per_s": round(N * steps / (r["ms"] * 1e-3), 1), "ms_per_step": round(r["ms"] / steps, 4),
             "fitting_forward_ms": round(sum(v[0] / max(v[1], 1) for k, v in r["kernels"].items()
-                                            if k.startswith("fit_fwd")), 4)}
+                                            if k.startswith(("fit_in", "fit_mid", "fit_fwd"))), 4)}
         del nl, m
     a, b = res[False], res[True]
     out["dE_per_atom"] = abs(float(a["E"][0] - b["E"][0])) / N

@@ -2,14 +2,20 @@
 // velocity-Verlet kernels, as sequences of launches on one stream.
 //
 // Compressed step (per configuration, all on the caller's stream):
-//   k_emb_fwd        env matrix + tabulated G fused with R^T G -> T, D
-//   3 x GEMM         fitting net forward (tanh / shortcut epilogues)
-//   k_energy         E_i, dz3
-//   3 x GEMM         fitting-net input gradient -> dD
-//   k_emb_bwd        dE/dT from dE/dD and T, then the adjoint of the fused
-//                    step -> F_i's own part, dE_i/dr_ij per candidate, W_i
+//   k_displacement   largest move since the list was built
+//   k_emb_fwd        env matrix + tabulated G fused with R^T G -> T (a wave per
+//                    atom; k_emb_fwd_wide, four, for few atoms)
+//   first layer      D = T<^T T and z1 = D V1: k_fit_in (FP64), k_split_in
+//                    (FP32), k_mix_in (mixed)
+//   inner layers     E_i and the input gradient down to dz1: k_fit_mid, k_mix_mid
+//   input gradient   dE/dD = dz1 V1^T, contracted at once into dE/dT: k_fit_out,
+//                    k_mix_out
+//   k_emb_bwd        the adjoint of the fused step -> F_i's own part, dE_i/dr_ij
+//                    per candidate, W_i (k_emb_bwd_wide for few atoms)
 //   k_force_gather   F_j -= dE_i/dr_ij over the atoms i that list j
 //   k_reduce_*       deterministic FP64 sums of E_i and W_i
+// The other modes run the net as GEMMs (gemm.hip) with k_fit_tail or k_energy
+// (fit.hip) and D and dE/dD in memory.
 // Buffers live in the neighbor list's workspace; rows are padded to 128 so
 // the GEMM tiles never read past an allocation.
 

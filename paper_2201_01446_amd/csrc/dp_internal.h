@@ -398,8 +398,9 @@ void launch_emb_fwd_pn(const dp_model *m, const dp_nlist *nl, int n, const doubl
 void launch_emb_bwd_pn(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, const void *T,
                        const void *dD, const void *rec, const int *rcnt, bool padded, double *force, double *w_atom,
                        hipStream_t st);
-// rec/rcnt: the forward's compacted neighbor records (sel slots per atom) and
-// their counts, written by launch_emb_fwd and read by launch_emb_bwd
+// rec/rcnt/slots: the forward's compacted neighbor records (sel slots per atom),
+// their counts and the records' candidate slots alone (or NULL), written by
+// launch_emb_fwd; launch_emb_bwd reads the records, launch_force_gather the slots
 void launch_emb_fwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, void *T,
                     void *D, void *rec, int *rcnt, unsigned short *slots, int *nnei, int *nseg, hipStream_t st);
 void launch_emb_bwd(const dp_model *m, const dp_nlist *nl, int n, const double *x, int precision, const void *dT,

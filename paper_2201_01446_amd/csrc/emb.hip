@@ -34,9 +34,10 @@
 // A run split because atoms moved since the list was sorted gives two
 // segments of the same interval.  In the forward, such duplicates within a
 // round of segments share one representative (the first of the round with
-// that interval), which alone is contracted, with the sum of their moments
-// (the backward's B, computed by the segments' quads in parallel, gains
-// nothing from sharing).
+// that interval), which alone is contracted, with the sum of their moments.
+// (The backward's B is computed by the segments' quads in parallel.  Rounds of
+// 16 distinct intervals there, 20 to an atom of copper instead of 26 segments,
+// gained 3 % in FP32 and lost 5 % in water and more in FP64, by their registers.)
 //
 // Work distribution (one 64-lane wavefront per atom, a block of its own:
 // nothing is shared, and a block of four held its LDS until its slowest wave

@@ -6,11 +6,12 @@
 // equal-width layers, linear output).  Its input gradient for the forces:
 //   dz3 = w4 (1 - t3^2);  dy2 = w4 + dz3 V3^T;  dz2 = dy2 (1 - t2^2);
 //   dy1 = dy2 + dz2 V2^T; dz1 = dy1 (1 - y1^2); dD = dz1 V1^T,
-// with t_k the tanh outputs.  The first layer and dD are products of the
-// GEMM in gemm.hip; the 256-wide layers, the energy and their gradients down
-// to dz1 are fused here (k_fit_tail), with k_energy for the mixed-precision
-// mode, whose 256-wide layers are GEMMs too.  Widths are padded to 256 with
-// zero weights and biases, so the padded columns stay exactly zero.
+// with t_k the tanh outputs.  The compressed step runs the net in fitnet.hip and
+// fitsplit.hip; the other modes run the first layer and dD as products of the
+// GEMM in gemm.hip, and the 256-wide layers, the energy and their gradients down
+// to dz1 fused here (k_fit_tail), with k_energy for the mixed precision, whose
+// 256-wide layers are GEMMs too.  Widths are padded to 256 with zero weights
+// and biases, so the padded columns stay exactly zero.
 //
 // Then dT (dE/dT from dE/dD through D = T<^T T), the per-atom energy, and
 // deterministic FP64 sums of the energy and virial.

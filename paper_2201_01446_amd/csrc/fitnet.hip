@@ -13,8 +13,8 @@
 // tile and four K steps contiguous) and stream from L2 straight into
 // registers, once per 16 or 32 atoms.
 //
-//   k_fit_in    z1 = D V1 (D = T<^T T formed in registers, 4 FMA per element
-//               and K step)
+//   k_fit_in    z1 = D V1 (D = T<^T T formed once per block, shared in LDS;
+//               FP64: the FP32 layer is k_split_in of fitsplit.hip)
 //   k_fit_mid   y1 = tanh(z1 + c1), the two inner layers, E_i, and their
 //               input gradients down to dz1
 //   k_fit_out   dE/dD = dz1 V1^T tile by tile, contracted at once with T into
@@ -31,9 +31,11 @@
 // cycles), and the chip clocks down to about 2.13 GHz under FP64 MFMA, so 71
 // TFLOP/s is the ceiling here.  Against the tiled GEMMs that kept D or dE/dD in
 // HBM (FP64, microseconds; 108 / 2,917 / 108,000 atoms): first layer 104 / 110 /
-// 1,990 -> 13 / 68 / 1,850, the 240-wide layers 106 / 110 / 1,180 -> 40 / 45 /
-// 1,040, dE/dD and dE/dT 14 + / 59 + / 1,620 + 450 (in the embedding backward)
-// -> 15 / 68 / 1,910.
+// 1,990 -> 13 / 68 / 1,800, the
+// 240-wide layers 106 / 110 / 1,180 -> 38 / 43 / 990, dE/dD and dE/dT 14 + / 59 +
+// / 1,620 + 450 (in the embedding backward) -> 14 / 67 / 1,840.  FP32, 500 /
+// 108,000 atoms: the 240-wide layers 50 / 580 -> 21 / 475; dE/dD 900, and dE/dT in
+// the embedding backward, -> 940 at 108,000.
 
 #include "dp_internal.h"
 #include "emb_common.h"

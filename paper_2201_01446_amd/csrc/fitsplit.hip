@@ -25,9 +25,9 @@
 // Sums run in an order that does not depend on the number of rows.
 //
 // Measured (microseconds): FP32 first layer, 500 / 13,500 / 108,000 atoms,
-// 159 / 174 / 1,010 as a tiled FP32 GEMM -> 11 / 94 / 600; mixed, 62,500 atoms,
-// first layer, inner layers and energy 333 + 430 -> 590, dE/dD and dE/dT 337 +
-// 130 -> 318, and no D through HBM (embedding forward 533 -> 400).
+// 159 / 174 / 1,010 as a tiled FP32 GEMM -> 12 / 85 / 545; mixed, 62,500 atoms,
+// first layer, inner layers and energy 333 + 430 -> 476, dE/dD and dE/dT 337 +
+// 130 -> 314, and no D through HBM (embedding forward 533 -> 400).
 
 #include "dp_internal.h"
 #include "emb_common.h"
