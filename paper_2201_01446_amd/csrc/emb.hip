@@ -761,6 +761,8 @@ __global__ void __launch_bounds__(64 * kWide) k_emb_bwd_wide(int natoms, EnvArgs
 // did: 1,371 atoms 32 and 27 us (forward, backward; FP32) against 28 and 25 by
 // one wave, 1,536 water atoms 58 and 52 against 33 and 33 (FP64).
 constexpr int kWideAtoms = 1024;
+static_assert(wide_lds_bytes<double>(512, false) <= 65536 && wide_lds_bytes<double>(512, true) <= 65536,
+              "fits a block's LDS at the largest sel");
 
 template <typename real, typename TD>
 static void launch_fwd_t(const dp_model *m, const dp_nlist *nl, int n, const double *x, void *T,
@@ -773,7 +775,7 @@ static void launch_fwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
     A.slots = slots;
     A.pg = nl->pg;
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
-    if (n <= kWideAtoms && !D && wide_lds_bytes<real>(A.sel, true) <= 65536) {
+    if (n <= kWideAtoms && !D) {
         hipLaunchKernelGGL(k_emb_fwd_wide<real>, dim3(xcd_grid(n)), dim3(64 * kWide), wide_lds_bytes<real>(A.sel, true), st,
                            n, A, tab, (real)m->cfg.desc_scale, (real *)T, nnei, nseg);
         return;
@@ -792,7 +794,7 @@ static void launch_bwd_t(const dp_model *m, const dp_nlist *nl, int n, const dou
     A.rcnt = const_cast<int *>(rcnt);
     A.pg = nl->pg;
     const real *tab = std::is_same<real, double>::value ? (const real *)m->tab64 : (const real *)m->tab32;
-    if (n <= kWideAtoms && wide_lds_bytes<real>(A.sel, false) <= 65536) {
+    if (n <= kWideAtoms) {
         hipLaunchKernelGGL(k_emb_bwd_wide<real>, dim3(xcd_grid(n)), dim3(64 * kWide), wide_lds_bytes<real>(A.sel, false), st,
                            n, A, tab, (real)m->cfg.desc_scale, (const real *)dT, (const real *)dTp, nparts, force, w_atom);
         return;
