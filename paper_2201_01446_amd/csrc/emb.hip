@@ -237,7 +237,8 @@ __device__ __forceinline__ unsigned long long round_moments(const NbrLDS<real> &
 // At 108,000 atoms 570 us (FP32) and 960 (FP64), 670 and 1,110 before the
 // lane reads, the blocks of one wave and the coalesced table: the scan with
 // the stores of records and T takes 40-45 %, the contraction 40 %; bound by
-// the instructions of the wave (FP32) and by latency at 3 waves a SIMD (FP64).
+// the instructions of the wave (FP32) and by latency at the 3 waves a SIMD that
+// its LDS allows (FP64).
 template <typename real, typename TD>
 __global__ void __launch_bounds__(64) k_emb_fwd(int natoms, EnvArgs A, const real *__restrict__ tab,
                                                  real sigma, real *__restrict__ T_out,
@@ -266,21 +267,22 @@ __global__ void __launch_bounds__(64) k_emb_fwd(int natoms, EnvArgs A, const rea
         int ns = min(kSegRound, nseg - s0);
         const unsigned long long reps = round_moments(L, seg, s0, ns, Ms, lane);
         // T[k][c] += sum_e a[theta][c][e] M[k][e], lanes over columns; the
-        // coefficients of up to four representatives are requested before any is used
+        // coefficients of up to NG representatives are requested before any is used
         for (unsigned long long left = reps; left;) {
-            int us[4];
+            constexpr int NG = 3;   // (four cost a wave a SIMD: 41,472 water atoms, FP32, 257 us against 245)
+            int us[NG];
             int nu = 0;
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
+            for (int u = 0; u < NG; u++) {
                 us[u] = left ? __builtin_ctzll(left) : -1;
                 if (left) {
                     left &= left - 1;
                     nu++;
                 }
             }
-            real a0[4][6], a1[4][6];
+            real a0[NG][6], a1[NG][6];
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
+            for (int u = 0; u < NG; u++) {
                 if (u < nu) {
                     int th = L.th[seg[s0 + us[u]]] & ~kOobBit;
                     coef_col(tab, th, lane, a0[u]);
@@ -288,7 +290,7 @@ __global__ void __launch_bounds__(64) k_emb_fwd(int natoms, EnvArgs A, const rea
                 }
             }
 #pragma unroll
-            for (int u = 0; u < 4; u++) {
+            for (int u = 0; u < NG; u++) {
                 if (u < nu) {
                     const real *m = Ms + us[u] * 24;
 #pragma unroll
