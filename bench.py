@@ -151,9 +151,7 @@ def kernel_work(N, sum_nei, sum_seg, rs):
     kernels count the interval-moment form they execute: forward 24 moments
     per neighbor and 24 per (segment, column); backward 24 per (segment,
     column) and 40 per neighbor.  (D and dE/dT, 3 x 16 x 128 x 4 per atom, are
-    VALU work of the fitting net's kernels that is not counted.)  The FP32
-    first layer runs as six BF16 products: they are what its row counts,
-    against the BF16 peak."""
+    VALU work of the fitting net's kernels that is not counted.)"""
     fit_in = N * 2.0 * 240 * 2048          # 2048 -> 240 (and its transpose)
     fit_hid = N * 2.0 * 240 * 240          # 240 -> 240
     return {
@@ -161,7 +159,7 @@ def kernel_work(N, sum_nei, sum_seg, rs):
         "emb_bwd": (2.0 * (24 * 128 * sum_seg + 40 * sum_nei), "alu"),
         # the compressed step's net: first layer, the four 240 -> 240 products, input gradient;
         # fit_fwd: the first two in one timer (mixed)
-        "fit_in": (fit_in, "mfma") if rs == 8 else (6 * fit_in, "mfma", "bf16"),
+        "fit_in": (fit_in, "mfma"),
         "fit_mid": (4 * fit_hid, "mfma"), "fit_out": (fit_in, "mfma"), "fit_fwd": (fit_in + 4 * fit_hid, "mfma"),
         # the other modes' net
         "fit_fwd1": (fit_in, "mfma"), "fit_bwd1": (fit_in, "mfma"),
@@ -184,11 +182,11 @@ def roofline(res, steps, work, dt_alu, dt_mfma, counter_tag):
         avg = tot_ms / max(cnt, 1)
         row = dict(avg_ms=round(avg, 4), launches_per_step=round(cnt / steps, 3))
         if name in work:
-            w, bound, own = (*work[name], None)[:3]
+            w, bound = work[name]
             if bound == "hbm":
                 ach, peak, unit = w / (avg * 1e-3) / 1e9, HBM_PEAK_GBS, "GB/s"
             else:
-                dt = own or (dt_alu if bound == "alu" else dt_mfma)
+                dt = dt_alu if bound == "alu" else dt_mfma
                 ach, peak, unit = w / (avg * 1e-3) / 1e12, PEAK[(bound, dt)], "TFLOP/s"
             row.update(bound=bound, achieved=round(ach, 3), peak=peak, unit=unit, frac=round(ach / peak, 4))
             if bound == "alu" and dt_alu == "f32":

@@ -5,8 +5,8 @@
 //   k_displacement   largest move since the list was built
 //   k_emb_fwd        env matrix + tabulated G fused with R^T G -> T (a wave per
 //                    atom; k_emb_fwd_wide, four, for few atoms)
-//   first layer      D = T<^T T and z1 = D V1: k_fit_in (FP64), k_split_in
-//                    (FP32), k_mix_in (mixed)
+//   first layer      D = T<^T T and z1 = D V1: k_fit_in (FP64, FP32),
+//                    k_mix_in (mixed)
 //   inner layers     E_i and the input gradient down to dz1: k_fit_mid, k_mix_mid
 //   input gradient   dE/dD = dz1 V1^T, contracted at once into dE/dT: k_fit_out,
 //                    k_mix_out
@@ -121,7 +121,7 @@ struct FitNet {
         fr.nlive = n;
         for (int t = 0; t < kMaxTypes; t++) fr.b4[t] = a.m->b4[t];
         const long ks = div_up(nt, 2);
-        fr.w_in = f64 ? (long)kM * nt * 256 : mixed ? kM * ks * 2 * 64 : kM * ks * 3 * 64;
+        fr.w_in = mixed ? kM * ks * 2 * 64 : (long)kM * nt * 256;
         fr.w_mid = mixed ? 16 * ks * ks * 64 : 4L * nt * nt * 256;
         fr.w_out = mixed ? kM * ks * 2 * 64 : (long)kM * nt * 256;
         tab = !a.m->tanh_on ? nullptr : (const TR *)(f64 ? (const void *)a.m->tanh_tab64 : (const void *)a.m->tanh_tab);
@@ -132,16 +132,8 @@ struct FitNet {
         if constexpr (mixed) {
             DP_TIMED("fit_fwd", st, launch_mix_fwd(fr, nt, (const float *)w.T, fw, fb, tab, (float *)w.dDr, w.e_atom, w.D, st));
         } else {
-            int zt = nt, parts;
-            if constexpr (f64) {
-                parts = fit_in_parts(fr);
-                DP_TIMED("fit_in", st, launch_fit_in(fr, nt, (const double *)w.T, fw.in, (double *)w.dDr, st));
-            } else {
-                zt = 2 * div_up(nt, 2);
-                parts = split_in_parts(fr);
-                DP_TIMED("fit_in", st, launch_split_in(fr, nt, (const float *)w.T, fw.in, (float *)w.dDr, st));
-            }
-            DP_TIMED("fit_mid", st, launch_fit_mid<TR>(fr, nt, zt, parts, (const TR *)w.dDr, fw.mid, fb, tab, w.e_atom, (TR *)w.D, st));
+            DP_TIMED("fit_in", st, launch_fit_in<TR>(fr, nt, (const TR *)w.T, fw.in, (TR *)w.dDr, st));
+            DP_TIMED("fit_mid", st, launch_fit_mid<TR>(fr, nt, nt, fit_in_parts<TR>(fr), (const TR *)w.dDr, fw.mid, fb, tab, w.e_atom, (TR *)w.D, st));
         }
     }
     void backward(hipStream_t st) const

@@ -355,13 +355,12 @@ struct FitRows {
     double b4[kMaxTypes] = {0, 0, 0, 0};
     long w_in = 0, w_mid = 0, w_out = 0;
 };
-constexpr int kFitSegs = 4;      // segments of K of the first layer, summed in order (FP64, FP32)
-// FP64: z [fit_in_parts][row tile][nt][256], the first layer's sums before bias and tanh
+constexpr int kFitSegs = 4;      // segments of K of the first layer, summed in order (FP64)
+// z [fit_in_parts][row tile][nt][256], the first layer's sums before bias and tanh
+template <typename real>
 int fit_in_parts(const FitRows &fr);
-void launch_fit_in(const FitRows &fr, int nt, const double *T, const void *W, double *z, hipStream_t st);
-// FP32: z [split_in_parts][row tile][nt rounded up to even][256]
-int split_in_parts(const FitRows &fr);
-void launch_split_in(const FitRows &fr, int nt, const float *T, const void *W, float *z, hipStream_t st);
+template <typename real>
+void launch_fit_in(const FitRows &fr, int nt, const real *T, const void *W, real *z, hipStream_t st);
 // FP64 and FP32: E_i and dz1 [row tile][nt][256] from z [parts][row tile][zt][256]
 template <typename real>
 void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z, const void *W, const real *fb,

@@ -13,8 +13,7 @@
 // tile and four K steps contiguous) and stream from L2 straight into
 // registers, once per 16 or 32 atoms.
 //
-//   k_fit_in    z1 = D V1 (D = T<^T T formed once per block, shared in LDS;
-//               FP64: the FP32 layer is k_split_in of fitsplit.hip)
+//   k_fit_in    z1 = D V1 (D = T<^T T formed once per block, shared in LDS)
 //   k_fit_mid   y1 = tanh(z1 + c1), the two inner layers, E_i, and their
 //               input gradients down to dz1
 //   k_fit_out   dE/dD = dz1 V1^T tile by tile, contracted at once with T into
@@ -22,7 +21,7 @@
 //
 // Sums run in the same order whatever the number of rows, so an atom's
 // results do not depend on the atoms beside it: z1 is the sum of four
-// segments of K, added in order, and the part of dE/dT that sums over all
+// segments of K, added in order (FP32: one chain), and the part of dE/dT that sums over all
 // columns b is built from groups of 4, 16 and 128 of them; few rows compute
 // the innermost ones side by side.
 //
@@ -34,7 +33,8 @@
 // 1,990 -> 13 / 68 / 1,800, the
 // 240-wide layers 106 / 110 / 1,180 -> 38 / 43 / 990, dE/dD and dE/dT 14 + / 59 +
 // / 1,620 + 450 (in the embedding backward) -> 14 / 67 / 1,840.  FP32, 500 /
-// 108,000 atoms: the 240-wide layers 50 / 580 -> 21 / 475; dE/dD 900, and dE/dT in
+// 108,000 atoms: first layer 159 / 1,010 -> 24 / 1,000 (one chain of 2,048 terms, D
+// formed beside it), the 240-wide layers 50 / 580 -> 21 / 475; dE/dD 900, and dE/dT in
 // the embedding backward, -> 940 at 108,000.
 
 #include "dp_internal.h"
@@ -104,7 +104,7 @@ template <> struct Net<float> {
 };
 constexpr int kPiece = 256;   // reals of a tile
 
-// ------------------------------------------------------ first layer, FP64
+// ------------------------------------------------------------ first layer
 // One block per RT row tiles and part of K, wave w owns output tile w.  K step
 // (b, s): a = col(s, q) in lane group q.  D of the chunk's kInItems (row tile,
 // b) pairs is formed once per block, for the next chunk while the products of
@@ -115,26 +115,31 @@ constexpr int kPiece = 256;   // reals of a tile
 // after segment; else the block's part is one segment.
 constexpr int kInItems = 16;
 
-template <int RT, bool WHOLE>
-__global__ void __launch_bounds__(1024) k_fit_in(FitRows fr, int nrt, int nt, const double *__restrict__ T,
-                                                 const double *__restrict__ W, double *__restrict__ z)
+// Segments of K, whose sums are added in order: FP64 4; FP32 one chain, as each
+// rounding of a sum of 2,048 terms is felt by the forces (that of other orders
+// and of products split into BF16 parts moved them by up to 4e-5).
+template <typename real> constexpr int in_segs() { return sizeof(real) == 8 ? kFitSegs : 1; }
+
+template <typename real, int RT, bool WHOLE>
+__global__ void __launch_bounds__(1024, sizeof(real) == 4 && RT < 4 ? 8 : 4) k_fit_in(FitRows fr, int nrt, int nt, const real *__restrict__ T,
+                                                 const real *__restrict__ W, real *__restrict__ z)
 {
-    using N = Net<double>;
-    using v4 = N::v4;
+    using N = Net<real>;
+    using v4 = typename N::v4;
     HIP_DYNAMIC_SHARED(uint4, smem_raw)
     constexpr int KC = kInItems / RT;                       // b of a chunk
-    constexpr int kSegB = kM / kFitSegs;                    // b of a segment
-    constexpr int PD = RT == 4 ? 2 : 4, NB = WHOLE ? kM : kSegB, NP = WHOLE ? 1 : kFitSegs;
+    constexpr int kSegB = kM / in_segs<real>();                  // b of a segment
+    constexpr int PD = RT == 4 ? 2 : 4, NB = WHOLE ? kM : kSegB, NP = WHOLE ? 1 : in_segs<real>();
     static_assert(kSegB % KC == 0 && KC % PD == 0, "whole chunks, whole turns of the ring");
     const int wave = wave_id(), lane = threadIdx.x & 63;   // wave < nt <= 16
     const int r = lane & 15, q = lane >> 4;
     const int part = blockIdx.x % NP, tile0 = blockIdx.x / NP * RT;
     if (row_atom(fr, tile0 * 16) < 0) return;   // padding rows only
-    double *Db = reinterpret_cast<double *>(smem_raw);         // [2][item][piece]
+    real *Db = reinterpret_cast<real *>(smem_raw);         // [2][item][piece]
     v4 *Tl = reinterpret_cast<v4 *>(Db + 2 * kInItems * kPiece);   // [RT][4][64]: T(a = col(s, q))
     const v4 *Tg = reinterpret_cast<const v4 *>(T);
     auto atom_of = [&](int t) { return tile0 + t < nrt ? row_atom(fr, (tile0 + t) * 16 + r) : -1; };
-    const double *Wl = W + (long)row_type(fr, tile0 * 16) * fr.w_in + (long)wave * kPiece;   // [b][tile][piece]
+    const real *Wl = W + (long)row_type(fr, tile0 * 16) * fr.w_in + (long)wave * kPiece;   // [b][tile][piece]
     const int b0 = part * NB;
     v4 w[PD];
     auto load_w = [&](int b, int u) { w[u] = N::get(Wl + (long)b * nt * kPiece, lane); };
@@ -145,12 +150,12 @@ __global__ void __launch_bounds__(1024) k_fit_in(FitRows fr, int nrt, int nt, co
         const int at = atom_of(it % RT);
         return Tg[(long)(at >= 0 ? at : 0) * kM + b + it / RT];
     };
-    auto put_d = [&](int it, const v4 &tb, double *buf) {
+    auto put_d = [&](int it, const v4 &tb, real *buf) {
         v4 d;
 #pragma unroll
         for (int s = 0; s < 4; s++) {
             const v4 t = Tl[((it % RT) * 4 + s) * 64 + lane];
-            double x = t[0] * tb[0];
+            real x = t[0] * tb[0];
 #pragma unroll
             for (int k = 1; k < 4; k++) x = fma(t[k], tb[k], x);
             d[s] = x;
@@ -159,7 +164,7 @@ __global__ void __launch_bounds__(1024) k_fit_in(FitRows fr, int nrt, int nt, co
     };
     v4 tb = load_t(wave, b0);
     // the chunk at b into buf; then the load of the one after it
-    auto put_chunk = [&](int b, double *buf) {
+    auto put_chunk = [&](int b, real *buf) {
         put_d(wave, tb, buf);
         for (int it = wave + nt; it < kInItems; it += nt) put_d(it, load_t(it, b), buf);
         if (b + KC < b0 + NB) tb = load_t(wave, b + KC);
@@ -181,7 +186,7 @@ __global__ void __launch_bounds__(1024) k_fit_in(FitRows fr, int nrt, int nt, co
     for (int b = b0; b < b0 + NB; b += KC) {
         const int buf = ((b - b0) / KC) & 1;
         const bool more = b + KC < b0 + NB;
-        const double *D = Db + buf * kInItems * kPiece;
+        const real *D = Db + buf * kInItems * kPiece;
 #pragma unroll
         for (int k = 0; k < KC; k++) {
             if (k % (KC / 4) == 0 && more && k == turn) put_chunk(b + KC, Db + (buf ^ 1) * kInItems * kPiece);
@@ -212,23 +217,24 @@ __global__ void __launch_bounds__(1024) k_fit_in(FitRows fr, int nrt, int nt, co
 
 // The same for few rows: one wave per row tile, output tile and segment of K,
 // D formed in its registers (four waves of a block share the weights).
-__global__ void __launch_bounds__(256) k_fit_in_few(FitRows fr, int nrt, int nt, const double *__restrict__ T,
-                                                    const double *__restrict__ W, double *__restrict__ z)
+template <typename real>
+__global__ void __launch_bounds__(256) k_fit_in_few(FitRows fr, int nrt, int nt, const real *__restrict__ T,
+                                                    const real *__restrict__ W, real *__restrict__ z)
 {
-    using N = Net<double>;
-    using v4 = N::v4;
-    constexpr int PD = 4, NB = kM / kFitSegs;
+    using N = Net<real>;
+    using v4 = typename N::v4;
+    constexpr int PD = 4, NS = in_segs<real>(), NB = kM / NS;
     const int wave = wave_id(), lane = threadIdx.x & 63;
     const int r = lane & 15, q = lane >> 4;
     int item = xcd_item(blockIdx.x, gridDim.x);   // the column tiles of one row block on one XCD
-    if (item >= (nrt + 3) / 4 * nt * kFitSegs) return;
+    if (item >= (nrt + 3) / 4 * nt * NS) return;
     const int ct = item % nt;
     item /= nt;
-    const int part = item % kFitSegs, tile = item / kFitSegs * 4 + wave;
+    const int part = item % NS, tile = item / NS * 4 + wave;
     if (tile >= nrt || row_atom(fr, tile * 16) < 0) return;   // beyond the rows, or padding
     const int atom = row_atom(fr, tile * 16 + r);
     const v4 *Trow = reinterpret_cast<const v4 *>(T) + (long)(atom >= 0 ? atom : 0) * kM;
-    const double *Wl = W + (long)row_type(fr, tile * 16) * fr.w_in + (long)ct * kPiece;
+    const real *Wl = W + (long)row_type(fr, tile * 16) * fr.w_in + (long)ct * kPiece;
     const int b0 = part * NB, b1 = b0 + NB;
     v4 tl[4], w[PD], tb[PD], acc = v4{0, 0, 0, 0};
     auto load = [&](int b, int u) {
@@ -247,7 +253,7 @@ __global__ void __launch_bounds__(256) k_fit_in_few(FitRows fr, int nrt, int nt,
         for (int u = 0; u < PD; u++) {
 #pragma unroll
             for (int s = 0; s < 4; s++) {
-                double x = tl[s][0] * tb[u][0];
+                real x = tl[s][0] * tb[u][0];
 #pragma unroll
                 for (int k = 1; k < 4; k++) x = fma(tl[s][k], tb[u][k], x);
                 acc = N::mfma(w[u][s], x, acc);
@@ -575,7 +581,7 @@ __global__ void __launch_bounds__(64 * out_waves(LEVEL), 2) k_fit_out(FitRows fr
 // Rows of 16 that a launch covers.
 int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
 
-// Row tiles from which on the first layer's (FP64) K stays whole, and up to
+// Row tiles from which on the first layer's K stays whole (FP64), and up to
 // which it is left to single waves.
 constexpr int kInWholeTiles = 1250, kInFewTiles = 48;
 // Row tiles up to which the input gradient's sums over all columns are left
@@ -585,22 +591,29 @@ constexpr int kOut4Tiles = 64, kOut32Tiles = 256, kOut8Tiles = 1024;
 }  // namespace
 
 // ----------------------------------------------------------- launchers
-int fit_in_parts(const FitRows &fr) { return row_tiles(fr) < kInWholeTiles ? kFitSegs : 1; }
+template <typename real>
+int fit_in_parts(const FitRows &fr) { return row_tiles(fr) < kInWholeTiles ? in_segs<real>() : 1; }
+template int fit_in_parts<double>(const FitRows &);
+template int fit_in_parts<float>(const FitRows &);
 
-void launch_fit_in(const FitRows &fr, int nt, const double *T, const void *W, double *z, hipStream_t st)
+template <typename real>
+void launch_fit_in(const FitRows &fr, int nt, const real *T, const void *W, real *z, hipStream_t st)
 {
-    const int nrt = row_tiles(fr);
+    constexpr bool f64 = sizeof(real) == 8;
+    const int nrt = row_tiles(fr), segs = in_segs<real>();
     auto go = [&](auto kern, int RT, int parts) {
-        const size_t lds = (size_t)(2 * kInItems + 4 * RT) * kPiece * sizeof(double);
-        hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT) * parts), dim3(64 * nt), lds, st, fr, nrt, nt, T, (const double *)W, z);
+        const size_t lds = (size_t)(2 * kInItems + 4 * RT) * kPiece * sizeof(real);
+        hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT) * parts), dim3(64 * nt), lds, st, fr, nrt, nt, T, (const real *)W, z);
     };
     if (nrt <= kInFewTiles)
-        hipLaunchKernelGGL(k_fit_in_few, dim3(xcd_grid(div_up(nrt, 4) * nt * kFitSegs)), dim3(256), 0, st, fr, nrt, nt, T,
-                           (const double *)W, z);
-    else if (nrt < 512) go(k_fit_in<1, false>, 1, kFitSegs);
-    else if (nrt < kInWholeTiles) go(k_fit_in<2, false>, 2, kFitSegs);
-    else go(k_fit_in<4, true>, 4, 1);
+        hipLaunchKernelGGL(k_fit_in_few<real>, dim3(xcd_grid(div_up(nrt, 4) * nt * segs)), dim3(256), 0, st, fr, nrt, nt, T,
+                           (const real *)W, z);
+    else if (nrt < 512) go(k_fit_in<real, 1, !f64>, 1, segs);
+    else if (nrt < kInWholeTiles) go(k_fit_in<real, 2, !f64>, 2, segs);
+    else go(k_fit_in<real, 4, true>, 4, 1);
 }
+template void launch_fit_in<double>(const FitRows &, int, const double *, const void *, double *, hipStream_t);
+template void launch_fit_in<float>(const FitRows &, int, const float *, const void *, float *, hipStream_t);
 
 template <typename real>
 void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z, const void *W, const real *fb,

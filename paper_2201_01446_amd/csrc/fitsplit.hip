@@ -1,20 +1,13 @@
-// fitsplit.hip -- products of the compressed step's fitting net on the BF16
-// matrix cores, over operands split into BF16 parts (gfx950): the first layer
-// in FP32, and the whole net, from T to dE/dT, in mixed precision.
+// fitsplit.hip -- the compressed step's fitting net in mixed precision, from T to
+// dE/dT, as products on the BF16 matrix cores over operands split into two BF16
+// parts (gfx950).
 //
-// An FP32 operand x is the sum of BF16 parts x0 = bf16(x), x1 = bf16(x - x0),
-// x2 = bf16(x - x0 - x1), and a product of two operands the sum of the products
-// of their parts, accumulated in FP32:
-//   FP32    w0 x0 + w0 x1 + w1 x0 + w1 x1 + w0 x2 + w2 x0: three parts hold the
-//           24 bits of an FP32 number, and what is left out is below 2^-24 of
-//           the product, so the sum is as exact as one of FP32 products (and
-//           rounds less often: the 32 terms of an instruction enter the
-//           accumulator together);
-//   mixed   w0 x0 over all of K, then w1 x0, then w0 x1 (two parts).
-// v_mfma_f32_16x16x32_bf16 does 16 times the work of the FP32 instruction per
-// clock, so six products still cost less than half of one in FP32.  (The other
-// FP32 products stay FP32, in fitnet.hip: their K is 240, and the forces feel
-// every rounding of dE/dD.)
+// An operand x is the sum of x0 = bf16(x) and x1 = bf16(x - x0) to 16 bits, and a
+// product the sum of w0 x0 over all of K, then w1 x0, then w0 x1, accumulated in
+// FP32.  (FP32 products as six of three parts each were as exact as, and 1.8 times
+// as fast as, the FP32 first layer, but their other rounding moved the forces of
+// one model in eleven by more than 2e-5; so that precision stays on the FP32
+// instructions, in fitnet.hip.)
 //
 // The layout is that of fitnet.hip: lane (r, q) carries atom r, and a result
 // tile holds columns 4 q + i in register i.  A block has one wave per pair of
@@ -24,8 +17,7 @@
 //
 // Sums run in an order that does not depend on the number of rows.
 //
-// Measured (microseconds): FP32 first layer, 500 / 13,500 / 108,000 atoms,
-// 159 / 174 / 1,010 as a tiled FP32 GEMM -> 12 / 85 / 545; mixed, 62,500 atoms,
+// Measured (microseconds), 62,500 atoms:
 // first layer, inner layers and energy 333 + 430 -> 476, dE/dD and dE/dT 337 +
 // 130 -> 314, and no D through HBM (embedding forward 533 -> 400).
 
@@ -55,181 +47,6 @@ __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadId
 // Keeps the loads issued before it where they are (the compiler otherwise
 // moves the loads of a ring down to their use).
 __device__ inline void keep_order() { __builtin_amdgcn_sched_barrier(0); }
-
-// Parts of eight values.
-template <int NP>
-__device__ inline void split8(const float (&x)[8], bf8v (&p)[NP])
-{
-    float r[8];
-#pragma unroll
-    for (int j = 0; j < 8; j++) r[j] = x[j];
-#pragma unroll
-    for (int n = 0; n < NP; n++)
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            p[n][j] = (__bf16)r[j];
-            if (n + 1 < NP) r[j] -= (float)p[n][j];
-        }
-}
-
-// The six products, the smallest first: part of the weights, part of the operand.
-__device__ constexpr int prod_w(int p) { return p == 0 ? 2 : (p == 2 || p == 3) ? 1 : 0; }
-__device__ constexpr int prod_x(int p) { return p == 1 ? 2 : (p == 2 || p == 4) ? 1 : 0; }
-
-// acc[c][r] += w[c] x[r] over one K step, RT row tiles and CT column tiles
-template <int RT, int CT>
-__device__ inline void mul_step(const bf8v (&w)[CT][3], const bf8v (&x)[RT][3], f4v (&acc)[CT][RT])
-{
-#pragma unroll
-    for (int p = 0; p < 6; p++)
-#pragma unroll
-        for (int r = 0; r < RT; r++)
-#pragma unroll
-            for (int c = 0; c < CT; c++)
-                acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[c][prod_w(p)], x[r][prod_x(p)], acc[c][r], 0, 0, 0);
-}
-
-// ----------------------------------------------------- first layer, FP32
-// K step bp: columns b = 2 bp, 2 bp + 1 of D, a = 4 q + j mod 4.  The block
-// forms D for kInItems (row tile, K step) pairs at a time, split into LDS for
-// the next chunk while the products of the present one run.  K step bp takes
-// element j of lane group q from a = 4 q + j mod 4, b = 2 bp + j / 4.
-constexpr int kInItems = 16;
-constexpr int kInSteps = kM / 2;                       // K steps of the layer
-constexpr int kInSegSteps = kInSteps / kFitSegs;       // of a segment
-
-template <int RT>
-__global__ void __launch_bounds__(512) k_split_in(FitRows fr, int nrt, int ks, int nparts, const float *__restrict__ T,
-                                                  const bf8v *__restrict__ W, float *__restrict__ z)
-{
-    HIP_DYNAMIC_SHARED(uint4, smem_raw)
-    constexpr int NP = 3;
-    constexpr int KC = kInItems / RT;   // K steps of a chunk
-    static_assert(kInSegSteps % KC == 0, "a segment is whole chunks");
-    const int wave = wave_id(), lane = threadIdx.x & 63;
-    const int r = lane & 15, q = lane >> 4;
-    const int part = blockIdx.x % nparts, tile0 = blockIdx.x / nparts * RT;
-    bool live = false;
-#pragma unroll
-    for (int t = 0; t < RT; t++) live = live || (tile0 + t < nrt && row_atom(fr, (tile0 + t) * 16) >= 0);
-    if (!live) return;   // padding rows only
-    const int ty = row_type(fr, tile0 * 16);
-    bf8v *Db = reinterpret_cast<bf8v *>(smem_raw);                 // [2][item][NP][64]
-    f4v *Tl = reinterpret_cast<f4v *>(Db + 2 * kInItems * NP * 64);   // [RT][4][64]: T(a = 4 q + j)
-    auto atom_of = [&](int t) { return tile0 + t < nrt ? row_atom(fr, (tile0 + t) * 16 + r) : -1; };
-    const f4v *Tg = reinterpret_cast<const f4v *>(T);
-    for (int k = wave; k < RT * 4; k += ks) {
-        const int at = atom_of(k >> 2);
-        const f4v v = Tg[(long)(at >= 0 ? at : 0) * kM + 4 * q + (k & 3)];
-        Tl[k * 64 + lane] = at >= 0 ? v : f4v{0, 0, 0, 0};   // rows without an atom: D = 0
-    }
-    // item it: row tile it % RT, K step it / RT of the chunk
-    auto load_t = [&](int it, int bp, f4v (&tb)[2]) {
-        const int at = atom_of(it % RT);
-        const f4v *p = Tg + (long)(at >= 0 ? at : 0) * kM + 2 * (bp + it / RT);
-        tb[0] = p[0];
-        tb[1] = p[1];
-    };
-    auto put_d = [&](int it, const f4v (&tb)[2], bf8v *buf) {
-        float d[8];
-#pragma unroll
-        for (int a = 0; a < 4; a++) {
-            const f4v t = Tl[((it % RT) * 4 + a) * 64 + lane];
-#pragma unroll
-            for (int s = 0; s < 2; s++) {
-                float x = t[0] * tb[s][0];
-#pragma unroll
-                for (int k = 1; k < 4; k++) x = fmaf(t[k], tb[s][k], x);
-                d[4 * s + a] = x;
-            }
-        }
-        bf8v p[NP];
-        split8<NP>(d, p);
-#pragma unroll
-        for (int n = 0; n < NP; n++) buf[(it * NP + n) * 64 + lane] = p[n];
-    };
-    const int s0 = part * (kInSteps / nparts), s1 = s0 + kInSteps / nparts;
-    const int it0 = wave, it1 = wave + ks;   // with eight waves the only two
-    f4v tb0[2], tb1[2];
-    auto load_chunk = [&](int bp) {
-        load_t(it0, bp, tb0);
-        if (it1 < kInItems) load_t(it1, bp, tb1);
-    };
-    auto put_chunk = [&](int bp, bf8v *buf) {
-        put_d(it0, tb0, buf);
-        if (it1 < kInItems) put_d(it1, tb1, buf);
-        for (int it = it1 + ks; it < kInItems; it += ks) {
-            f4v tb[2];
-            load_t(it, bp, tb);
-            put_d(it, tb, buf);
-        }
-        if (bp + KC < s1) load_chunk(bp + KC);
-    };
-    // the two waves of a SIMD do that at different times, so that the other's
-    // products go on
-    const int turn = (wave >> 2) * (KC / 2);
-    // weights [K step][tile][part][lane], two K steps ahead
-    const bf8v *Wl = W + (long)ty * fr.w_in + (long)wave * 2 * NP * 64;
-    bf8v w[2][2][NP];
-    auto load_w = [&](int bp, int u) {
-        const bf8v *p = Wl + (long)bp * ks * 2 * NP * 64;
-#pragma unroll
-        for (int c = 0; c < 2; c++)
-#pragma unroll
-            for (int n = 0; n < NP; n++) w[u][c][n] = p[(c * NP + n) * 64 + lane];
-    };
-    f4v acc[2][RT], tot[2][RT];
-#pragma unroll
-    for (int c = 0; c < 2; c++)
-#pragma unroll
-        for (int t = 0; t < RT; t++) {
-            acc[c][t] = f4v{0, 0, 0, 0};
-            tot[c][t] = f4v{0, 0, 0, 0};
-        }
-    load_chunk(s0);
-    load_w(s0, 0);
-    load_w(s0 + 1, 1);
-    __syncthreads();
-    put_chunk(s0, Db);
-    __syncthreads();
-    for (int s = s0; s < s1; s += KC) {
-        const int buf = ((s - s0) / KC) & 1;
-        const bool more = s + KC < s1;
-        const bf8v *D = Db + buf * kInItems * NP * 64;
-#pragma unroll 2
-        for (int k = 0; k < KC; k += 2) {
-            if (more && k == turn) put_chunk(s + KC, Db + (buf ^ 1) * kInItems * NP * 64);
-#pragma unroll
-            for (int u = 0; u < 2; u++) {
-                bf8v x[RT][NP];
-#pragma unroll
-                for (int t = 0; t < RT; t++)
-#pragma unroll
-                    for (int n = 0; n < NP; n++) x[t][n] = D[(((k + u) * RT + t) * NP + n) * 64 + lane];
-                mul_step<RT, 2>(w[u], x, acc);
-                load_w(min(s + k + u + 2, s1 - 1), u);
-                keep_order();
-            }
-        }
-        if ((s + KC) % kInSegSteps == 0) {
-#pragma unroll
-            for (int c = 0; c < 2; c++)
-#pragma unroll
-                for (int t = 0; t < RT; t++) {
-                    tot[c][t] += acc[c][t];
-                    acc[c][t] = f4v{0, 0, 0, 0};
-                }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int t = 0; t < RT; t++)
-        if (tile0 + t < nrt) {
-#pragma unroll
-            for (int c = 0; c < 2; c++)
-                reinterpret_cast<f4v *>(z)[((long)(part * nrt + tile0 + t) * 2 * ks + 2 * wave + c) * 64 + lane] = tot[c][t];
-        }
-}
 
 // ---------------------------------------------------------------- mixed
 // K runs in its natural order, K step g: element j of lane group q is k = 32 g
@@ -683,28 +500,13 @@ __global__ void __launch_bounds__(64 * WPB) k_mix_out(FitRows fr, int nrt, int k
 
 int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
 
-// Rows up to which the FP32 first layer's segments of K, and the mixed input
-// gradient's groups of 16 columns, go to blocks of their own.
+// Rows up to which the input gradient's groups of 16 columns go to blocks of
+// their own.
 constexpr int kSplitRows = 8192;
 
 }  // namespace
 
 // ----------------------------------------------------------- launchers
-int split_in_parts(const FitRows &fr) { return row_tiles(fr) * 16 <= kSplitRows ? kFitSegs : 1; }
-
-void launch_split_in(const FitRows &fr, int nt, const float *T, const void *W, float *z, hipStream_t st)
-{
-    const int nrt = row_tiles(fr), ks = div_up(nt, 2), parts = split_in_parts(fr);
-    auto go = [&](auto kern, int RT) {
-        const size_t lds = (size_t)2 * kInItems * 3 * 1024 + RT * 4096;
-        hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT) * parts), dim3(64 * ks), lds, st, fr, nrt, ks, parts, T,
-                           (const bf8v *)W, z);
-    };
-    if (nrt <= 64) go(k_split_in<1>, 1);
-    else if (parts > 1) go(k_split_in<2>, 2);
-    else go(k_split_in<4>, 4);
-}
-
 void launch_mix_fwd(const FitRows &fr, int nt, const float *T, const FitWeights &fw, const float *fb,
                     const float *tanh_tab, float *z, double *e_atom, void *dz1, hipStream_t st)
 {

@@ -118,21 +118,6 @@ __global__ void k_pack_mid(long n, int nt, MidMats M, real *__restrict__ out)
 
 constexpr int kBf = 512;   // BF16 elements of a tile and K step: 64 lanes x 8
 
-// The first layer as three BF16 parts in the lane order of the FP32 kernel of
-// fitsplit.hip: [type][K step][tile][part][lane][8], element j of lane l: a = 4 (l
-// / 16) + j mod 4, b = 2 (K step) + j / 4.
-__global__ void k_pack_split3(long n, int nt, const double *__restrict__ V1, unsigned short *__restrict__ out)
-{
-    const long id = thread_of();
-    if (id >= n) return;
-    const int e = (int)(id % kBf), l = e / 8, j = e % 8;
-    const long p = id / kBf;
-    const int ot = (int)(p % nt), bp = (int)(p / nt % (kM / 2));
-    const long t = p / nt / (kM / 2);
-    const int a = 4 * (l / 16) + j % 4, b = 2 * bp + j / 4;
-    put_parts(out + p * 3 * kBf + e, kBf, 3, V1[t * kDdim * kFitPad + (long)(a * kM + b) * kFitPad + 16 * ot + l % 16]);
-}
-
 // The weights as two BF16 parts in the lane order of the mixed kernels of
 // fitsplit.hip: K in its natural order, element j of lane l of K step g: k =
 // 32 g + 8 (l / 16) + j.  in [type][part][K step][tile][lane][8]; mid [type]
@@ -178,10 +163,8 @@ template <typename real>
 dp_status pack_fitnet(const FitWeights &d, FitWeights &w, int ntypes, int nt, const MidMats &mm)
 {
     const long nf = (long)ntypes * kM * nt * 256, nm = (long)ntypes * 4 * nt * nt * 256;
-    if (sizeof(real) == 8) {   // (the FP32 first layer takes split products)
-        DP_HIP(hipMalloc(&w.in, nf * sizeof(real)));
-        DP_PACK((k_pack_first<real, true>), nf, nt, (const double *)d.V1, (real *)w.in);
-    }
+    DP_HIP(hipMalloc(&w.in, nf * sizeof(real)));
+    DP_PACK((k_pack_first<real, true>), nf, nt, (const double *)d.V1, (real *)w.in);
     DP_HIP(hipMalloc(&w.mid, nm * sizeof(real)));
     DP_HIP(hipMalloc(&w.out, nf * sizeof(real)));
     DP_PACK(k_pack_mid<real>, nm, nt, mm, (real *)w.mid);
@@ -217,13 +200,11 @@ dp_status pack_weights(FitWeights &d, FitWeights &w32, FitWeights &wbf, int ntyp
     if ((s = pack_fitnet<double>(d, d, ntypes, nt, mm)) != DP_OK) return s;
     if ((s = pack_fitnet<float>(d, w32, ntypes, nt, mm)) != DP_OK) return s;
     const double *V1 = (const double *)d.V1;
-    const long ns = (long)ntypes * (kM / 2) * 2 * ks * kBf, ni = (long)ntypes * (kDdim / 32) * 2 * ks * kBf,
+    const long ni = (long)ntypes * (kDdim / 32) * 2 * ks * kBf,
                nm = (long)ntypes * 4 * ks * 2 * ks * kBf, no = (long)ntypes * kM * ks * kBf;
-    DP_HIP(hipMalloc(&w32.in, 3 * ns * sizeof(short)));
     DP_HIP(hipMalloc(&wbf.in, 2 * ni * sizeof(short)));
     DP_HIP(hipMalloc(&wbf.mid, 2 * nm * sizeof(short)));
     DP_HIP(hipMalloc(&wbf.out, 2 * no * sizeof(short)));
-    DP_PACK(k_pack_split3, ns, 2 * ks, V1, (unsigned short *)w32.in);
     DP_PACK(k_pack_mix_in, ni, 2 * ks, V1, (unsigned short *)wbf.in);
     DP_PACK(k_pack_mix_mid, nm, ks, mm, (unsigned short *)wbf.mid);
     DP_PACK(k_pack_mix_out, no, ks, V1, (unsigned short *)wbf.out);
