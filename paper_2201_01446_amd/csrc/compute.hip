@@ -96,9 +96,9 @@ WS carve(void *base, int np, int precision, int sel)
     return w;
 }
 
-// The compressed step's fitting net from T to dE/dT: fitnet.hip (FP64; FP32
-// but for its first layer) and fitsplit.hip (FP32's first layer, mixed).  z and
-// the parts of dE/dT that sum over all columns take dD's place, dz1 that of D.
+// The compressed step's fitting net from T to dE/dT: fitnet.hip (FP64, FP32) and
+// fitsplit.hip (mixed).  z and the parts of dE/dT that sum over all columns take
+// dD's place, dz1 that of D.
 template <typename TA, typename TR>
 struct FitNet {
     const FitWeights &fw;
