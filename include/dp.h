@@ -341,8 +341,11 @@ dp_status dp_batch_create(dp_model *model, int max_atoms, int max_requests, doub
 dp_status dp_batch_destroy(dp_batch *batch);
 /* energy_d[nreq], force_d[total*3], virial_d[nreq*9], atom_energy_d[total]
  * (device, FP64, NULL skips).  Enqueued on `stream`; one batch object must
- * not be used by two streams at once.  Returns DP_ERR_CAPACITY when the
- * requests exceed max_atoms or max_requests. */
+ * not be used by two streams at once.  `model` may be another than the one
+ * the batch was created for: its rcut must lie below that one's rcut + skin
+ * (DP_ERR_ARG), and one that keeps more neighbors (sel) grows the batch's
+ * scratch at its first call.  Returns DP_ERR_CAPACITY when the requests
+ * exceed max_atoms or max_requests. */
 dp_status dp_batch_compute(dp_model *model, dp_batch *batch, int nreq, const dp_request *reqs_h,
                            const double *coords_d, int precision, double *energy_d,
                            double *force_d, double *virial_d, double *atom_energy_d, void *stream);

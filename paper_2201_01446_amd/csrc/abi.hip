@@ -902,6 +902,7 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
     hipStream_t st = (hipStream_t)stream;
     dp_nlist *nl = b->nl;
     double rcs = nl->rc_build;
+    if (m->cfg.rcut >= rcs) return fail(DP_ERR_ARG, "the model's rcut reaches past the batch's rcut + skin");
     long total = 0;
     int cellcap = 0;
     bool uniq = true;   // no list holds two images of one atom
@@ -937,6 +938,9 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
         groups.back().nmax = std::max(groups.back().nmax, q.natoms);
     }
     if (total > b->max_atoms) return fail(DP_ERR_CAPACITY, "batch exceeds max_atoms");
+    // the scratch was sized for the model of dp_batch_create; another may keep more neighbors
+    dp_status s = ensure_ws(nl, precision, m->cfg.sel);
+    if (s != DP_OK) return s;
     long cells = 0;
     for (const Group &g : groups) cells = std::max(cells, g.cells);
     cellcap = std::max(cellcap, nl->cellcap);
@@ -988,8 +992,7 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
                            g == 0, coords_d, b->ireq, st);
     }
     launch_reverse(nl, 0, (int)total, st, uniq);
-    dp_status s = step_check("batch_nlist", st);
-    if (s != DP_OK) return s;
+    if ((s = step_check("batch_nlist", st)) != DP_OK) return s;
     nl->fwd_token = 0;
     ComputeArgs a{};
     a.m = m;

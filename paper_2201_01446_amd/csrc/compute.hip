@@ -333,6 +333,7 @@ dp_status ensure_ws(dp_nlist *nl, int precision, int sel)
     nl->ws_bytes = need;
     // rows past natoms are read by GEMM tiles: keep them finite (zero)
     DP_HIP(hipMemset(nl->ws, 0, need));
+    DP_HIP(hipStreamSynchronize(nullptr));   // a caller's stream need not wait for the null stream
     return DP_OK;
 }
 
