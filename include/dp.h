@@ -226,8 +226,8 @@ dp_status dp_compute_noalloc(dp_model *model, dp_nlist *nlist, int natoms, const
  * which recomputes G and G' from the table (G is never stored).  The two
  * halves give E, F and W bit-identical to one dp_compute call.
  * It writes F = -dE/dx and/or W.  coords_d must be the forward's coordinates.
- * DP_ERR_STATE if no forward of the same mode and precision is kept (any other
- * compute on the list discards it). */
+ * DP_ERR_STATE if no forward of the same mode, precision and sel is kept (any
+ * other compute on the list discards it). */
 dp_status dp_energy_forward(dp_model *model, dp_nlist *nlist, int natoms, const double *coords_d,
                             int mode, int precision, double *energy_d, double *atom_energy_d,
                             void *stream);

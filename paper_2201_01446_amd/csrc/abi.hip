@@ -558,8 +558,10 @@ static dp_status compute_common(dp_model *m, dp_nlist *nl, int natoms, const dou
 {
     dp_status s = check_compute_args(m, nl, natoms, x, mode, precision);
     if (s != DP_OK) return s;
-    if (phase == 2 && nl->fwd_token != precision + 1 + 8 * mode)
-        return fail(DP_ERR_STATE, "no kept forward of this precision and mode on this list");
+    // what a forward keeps is laid out by its precision, mode and sel
+    const int token = precision + 1 + 8 * mode + 64 * m->cfg.sel;
+    if (phase == 2 && nl->fwd_token != token)
+        return fail(DP_ERR_STATE, "no kept forward of this precision, mode and sel on this list");
     if (noalloc) {
         // the plain rungs keep their activations in a scratch of their own
         if (mode == DP_PLAIN || mode == DP_TAB_UNFUSED)
@@ -585,7 +587,7 @@ static dp_status compute_common(dp_model *m, dp_nlist *nl, int natoms, const dou
     a.phase = phase;
     a.noalloc = noalloc;
     // any forward overwrites the kept activations
-    nl->fwd_token = phase == 1 ? precision + 1 + 8 * mode : (phase == 2 ? nl->fwd_token : 0);
+    nl->fwd_token = phase == 1 ? token : (phase == 2 ? nl->fwd_token : 0);
     a.mode = mode;
     return (mode == DP_PLAIN || mode == DP_TAB_UNFUSED) ? run_plain(a, st) : run_compressed(a, st);
 }

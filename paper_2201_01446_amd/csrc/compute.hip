@@ -328,6 +328,7 @@ dp_status ensure_ws(dp_nlist *nl, int precision, int sel)
     if (nl->ws) DP_HIP(hipFree(nl->ws));
     nl->ws = nullptr;
     nl->ws_bytes = 0;
+    nl->fwd_token = 0;   // a kept forward goes with it
     hipError_t e = hipMalloc(&nl->ws, need);
     if (e != hipSuccess) return fail(DP_ERR_OOM, "workspace allocation failed");
     nl->ws_bytes = need;

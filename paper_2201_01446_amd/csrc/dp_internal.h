@@ -147,7 +147,7 @@ struct dp_nlist {
     size_t ws_plain_bytes = 0;
     double *atomL = nullptr;       // per-atom box edges when the list spans a batch of cells
     double *force_tmp = nullptr;   // forces when the caller wants only the virial
-    int fwd_token = 0;             // precision+1 while a forward's activations are kept
+    int fwd_token = 0;             // precision, mode and sel of the forward whose activations are kept; 0: none
     double *scal = nullptr;        // [16] device scalars (energy, partial sums)
     // the trajectory left by the last dp_nve_run / dp_nve_continue on this
     // list, from which dp_nve_continue resumes: forces (nve_F) and energy
