@@ -352,8 +352,11 @@ dp_status dp_batch_compute(dp_model *model, dp_batch *batch, int nreq, const dp_
 /* Counters of the last batch (synchronises), as dp_nlist_stats. */
 dp_status dp_batch_stats(dp_batch *batch, int *max_nei, int *n_sel_overflow, int *n_table_oob,
                          int *n_cap_overflow);
-/* Device bytes one evaluation of natoms atoms needs (neighbor list and
- * scratch): the unit of the serving loop's HBM admission. */
+/* Device bytes one evaluation of natoms atoms needs (neighbor list, cell grids
+ * and scratch): the unit of the serving loop's HBM admission.  The cell grids
+ * count as a batch reserves them, for cells of ordinary density; boxes so sparse
+ * that they need more grow a batch's grids to at most 65 MB, or to those of its
+ * largest single request. */
 dp_status dp_footprint_bytes(const dp_model *model, int natoms, size_t *bytes);
 
 /* Kernel timing for measurement: while enabled, every kernel launch of the

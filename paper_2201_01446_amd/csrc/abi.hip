@@ -6,6 +6,7 @@
 #include "env.h"
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -28,6 +29,7 @@ dp_status fail(dp_status st, const std::string &msg)
 dp_status hip_fail(hipError_t e, const char *what)
 {
     g_err = std::string(what) + ": " + hipGetErrorString(e);
+    (void)hipGetLastError();   // reported here: the next call's checks must not find it again
     return e == hipErrorOutOfMemory ? DP_ERR_OOM : DP_ERR_HIP;
 }
 
@@ -224,9 +226,52 @@ dp_status prepare_nlist(const dp_model *m, int natoms, const double *box, double
     return DP_OK;
 }
 
-// Cells of all the requests of a batch that are binned together (64 MB of
-// slots at a cell capacity of 32).
-constexpr long kBatchCells = 1 << 16;
+// Requests of a batch are binned together in groups of at most kBatchCells cells
+// and kBatchSlots atom slots (cells times their capacity; 65 MB with the counts),
+// so that the shared grids stay bounded whatever the mix: one crowded cell sets
+// the capacity of all, and sparse boxes have many cells.  A larger single
+// request is a group of its own.
+constexpr long kBatchCells = 1 << 16, kBatchSlots = 1 << 21;
+
+// Slots that a batch reserves when it is created: 32 an atom, what ordinary
+// cells need beside a crowded one (copper: 4.5 among its like, 25 beside a box
+// of one cell with 85 atoms).  Sparser ones grow the grids (grid_slots).
+long batch_slots(long natoms) { return std::min(kBatchSlots, 32 * natoms); }
+
+// The next size of grids that need `need` slots: doubled up to kBatchSlots, so
+// that batches of growing size do not wait for an allocation each.
+long grid_slots(long need, long have) { return std::max(need, std::min(kBatchSlots, 2 * have)); }
+
+// Bytes of that many slots and of their cells' counts (a cell has 8 slots or more).
+size_t grid_bytes(long slots) { return (size_t)slots * sizeof(CellAtom) + (size_t)slots / 8 * sizeof(int); }
+
+dp_status alloc_grids(dp_nlist *nl, long slots)
+{
+    if (nl->cell_atoms) DP_HIP(hipFree(nl->cell_atoms));
+    if (nl->cell_cnt) DP_HIP(hipFree(nl->cell_cnt));
+    nl->cell_atoms = nullptr;
+    nl->cell_cnt = nullptr;
+    nl->ncell_alloc = 0;
+    DP_HIP(hipMalloc(&nl->cell_atoms, sizeof(CellAtom) * (size_t)slots));
+    DP_HIP(hipMalloc(&nl->cell_cnt, sizeof(int) * ((size_t)slots / 8)));
+    nl->ncell_alloc = (size_t)slots;
+    return DP_OK;
+}
+
+// A batch's requests in groups that are binned together.
+struct BatchGroup {
+    long cells = 0;
+    int nmax = 0;   // atoms of its largest request
+    // whether a request of n atoms and ncell cells joins (else it begins the next group)
+    bool take(long ncell, int n, int cellcap)
+    {
+        const long c = cells + ncell;
+        if (nmax && (c > kBatchCells || c * cellcap > kBatchSlots)) return false;
+        cells = c;
+        nmax = std::max(nmax, n);
+        return true;
+    }
+};
 
 // Bytes of a batch's request table: the cells and the atom offsets.
 size_t request_table_bytes(int max_req) { return sizeof(BatchCell) * max_req + sizeof(int) * ((size_t)max_req + 1); }
@@ -825,7 +870,7 @@ dp_status dp_footprint_bytes(const dp_model *m, int natoms, size_t *bytes)
     size_t ws = std::max(ws_bytes_for_atoms(natoms, DP_FP64, m->cfg.sel, m->cfg.ntypes),
                          ws_bytes_for_atoms(natoms, DP_MIXED_BF16, m->cfg.sel, m->cfg.ntypes));
     if (m->cfg.ntypes > 1) per += 4 * (2 + kMaxTypes) + 4;   // type, row, per-type counts, row map
-    *bytes = per * (size_t)natoms + ws;
+    *bytes = per * (size_t)natoms + ws + grid_bytes(batch_slots(natoms));
     return DP_OK;
 }
 
@@ -870,8 +915,9 @@ dp_status dp_batch_create(dp_model *m, int max_atoms, int max_requests, double s
     DP_HIP(hipHostMalloc((void **)&b->req_h, table, hipHostMallocDefault));
     DP_HIP(hipMalloc(&b->ireq, sizeof(int) * A));
     DP_HIP(hipEventCreateWithFlags(&b->staged, hipEventDisableTiming));
-    dp_status s = ensure_ws(nl, DP_FP64, m->cfg.sel);
+    dp_status s = alloc_grids(nl, batch_slots(max_atoms));
     if (s != DP_OK) return s;
+    if ((s = ensure_ws(nl, DP_FP64, m->cfg.sel)) != DP_OK) return s;
     *out = b;
     return DP_OK;
 }
@@ -908,13 +954,6 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
     long total = 0;
     int cellcap = 0;
     bool uniq = true;   // no list holds two images of one atom
-    // the requests are binned together, in as many groups as keep the cells of
-    // a group within kBatchCells (a larger single request is a group of its own)
-    struct Group {
-        int r0, nmax;
-        long cells;
-    };
-    std::vector<Group> groups;
     for (int r = 0; r < nreq; r++) {
         const dp_request &q = reqs[r];
         if (q.natoms < 1 || q.offset != total) return fail(DP_ERR_ARG, "requests must be contiguous and non-empty");
@@ -924,10 +963,14 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
             double L[3];
             int nc[3], R[3];
             if (!box_ok(q.box, L)) return fail(DP_ERR_UNSUPPORTED, "box must be orthorhombic");
+            double grid = 1;
             for (int a = 0; a < 3; a++) {
                 if (L[a] < 0.5 * rcs) return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
                 uniq = uniq && L[a] >= 2 * rcs;
+                grid *= std::floor(L[a] / (0.5 * rcs));
             }
+            // (cells are numbered in 32 bits; that many would take a terabyte)
+            if (grid > INT_MAX) return fail(DP_ERR_OOM, "the box has too many cells");
             if (!cell_axes(L, rcs, nc, R)) return fail(DP_ERR_UNSUPPORTED, "box edge shorter than (rcut + skin) / 2");
             ncell = (long)nc[0] * nc[1] * nc[2];
             const int per = (int)std::ceil((double)q.natoms / ncell);
@@ -935,63 +978,55 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
         } else if (q.natoms > kCapMax) {
             return fail(DP_ERR_UNSUPPORTED, "open clusters in a batch hold at most 1024 atoms");
         }
-        if (groups.empty() || groups.back().cells + ncell > kBatchCells) groups.push_back({r, 0, 0});
-        groups.back().cells += ncell;
-        groups.back().nmax = std::max(groups.back().nmax, q.natoms);
     }
     if (total > b->max_atoms) return fail(DP_ERR_CAPACITY, "batch exceeds max_atoms");
     // the scratch was sized for the model of dp_batch_create; another may keep more neighbors
     dp_status s = ensure_ws(nl, precision, m->cfg.sel);
     if (s != DP_OK) return s;
-    long cells = 0;
-    for (const Group &g : groups) cells = std::max(cells, g.cells);
     cellcap = std::max(cellcap, nl->cellcap);
-    if ((size_t)cells * cellcap > nl->ncell_alloc || (cells && !nl->cell_cnt)) {
-        // grow the cell grids (rare: only for more cells than seen before)
-        DP_HIP(hipStreamSynchronize(st));
-        if (nl->cell_atoms) DP_HIP(hipFree(nl->cell_atoms));
-        if (nl->cell_cnt) DP_HIP(hipFree(nl->cell_cnt));
-        nl->cell_atoms = nullptr;
-        nl->cell_cnt = nullptr;
-        nl->ncell_alloc = 0;
-        const size_t nc = std::max((size_t)cells, (size_t)1);
-        DP_HIP(hipMalloc(&nl->cell_atoms, sizeof(CellAtom) * nc * cellcap));
-        DP_HIP(hipMalloc(&nl->cell_cnt, sizeof(int) * nc * cellcap));
-        nl->ncell_alloc = nc * cellcap;
-    }
-    nl->cellcap = cellcap ? cellcap : nl->cellcap;
     // request table: the staging buffer is reused, so wait for the last upload
     DP_HIP(hipEventSynchronize(b->staged));
     int *off_h = reinterpret_cast<int *>(b->req_h + b->max_req);
     int *off_d = reinterpret_cast<int *>(b->req_d + b->max_req);
-    size_t gi = 0;
-    int cell0 = 0;
+    long slots = 0;   // of the largest group
+    BatchGroup g;
     for (int r = 0; r < nreq; r++) {
-        if (gi < groups.size() && groups[gi].r0 == r) {
-            gi++;
-            cell0 = 0;
-        }
         BatchCell c{};
         c.off = reqs[r].offset;
         c.n = reqs[r].natoms;
         if (reqs[r].periodic) {
             box_ok(reqs[r].box, c.L);
             cell_axes(c.L, rcs, c.nc, c.R);
-            c.cell0 = cell0;
-            cell0 += c.nc[0] * c.nc[1] * c.nc[2];
         }
+        const long ncell = (long)c.nc[0] * c.nc[1] * c.nc[2];
+        c.cell0 = (int)g.cells;
+        if (!g.take(ncell, c.n, cellcap)) {
+            g = BatchGroup();
+            c.cell0 = 0;
+            g.take(ncell, c.n, cellcap);
+        }
+        slots = std::max(slots, g.cells * cellcap);
         b->req_h[r] = c;
         off_h[r] = c.off;
     }
     off_h[nreq] = (int)total;
+    if ((size_t)slots > nl->ncell_alloc) {
+        DP_HIP(hipStreamSynchronize(st));
+        if ((s = alloc_grids(nl, grid_slots(slots, (long)nl->ncell_alloc))) != DP_OK) return s;
+    }
+    nl->cellcap = cellcap;
     DP_HIP(hipMemcpyAsync(b->req_d, b->req_h, sizeof(BatchCell) * nreq, hipMemcpyHostToDevice, st));
     DP_HIP(hipMemcpyAsync(off_d, off_h, sizeof(int) * (nreq + 1), hipMemcpyHostToDevice, st));
     DP_HIP(hipEventRecord(b->staged, st));
     nl->natoms = (int)total;
-    for (size_t g = 0; g < groups.size(); g++) {
-        const int r0 = groups[g].r0, r1 = g + 1 < groups.size() ? groups[g + 1].r0 : nreq;
-        launch_build_batch(nl, b->req_d + r0, r1 - r0, off_h[r0], off_h[r1] - off_h[r0], groups[g].nmax, groups[g].cells,
-                           g == 0, coords_d, b->ireq, st);
+    for (int r0 = 0, r1; r0 < nreq; r0 = r1) {
+        g = BatchGroup();
+        for (r1 = r0; r1 < nreq; r1++) {
+            const BatchCell &c = b->req_h[r1];
+            if (!g.take((long)c.nc[0] * c.nc[1] * c.nc[2], c.n, cellcap)) break;
+        }
+        launch_build_batch(nl, b->req_d + r0, r1 - r0, off_h[r0], off_h[r1] - off_h[r0], g.nmax, g.cells, r0 == 0, coords_d,
+                           b->ireq, st);
     }
     launch_reverse(nl, 0, (int)total, st, uniq);
     if ((s = step_check("batch_nlist", st)) != DP_OK) return s;

@@ -111,10 +111,11 @@ class Server:
 
     The HBM budget is split evenly over the slots: each slot's resident
     batch is created for the largest atom count whose device footprint
-    (neighbor list and scratch, dp_footprint_bytes) fits its share, so the
-    whole server never holds more than the budget.  Admission is then a
-    capacity check: a free slot takes waiting requests in arrival order while
-    their atoms fit."""
+    (neighbor list, cell grids and scratch, dp_footprint_bytes) fits its
+    share, so the whole server never holds more than the budget (mostly empty
+    boxes aside, whose cell grids can outgrow it as that function's comment
+    says).  Admission is then a capacity check: a free slot takes waiting
+    requests in arrival order while their atoms fit."""
 
     def __init__(self, model, precision=FP32, slots=3, hbm_budget=8 << 30, skin=2.0, max_requests=1024,
                  device="cuda"):
