@@ -559,11 +559,15 @@ dp_status dp_table_download(dp_model *m, double *coef_h, int *n_int)
     if (n_int) *n_int = n;
     if (coef_h) {
         DP_HIP(hipDeviceSynchronize());
-        std::vector<double> t((size_t)m->ntypes * n * kM * 6);
-        DP_HIP(hipMemcpy(t.data(), m->tab64, sizeof(double) * t.size(), hipMemcpyDeviceToHost));
-        for (size_t b = 0; b < t.size(); b += kM * 6)   // as [interval][column][6]
+        const size_t blk = kM * 6, nb = (size_t)m->ntypes * n;
+        DP_HIP(hipMemcpy(coef_h, m->tab64, sizeof(double) * nb * blk, hipMemcpyDeviceToHost));
+        double t[kM * 6];
+        for (size_t b = 0; b < nb; b++) {   // in place: each interval as [column][6]
+            double *o = coef_h + b * blk;
+            std::memcpy(t, o, sizeof(t));
             for (int c = 0; c < kM; c++)
-                for (int e = 0; e < 6; e++) coef_h[b + c * 6 + e] = t[b + coef_pos(0.0, e, c)];
+                for (int e = 0; e < 6; e++) o[c * 6 + e] = t[coef_pos(0.0, e, c)];
+        }
     }
     return DP_OK;
 }
