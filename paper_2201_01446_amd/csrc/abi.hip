@@ -104,7 +104,7 @@ void free_nlist_arrays(dp_nlist *nl)
 }
 
 // (Re)allocates the list for natoms atoms in box (NULL: open); no launch.
-dp_status prepare_nlist(const dp_model *m, int natoms, const double *box, double skin, dp_nlist **inout)
+dp_status prepare_nlist(const dp_model *m, int natoms, const double *box, double skin, dp_nlist **inout, hipStream_t st)
 {
     if (natoms <= 0) return fail(DP_ERR_ARG, "natoms must be positive");
     if (natoms >= (1 << 24)) return fail(DP_ERR_UNSUPPORTED, "at most 2^24 - 1 atoms");
@@ -220,7 +220,7 @@ dp_status prepare_nlist(const dp_model *m, int natoms, const double *box, double
     if (!nl->disp) DP_HIP(hipMalloc(&nl->disp, sizeof(unsigned long long)));
     nl->margin = 0.25 * skin;
     nl->natoms = natoms;
-    dp_status s = ensure_ws(nl, DP_FP64, m->cfg.sel);
+    dp_status s = ensure_ws(nl, DP_FP64, m->cfg.sel, st);
     if (s != DP_OK) return s;
     *inout = nl;
     return DP_OK;
@@ -578,7 +578,7 @@ dp_status dp_build_nlist(dp_model *m, int natoms, const double *coords_d, const 
     if (!m || !coords_d || !inout) return fail(DP_ERR_ARG, "NULL argument");
     hipStream_t st = (hipStream_t)stream;
     for (int attempt = 0; attempt < 4; attempt++) {
-        dp_status s = prepare_nlist(m, natoms, box_h, skin, inout);
+        dp_status s = prepare_nlist(m, natoms, box_h, skin, inout, st);
         if (s != DP_OK) return s;
         dp_nlist *nl = *inout;
         s = build_all(nl, coords_d, types_d, st);
@@ -615,7 +615,7 @@ static dp_status compute_common(dp_model *m, dp_nlist *nl, int natoms, const dou
         // the plain rungs keep their activations in a scratch of their own
         if (mode == DP_PLAIN || mode == DP_TAB_UNFUSED)
             return fail(DP_ERR_UNSUPPORTED, "dp_compute_noalloc runs the fused modes (0, 3, 4) only");
-    } else if ((s = ensure_ws(nl, precision, m->cfg.sel)) != DP_OK) {
+    } else if ((s = ensure_ws(nl, precision, m->cfg.sel, st)) != DP_OK) {
         return s;
     }
     ComputeArgs a;
@@ -732,7 +732,7 @@ static dp_status nve_steps(dp_model *m, dp_nlist **nlp, int natoms, double *x, d
     dp_nlist *nl = *nlp;
     if (fresh) {
         for (int attempt = 0;; attempt++) {   // the first build, checked as in dp_build_nlist
-            if ((s = prepare_nlist(m, natoms, box_h, skin, nlp)) != DP_OK) return s;
+            if ((s = prepare_nlist(m, natoms, box_h, skin, nlp, st)) != DP_OK) return s;
             nl = *nlp;
             if ((s = check_compute_args(m, nl, natoms, x, mode, precision)) != DP_OK) return s;
             if ((s = build_all(nl, x, types, st)) != DP_OK) return s;
@@ -787,7 +787,7 @@ static dp_status nve_steps(dp_model *m, dp_nlist **nlp, int natoms, double *x, d
                 if (attempt < 3 && grow_after_overflow(nl, f)) {
                     launch_fill_zero_int(nl->flags + kFlagCapOverflow, 1, st);
                     launch_fill_zero_int(nl->flags + kFlagCellOverflow, 1, st);
-                    if ((s = prepare_nlist(m, natoms, box, skin_l, nlp)) != DP_OK) return s;
+                    if ((s = prepare_nlist(m, natoms, box, skin_l, nlp, st)) != DP_OK) return s;
                     // a reallocation drops the forces of the step; they are
                     // evaluated again below at the same positions
                     F = nl->nve_F;
@@ -921,7 +921,8 @@ dp_status dp_batch_create(dp_model *m, int max_atoms, int max_requests, double s
     DP_HIP(hipEventCreateWithFlags(&b->staged, hipEventDisableTiming));
     dp_status s = alloc_grids(nl, batch_slots(max_atoms));
     if (s != DP_OK) return s;
-    if ((s = ensure_ws(nl, DP_FP64, m->cfg.sel)) != DP_OK) return s;
+    if ((s = ensure_ws(nl, DP_FP64, m->cfg.sel, nullptr)) != DP_OK) return s;
+    DP_HIP(hipStreamSynchronize(nullptr));   // the stream of the first batch is not known here
     *out = b;
     return DP_OK;
 }
@@ -985,7 +986,7 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
     }
     if (total > b->max_atoms) return fail(DP_ERR_CAPACITY, "batch exceeds max_atoms");
     // the scratch was sized for the model of dp_batch_create; another may keep more neighbors
-    dp_status s = ensure_ws(nl, precision, m->cfg.sel);
+    dp_status s = ensure_ws(nl, precision, m->cfg.sel, st);
     if (s != DP_OK) return s;
     cellcap = std::max(cellcap, nl->cellcap);
     // request table: the staging buffer is reused, so wait for the last upload

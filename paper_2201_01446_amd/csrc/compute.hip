@@ -317,7 +317,7 @@ size_t ws_bytes_for_atoms(int natoms, int precision, int sel, int ntypes)
     return ws_bytes_for((int)fit_rows(natoms, ntypes), precision, sel);
 }
 
-dp_status ensure_ws(dp_nlist *nl, int precision, int sel)
+dp_status ensure_ws(dp_nlist *nl, int precision, int sel, hipStream_t st)
 {
     int np = (int)fit_rows(nl->alloc_atoms, nl->ntypes);
     size_t need = ws_bytes_for(np, DP_FP64, sel);
@@ -330,11 +330,14 @@ dp_status ensure_ws(dp_nlist *nl, int precision, int sel)
     nl->ws_bytes = 0;
     nl->fwd_token = 0;   // a kept forward goes with it
     hipError_t e = hipMalloc(&nl->ws, need);
-    if (e != hipSuccess) return fail(DP_ERR_OOM, "workspace allocation failed");
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(DP_ERR_OOM, "workspace allocation failed");
+    }
     nl->ws_bytes = need;
     // rows past natoms are read by GEMM tiles: keep them finite (zero)
-    DP_HIP(hipMemset(nl->ws, 0, need));
-    DP_HIP(hipStreamSynchronize(nullptr));   // a caller's stream need not wait for the null stream
+    // (on the caller's stream, which need not wait for the null stream)
+    DP_HIP(hipMemsetAsync(nl->ws, 0, need, st));
     return DP_OK;
 }
 

@@ -430,7 +430,7 @@ dp_status plain_forward(const dp_model *m, dp_nlist *nl, int n, const double *x,
 template <typename real>
 dp_status plain_backward(const dp_model *m, dp_nlist *nl, int n, const void *dT, double *force, double *w_atom,
                          hipStream_t st, bool tabulated);
-dp_status ensure_ws(dp_nlist *nl, int precision, int sel);
+dp_status ensure_ws(dp_nlist *nl, int precision, int sel, hipStream_t st);
 // GEMM rows a list of alloc_atoms atoms of ntypes types may need
 inline long fit_rows(long atoms, int ntypes) { return round_up(atoms, kRowPad) + (long)kRowPad * (ntypes - 1); }
 // Copies the types into the list, checks them, counts them per type and

@@ -333,7 +333,7 @@ static EmbW<real> emb_weights(const dp_model *m)
 }
 
 template <typename real>
-dp_status plain_ensure(dp_nlist *nl, long rows)
+dp_status plain_ensure(dp_nlist *nl, long rows, hipStream_t st)
 {
     size_t need = plain_bytes<real>(round_up(rows, kRowPad));
     if (nl->ws_plain_bytes >= need) return DP_OK;
@@ -345,7 +345,7 @@ dp_status plain_ensure(dp_nlist *nl, long rows)
         return fail(DP_ERR_OOM, "plain-path workspace allocation failed");
     }
     nl->ws_plain_bytes = need;
-    DP_HIP(hipMemset(nl->ws_plain, 0, need));
+    DP_HIP(hipMemsetAsync(nl->ws_plain, 0, need, st));
     return DP_OK;
 }
 
@@ -357,7 +357,7 @@ dp_status plain_forward(const dp_model *m, dp_nlist *nl, int n, const double *x,
 {
     int sel = m->cfg.sel;
     long rows = (long)n * sel, rows_p = round_up(rows, kRowPad);
-    dp_status s = plain_ensure<real>(nl, rows);
+    dp_status s = plain_ensure<real>(nl, rows, st);
     if (s != DP_OK) return s;
     PlainWS<real> w = plain_carve<real>(nl->ws_plain, rows_p);
     EmbW<real> ew = emb_weights<real>(m);
