@@ -133,7 +133,7 @@ struct FitNet {
             DP_TIMED("fit_fwd", st, launch_mix_fwd(fr, nt, (const float *)w.T, fw, fb, tab, (float *)w.dDr, w.e_atom, w.D, st));
         } else {
             DP_TIMED("fit_in", st, launch_fit_in<TR>(fr, nt, (const TR *)w.T, fw.in, (TR *)w.dDr, st));
-            DP_TIMED("fit_mid", st, launch_fit_mid<TR>(fr, nt, nt, fit_in_parts<TR>(fr), (const TR *)w.dDr, fw.mid, fb, tab, w.e_atom, (TR *)w.D, st));
+            DP_TIMED("fit_mid", st, launch_fit_mid<TR>(fr, nt, fit_in_parts<TR>(fr), (const TR *)w.dDr, fw.mid, fb, tab, w.e_atom, (TR *)w.D, st));
         }
     }
     void backward(hipStream_t st) const

@@ -244,13 +244,11 @@ __device__ inline int xcd_item(int b, int grid) { return (b % kXcd) * (grid / kX
 // ------------------------------------------------------------- launchers
 // (defined in the kernel translation units; all enqueue on `st`)
 void launch_fill_zero(double *p, long n, hipStream_t st);
-void launch_fill_zero_bytes(void *p, size_t nbytes, hipStream_t st);
 void launch_fill_zero_int(int *p, long n, hipStream_t st);
 // The largest |x_i - x0_i| into nl->disp (no-op for lists without x0); sets
 // kFlagSkin when twice it reaches `lim` (the list's reach beyond the
 // evaluating model's cut-off: a pair within that cut-off may then lack its
 // candidate) and kFlagBadCoord on a non-finite position.
-dp_status pack_weights(FitWeights &d, FitWeights &w32, FitWeights &wbf, int ntypes, int f1);
 void launch_displacement(const dp_nlist *nl, int n, const double *x, double lim, hipStream_t st);
 dp_status launch_tabulate(dp_model *m, hipStream_t st);
 constexpr int kTanhN = 1024;   // tanh table intervals of width 1/128 on [0, 8)
@@ -343,6 +341,8 @@ struct TailLaunch {
 template <typename T>
 void launch_fit_tail(int rows, const T *y1, const FitWeights &fw, const T *fb, const TailLaunch &tl, double *e_atom,
                      T *dz1, T *t2s, T *dy2s, hipStream_t st);
+// Every layout of the weights (pack.hip) from d, which holds the FP64 matrices.
+dp_status pack_weights(FitWeights &d, FitWeights &w32, FitWeights &wbf, int ntypes, int f1);
 // The fitting net of the compressed step (fitnet.hip, fitsplit.hip): its rows
 // of 16 atoms (several types: grouped by type, ratom row -> atom, -1: padding;
 // one type: the atoms below nlive) and the size of one type's weights (in
@@ -361,9 +361,9 @@ template <typename real>
 int fit_in_parts(const FitRows &fr);
 template <typename real>
 void launch_fit_in(const FitRows &fr, int nt, const real *T, const void *W, real *z, hipStream_t st);
-// FP64 and FP32: E_i and dz1 [row tile][nt][256] from z [parts][row tile][zt][256]
+// FP64 and FP32: E_i and dz1 [row tile][nt][256] from z [parts][row tile][nt][256]
 template <typename real>
-void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z, const void *W, const real *fb,
+void launch_fit_mid(const FitRows &fr, int nt, int parts, const real *z, const void *W, const real *fb,
                     const real *tanh_tab, double *e_atom, real *dz1, hipStream_t st);
 // dT [atom][column][4] without, and part [fit_out_parts][atom][16][4] with, the sums over all columns
 int fit_out_parts(const FitRows &fr);

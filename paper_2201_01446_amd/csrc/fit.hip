@@ -494,12 +494,6 @@ __global__ void k_fill_zero(double *p, long n)
     if (i < n) p[i] = 0.0;
 }
 
-__global__ void k_fill_zero_u32(unsigned *p, long n)
-{
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
-}
-
 }  // namespace
 
 // ----------------------------------------------------------- launchers
@@ -596,12 +590,6 @@ template void launch_op_to_double<__bf16>(int, int, const __bf16 *, const int *,
 void launch_fill_zero(double *p, long n, hipStream_t st)
 {
     if (n > 0) hipLaunchKernelGGL(k_fill_zero, dim3(div_up(n, 256)), dim3(256), 0, st, p, n);
-}
-
-void launch_fill_zero_bytes(void *p, size_t nbytes, hipStream_t st)
-{
-    long n = (long)(nbytes / 4);
-    if (n > 0) hipLaunchKernelGGL(k_fill_zero_u32, dim3(div_up(n, 256)), dim3(256), 0, st, (unsigned *)p, n);
 }
 
 }  // namespace dp

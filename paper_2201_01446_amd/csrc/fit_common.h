@@ -1,6 +1,7 @@
 // fit_common.h -- MFMA fragments, precision conversions and the epilogue
-// tanh shared by the fitting-net GEMM (gemm.hip) and the fused fitting tail
-// (fit.hip).
+// tanh shared by the fitting-net GEMM (gemm.hip), the fused fitting tail
+// (fit.hip) and the compressed step's net (fitnet.hip, fitsplit.hip), and the
+// rows, the scheduling and the lane sums of the last two.
 #pragma once
 
 #include "dp_internal.h"
@@ -97,6 +98,51 @@ __device__ inline double tanh_e(double x, const double *tab)
 // The table an epilogue of result type TR takes (NULL: native tanh).
 __device__ inline const float *tanh_table_for(const Epi &e, float) { return e.tanh_tab; }
 __device__ inline const double *tanh_table_for(const Epi &e, double) { return e.tanh_tab64; }
+
+
+// ------------------------------------ the compressed step's net (fitnet.hip, fitsplit.hip)
+// Rows of the net: row -> atom (-1: padding), and the type group of a tile.
+__device__ inline int row_atom(const FitRows &fr, int row)
+{
+    if (fr.ratom) return fr.ratom[row];
+    return row < fr.nlive ? row : -1;
+}
+__device__ inline int row_type(const FitRows &fr, int row)
+{
+    int ty = 0;
+    for (int g = 1; g < fr.ntr; g++) ty += row >= fr.trow[g] ? 1 : 0;
+    return ty;
+}
+
+// The wave's number in its block, in a scalar register: what follows from it
+// (the weights' addresses) is then computed by the scalar unit.  FP64 MFMA and
+// the vector ALU share their pipe, so vector address arithmetic costs MFMA time.
+__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// Keeps the loads issued before it where they are: the compiler otherwise
+// moves a ring's loads down to their use, a whole turn of the ring later.
+__device__ inline void keep_order() { __builtin_amdgcn_sched_barrier(0); }
+
+// UP false: even rows of 16 lanes get a + a of the odd row beside, odd rows
+// b + b of the even row; UP true: the same between the halves of 32 lanes.
+template <bool UP>
+__device__ inline float swap_add(float a, float b)
+{
+    const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
+    auto s = UP ? __builtin_amdgcn_permlane32_swap(x, y, false, false) : __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
+}
+template <bool UP>
+__device__ inline double swap_add(double a, double b)
+{
+    const int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
+    auto s = UP ? __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false) : __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+    auto t = UP ? __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false) : __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    return __builtin_bit_cast(double, int2{(int)s[0], (int)t[0]}) + __builtin_bit_cast(double, int2{(int)s[1], (int)t[1]});
+}
+
+// Rows of 16 that a launch covers.
+inline int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
 
 }  // namespace
 

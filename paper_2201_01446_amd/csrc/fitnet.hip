@@ -48,28 +48,6 @@ namespace dp {
 
 namespace {
 
-// Rows of the net: row -> atom (-1: padding), and the type group of a tile.
-__device__ inline int row_atom(const FitRows &fr, int row)
-{
-    if (fr.ratom) return fr.ratom[row];
-    return row < fr.nlive ? row : -1;
-}
-__device__ inline int row_type(const FitRows &fr, int row)
-{
-    int ty = 0;
-    for (int g = 1; g < fr.ntr; g++) ty += row >= fr.trow[g] ? 1 : 0;
-    return ty;
-}
-
-// The wave's number in its block, in a scalar register: what follows from it
-// (the weights' addresses) is then computed by the scalar unit.  FP64 MFMA and
-// the vector ALU share their pipe, so vector address arithmetic costs MFMA time.
-__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-
-// Keeps the loads issued before it where they are: the compiler otherwise
-// moves a ring's loads down to their use, a whole turn of the ring later.
-__device__ inline void keep_order() { __builtin_amdgcn_sched_barrier(0); }
-
 // Four values of a lane (one tile, or one operand of four K steps), the MFMA
 // on them, and their place in memory: a piece of 256 reals per tile, read 16
 // bytes a lane at a time.
@@ -334,7 +312,7 @@ struct MidRing {
 };
 
 template <typename real, int RT, int PD, int NTC, bool TAB>
-__global__ void __launch_bounds__(1024, sizeof(real) == 4 ? 8 : 4) k_fit_mid(FitRows fr, int nrt, int nt, int zt, int parts,
+__global__ void __launch_bounds__(1024, sizeof(real) == 4 ? 8 : 4) k_fit_mid(FitRows fr, int nrt, int nt, int parts,
                                                   const real *__restrict__ z, const real *__restrict__ W,
                                                   const real *__restrict__ fb, const real *__restrict__ tanh_tab,
                                                   double *__restrict__ e_atom, real *__restrict__ dz1)
@@ -362,9 +340,9 @@ __global__ void __launch_bounds__(1024, sizeof(real) == 4 ? 8 : 4) k_fit_mid(Fit
     v4 y1[RT], t2[RT], dy2[RT], acc[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; rt++) {
-        const real *p = z + ((long)min(tile0 + rt, nrt - 1) * zt + wave) * kPiece;
+        const real *p = z + ((long)min(tile0 + rt, nrt - 1) * nt + wave) * kPiece;
         v4 v = N::get(p, lane);
-        for (int s = 1; s < parts; s++) v += N::get(p + (long)s * nrt * zt * kPiece, lane);
+        for (int s = 1; s < parts; s++) v += N::get(p + (long)s * nrt * nt * kPiece, lane);
 #pragma unroll
         for (int i = 0; i < 4; i++) y1[rt][i] = tanh_e(v[i] + c1[N::col(i, q)], tab);
     }
@@ -431,24 +409,6 @@ __global__ void __launch_bounds__(1024, sizeof(real) == 4 ? 8 : 4) k_fit_mid(Fit
 //   dT2[k][a] += dD[a][b] T[k][b]          (16 sums in the lane, over all b)
 // and dE/dT[k][c] = dT1[k][c] + [c < M<] dT2[k][c].  A wave takes consecutive
 // b, two at a time; the block's rows of dz1 sit in LDS.
-template <bool UP>
-__device__ inline float swap_add(float a, float b)
-{
-    // UP false: even rows of 16 lanes get a + a of the odd row beside, odd rows
-    // b + b of the even row; UP true: the same between the halves of 32 lanes
-    const unsigned x = __builtin_bit_cast(unsigned, a), y = __builtin_bit_cast(unsigned, b);
-    auto s = UP ? __builtin_amdgcn_permlane32_swap(x, y, false, false) : __builtin_amdgcn_permlane16_swap(x, y, false, false);
-    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
-}
-template <bool UP>
-__device__ inline double swap_add(double a, double b)
-{
-    const int2 x = __builtin_bit_cast(int2, a), y = __builtin_bit_cast(int2, b);
-    auto s = UP ? __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false) : __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
-    auto t = UP ? __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false) : __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
-    return __builtin_bit_cast(double, int2{(int)s[0], (int)t[0]}) + __builtin_bit_cast(double, int2{(int)s[1], (int)t[1]});
-}
-
 constexpr int kOutB0 = 4;    // b of the innermost sums of dT2
 constexpr int kOutB1 = 16;   // b of the middle ones
 
@@ -578,9 +538,6 @@ __global__ void __launch_bounds__(64 * out_waves(LEVEL), 2) k_fit_out(FitRows fr
     }
 }
 
-// Rows of 16 that a launch covers.
-int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
-
 // Row tiles from which on the first layer's K stays whole (FP64), and up to
 // which it is left to single waves.
 constexpr int kInWholeTiles = 1250, kInFewTiles = 48;
@@ -616,13 +573,13 @@ template void launch_fit_in<double>(const FitRows &, int, const double *, const 
 template void launch_fit_in<float>(const FitRows &, int, const float *, const void *, float *, hipStream_t);
 
 template <typename real>
-void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z, const void *W, const real *fb,
+void launch_fit_mid(const FitRows &fr, int nt, int parts, const real *z, const void *W, const real *fb,
                     const real *tanh_tab, double *e_atom, real *dz1, hipStream_t st)
 {
     const int nrt = row_tiles(fr);
     auto go = [&](auto kern, int RT) {
         hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT)), dim3(64 * nt), (size_t)2 * nt * RT * kPiece * sizeof(real), st, fr,
-                           nrt, nt, zt, parts, z, (const real *)W, fb, tanh_tab, e_atom, dz1);
+                           nrt, nt, parts, z, (const real *)W, fb, tanh_tab, e_atom, dz1);
     };
     // two row tiles to a block once there are two blocks for every CU; widths
     // of 15 tiles (225 to 240, the paper's 240 among them) have loops of their own
@@ -642,9 +599,9 @@ void launch_fit_mid(const FitRows &fr, int nt, int zt, int parts, const real *z,
         else go(k_fit_mid<real, 2, PD2, 0, true>, 2);
     }
 }
-template void launch_fit_mid<double>(const FitRows &, int, int, int, const double *, const void *, const double *,
+template void launch_fit_mid<double>(const FitRows &, int, int, const double *, const void *, const double *,
                                      const double *, double *, double *, hipStream_t);
-template void launch_fit_mid<float>(const FitRows &, int, int, int, const float *, const void *, const float *,
+template void launch_fit_mid<float>(const FitRows &, int, int, const float *, const void *, const float *,
                                     const float *, double *, float *, hipStream_t);
 
 int fit_out_parts(const FitRows &fr)

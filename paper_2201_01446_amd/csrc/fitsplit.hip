@@ -32,22 +32,6 @@ namespace dp {
 
 namespace {
 
-__device__ inline int row_atom(const FitRows &fr, int row)
-{
-    if (fr.ratom) return fr.ratom[row];
-    return row < fr.nlive ? row : -1;
-}
-__device__ inline int row_type(const FitRows &fr, int row)
-{
-    int ty = 0;
-    for (int g = 1; g < fr.ntr; g++) ty += row >= fr.trow[g] ? 1 : 0;
-    return ty;
-}
-__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
-// Keeps the loads issued before it where they are (the compiler otherwise
-// moves the loads of a ring down to their use).
-__device__ inline void keep_order() { __builtin_amdgcn_sched_barrier(0); }
-
 // ---------------------------------------------------------------- mixed
 // K runs in its natural order, K step g: element j of lane group q is k = 32 g
 // + 8 q + j (k = a M + b for D).  Four values of a result tile, columns 16 t +
@@ -352,17 +336,6 @@ __global__ void __launch_bounds__(512, 4) k_mix_mid(FitRows fr, int nrt, int ks_
 // wave takes 16 columns b, two at a time, for RT row tiles whose dz1 sits in
 // LDS.  WPB waves to a block; 8: the block covers all 128 columns and adds the
 // waves' dT2 in order; fewer: each wave writes its own to part[b / 16].
-__device__ inline float swap_add16(float a, float b)
-{
-    auto s = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
-}
-__device__ inline float swap_add32(float a, float b)
-{
-    auto s = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-    return __builtin_bit_cast(float, (unsigned)s[0]) + __builtin_bit_cast(float, (unsigned)s[1]);
-}
-
 constexpr int kMixOutB = 16;   // columns of a wave
 
 template <int RT, int WPB, int KS>
@@ -466,7 +439,7 @@ __global__ void __launch_bounds__(64 * WPB) k_mix_out(FitRows fr, int nrt, int k
 #pragma unroll
                     for (int k = 0; k < 4; k++) acc2[t][i][k] = fmaf(cc[i], tb[k], acc2[t][i][k]);
                 // lane group q ends with k = q
-                const float v = swap_add32(swap_add16(p[0], p[1]), swap_add16(p[2], p[3]));
+                const float v = swap_add<true>(swap_add<false>(p[0], p[1]), swap_add<false>(p[2], p[3]));
                 if (atom[t] >= 0) dT[((long)atom[t] * kM + b + u) * 4 + q] = v;
             }
         }
@@ -497,8 +470,6 @@ __global__ void __launch_bounds__(64 * WPB) k_mix_out(FitRows fr, int nrt, int k
         }
     }
 }
-
-int row_tiles(const FitRows &fr) { return fr.ntr > 1 ? fr.trow[fr.ntr] / 16 : div_up(fr.nlive, 16); }
 
 // Rows up to which the input gradient's groups of 16 columns go to blocks of
 // their own.

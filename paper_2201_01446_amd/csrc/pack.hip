@@ -22,15 +22,13 @@ __device__ inline unsigned short bf16_of(float f)
 }
 __device__ inline float bf16_value(unsigned short h) { return __builtin_bit_cast(float, (unsigned)h << 16); }
 
-// BF16 parts of v (as FP32), pitch apart: the rounded value, then what is left of it.
-__device__ inline void put_parts(unsigned short *p, long pitch, int np, double v)
+// Two BF16 parts of v (as FP32), pitch apart: the rounded value and what is left of it.
+__device__ inline void put_parts(unsigned short *p, long pitch, double v)
 {
-    float r = (float)v;
-    for (int n = 0; n < np; n++) {
-        const unsigned short h = bf16_of(r);
-        p[n * pitch] = h;
-        r -= bf16_value(h);
-    }
+    const float f = (float)v;
+    const unsigned short h = bf16_of(f);
+    p[0] = h;
+    p[pitch] = bf16_of(f - bf16_value(h));
 }
 
 __device__ inline long thread_of() { return blockIdx.x * (long)blockDim.x + threadIdx.x; }
@@ -60,7 +58,7 @@ __global__ void k_split_rows(long n, int K, const double *__restrict__ a, unsign
     const long r = i / K;
     const int c = (int)(i % K);
     unsigned short *p = b + r * 3 * K + c;
-    put_parts(p, K, 2, a[i]);
+    put_parts(p, K, a[i]);
     p[2 * K] = p[0];
 }
 
@@ -130,7 +128,7 @@ __global__ void k_pack_mix_in(long n, int nt, const double *__restrict__ V1, uns
     const long p = id / kBf, part = (long)(kDdim / 32) * nt * kBf;
     const int ot = (int)(p % nt), g = (int)(p / nt % (kDdim / 32));
     const long t = p / nt / (kDdim / 32);
-    put_parts(out + t * 2 * part + ((long)g * nt + ot) * kBf + e, part, 2,
+    put_parts(out + t * 2 * part + ((long)g * nt + ot) * kBf + e, part,
               V1[t * kDdim * kFitPad + (long)(32 * g + 8 * (l / 16) + j) * kFitPad + 16 * ot + l % 16]);
 }
 __global__ void k_pack_mix_mid(long n, int ks, MidMats M, unsigned short *__restrict__ out)
@@ -141,7 +139,7 @@ __global__ void k_pack_mix_mid(long n, int ks, MidMats M, unsigned short *__rest
     const long p = id / kBf, part = (long)ks * nt * kBf;
     const int ot = (int)(p % nt), g = (int)(p / nt % ks), m = (int)(p / nt / ks % 4);
     const long t = p / nt / ks / 4;
-    put_parts(out + (t * 4 + m) * 2 * part + ((long)g * nt + ot) * kBf + e, part, 2,
+    put_parts(out + (t * 4 + m) * 2 * part + ((long)g * nt + ot) * kBf + e, part,
               M.V[m][t * kFitPad * kFitPad + (long)(16 * ot + l % 16) * kFitPad + 32 * g + 8 * (l / 16) + j]);
 }
 __global__ void k_pack_mix_out(long n, int ks, const double *__restrict__ V1, unsigned short *__restrict__ out)
@@ -152,7 +150,7 @@ __global__ void k_pack_mix_out(long n, int ks, const double *__restrict__ V1, un
     const long p = id / kBf, part = (long)ks * kBf;
     const int g = (int)(p % ks), b = (int)(p / ks % kM);
     const long t = p / ks / kM;
-    put_parts(out + (t * kM + b) * 2 * part + (long)g * kBf + e, part, 2,
+    put_parts(out + (t * kM + b) * 2 * part + (long)g * kBf + e, part,
               V1[t * kDdim * kFitPad + (long)(l % 16 * kM + b) * kFitPad + 32 * g + 8 * (l / 16) + j]);
 }
 
