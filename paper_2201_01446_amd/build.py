@@ -24,10 +24,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-I", os.path.join(ROOT, "include"), "-Wall", "-Wno-unused-function"]
 
 
-# per translation unit: the GEMM keeps MFMA results in VGPRs (with
-# accumulation registers the compiler copied the FP64 accumulators out and
-# back on every K stage); the other MFMA kernel, the fused fitting tail,
-# gets VGPR results without it
+# per translation unit: the GEMM and the compressed step's fitting net keep MFMA
+# results in VGPRs (with accumulation registers the compiler copied the GEMM's FP64
+# accumulators out and back on every K stage; the net's results are the next
+# product's operands); the fused fitting tail gets VGPR results without it
 FILE_FLAGS = {"gemm.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "fitnet.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "fitsplit.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 

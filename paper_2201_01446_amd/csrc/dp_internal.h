@@ -119,7 +119,8 @@ struct dp_nlist {
     // exact early end of the candidate scan: the positions at build, per atom
     // and type the candidates whose build distance is <= rcut + margin (a
     // prefix of the sorted run), and the largest displacement since the build
-    // (FP64 bits, set before each evaluation); none of these in batch lists
+    // (FP64 bits, set before each evaluation).  Batch lists are built and
+    // evaluated at the same positions: no x0, disp stays zero
     double *x0 = nullptr;                 // [natoms * 3]
     int *inner = nullptr;                 // [natoms * kMaxTypes]
     unsigned long long *disp = nullptr;   // [1]

@@ -234,7 +234,7 @@ __device__ __forceinline__ unsigned long long round_moments(const NbrLDS<real> &
     return reps;
 }
 
-// At 108,000 atoms 570 us (FP32) and 960 (FP64), 670 and 1,110 before the
+// At 108,000 atoms 570 us (FP32) and 1,000 (FP64), 670 and 1,110 before the
 // lane reads, the blocks of one wave and the coalesced table: the scan with
 // the stores of records and T takes 40-45 %, the contraction 40 %; bound by
 // the instructions of the wave (FP32) and by latency at the 3 waves a SIMD that
@@ -758,10 +758,12 @@ __global__ void __launch_bounds__(64 * kWide) k_emb_bwd_wide(int natoms, EnvArgs
 }  // namespace
 
 // ---------------------------------------------------------- launchers
-// Up to this many atoms four waves take one: a wave to each SIMD of the chip.
-// Past it the redundant parts (segments, barriers) cost more than the idle SIMDs
-// did: 1,371 atoms 32 and 27 us (forward, backward; FP32) against 28 and 25 by
-// one wave, 1,536 water atoms 58 and 52 against 33 and 33 (FP64).
+// Up to this many atoms four waves take one: with a wave an atom that many would
+// have one wave to each SIMD of the chip.  Past it the redundant parts (segments,
+// barriers) cost more than the idle SIMDs did.  Forward and backward together,
+// microseconds, four waves | one: FP32 500 atoms 34 | 45, 800 45 | 45, 1,024 44 | 44,
+// 1,371 59 | 49; FP64 500 38 | 49, 800 61 | 52, 1,024 62 | 53, 1,371 81 | 61.  FP64
+// crosses between 500 and 800; one line, FP32's, serves both.
 constexpr int kWideAtoms = 1024;
 static_assert(wide_lds_bytes<double>(512, false) <= 65536 && wide_lds_bytes<double>(512, true) <= 65536,
               "fits a block's LDS at the largest sel");

@@ -538,11 +538,36 @@ __global__ void __launch_bounds__(64 * out_waves(LEVEL), 2) k_fit_out(FitRows fr
     }
 }
 
-// Row tiles from which on the first layer's K stays whole (FP64), and up to
-// which it is left to single waves.
-constexpr int kInWholeTiles = 1250, kInFewTiles = 48;
-// Row tiles up to which the input gradient's sums over all columns are left
-// in 32 parts (a wave has 4 columns, then 8), and in 8 parts.
+// Where the launches change, in row tiles (16 atoms each; width 240, copper;
+// microseconds of the kernel on either side, "fewer rows | more rows").  Blocks of
+// one tile fill the 256 CUs at 256 of them, so times go in steps, and the better
+// side changes back and forth about each line; one set of lines serves FP64
+// and FP32.
+//
+// First layer.  Up to kInFewTiles single waves, four times as many in FP64 (four
+// segments of K) as in FP32 (one chain), so that the two cross at different
+// places: FP64 at 16 tiles 16 | 23, at 20 26 | 24, at 48 37 | 24; FP32 at 48 25 | 47,
+// at 125 41 | 48, at 144 60 | 48.  The line lies between.
+// Below kInOneTiles a block takes one tile, then two, which share its weights:
+// FP64 at 256 82 | 76, at 282 100 | 108, at 512 159 | 146, at 844 277 | 251; FP32 at 250
+// 49 | 82, at 512 87 | 84, at 625 125 | 154, at 844 164 | 155.
+// From kInWholeTiles on four tiles, in FP64 with all of K (the inner layers then read
+// one part instead of four), both kernels together: FP64 at 512 229 | 329, at 1,024 443 |
+// 401, at 1,250 579 | 710, at 2,000 886 | 789; FP32 at 1,024 227 | 214, at 1,250 328 | 376, at
+// 2,000 436 | 414.
+constexpr int kInFewTiles = 48, kInOneTiles = 512, kInWholeTiles = 1250;
+// Inner layers: one tile to a block up to here, then two: FP64 at 250 43 | 72, at 375
+// 78 | 73, at 512 84 | 78, at 625 120 | 145, at 844 157 | 148; FP32 at 250 23 | 38, at 512 39 | 40,
+// at 625 56 | 68, at 844 72 | 69.
+constexpr int kMidOneTiles = 512;
+// Input gradient: the sums over all columns are left in 32 parts up to
+// kOut32Tiles (a wave has 4 columns up to kOut4Tiles, then 8), in 8 up to
+// kOut8Tiles, then added by the block; more parts are more waves, and more to read
+// for the backward embedding, whose time is in the last two.  4 | 8 columns: FP64 at 32
+// tiles 18 | 25, at 64 29 | 27, at 125 50 | 44; FP32 at 32 12 | 16, at 64 19 | 19, at 125 29 |
+// 27.  32 | 8 parts: FP64 at 125 78 | 72, at 183 105 | 109, at 256 133 | 120, at 500 257 | 222; FP32
+// at 183 64 | 66, at 256 79 | 70, at 500 139 | 126.  8 | 1: FP64 at 625 276 | 299, at 1,024 464 | 437,
+// at 1,875 847 | 818; FP32 at 625 155 | 162, at 1,024 239 | 225, at 1,875 443 | 422.
 constexpr int kOut4Tiles = 64, kOut32Tiles = 256, kOut8Tiles = 1024;
 
 }  // namespace
@@ -565,7 +590,7 @@ void launch_fit_in(const FitRows &fr, int nt, const real *T, const void *W, real
     if (nrt <= kInFewTiles)
         hipLaunchKernelGGL(k_fit_in_few<real>, dim3(xcd_grid(div_up(nrt, 4) * nt * segs)), dim3(256), 0, st, fr, nrt, nt, T,
                            (const real *)W, z);
-    else if (nrt < 512) go(k_fit_in<real, 1, !f64>, 1, segs);
+    else if (nrt < kInOneTiles) go(k_fit_in<real, 1, !f64>, 1, segs);
     else if (nrt < kInWholeTiles) go(k_fit_in<real, 2, !f64>, 2, segs);
     else go(k_fit_in<real, 4, true>, 4, 1);
 }
@@ -581,9 +606,8 @@ void launch_fit_mid(const FitRows &fr, int nt, int parts, const real *z, const v
         hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT)), dim3(64 * nt), (size_t)2 * nt * RT * kPiece * sizeof(real), st, fr,
                            nrt, nt, parts, z, (const real *)W, fb, tanh_tab, e_atom, dz1);
     };
-    // two row tiles to a block once there are two blocks for every CU; widths
-    // of 15 tiles (225 to 240, the paper's 240 among them) have loops of their own
-    const int RT = nrt <= 512 ? 1 : 2;
+    // widths of 15 tiles (225 to 240, the paper's 240 among them) have loops of their own
+    const int RT = nrt <= kMidOneTiles ? 1 : 2;
     // FP32: the registers of eight waves a SIMD, so that two blocks of 15 waves
     // share a CU (503 -> 475 us at 108,000 atoms); one tile of weights ahead is
     // what fits

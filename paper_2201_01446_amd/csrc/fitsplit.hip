@@ -471,9 +471,20 @@ __global__ void __launch_bounds__(64 * WPB) k_mix_out(FitRows fr, int nrt, int k
     }
 }
 
-// Rows up to which the input gradient's groups of 16 columns go to blocks of
-// their own.
-constexpr int kSplitRows = 8192;
+// Where the launches change, in row tiles (16 atoms each; width 240, copper;
+// microseconds on either side, "fewer rows | more rows"; the times go in steps,
+// as the blocks fill the 256 CUs).
+// First layer: one tile to a block up to kInOneTiles (with the inner layers at 183
+// tiles 56 | 67, at 256 58 | 68, at 375 81 | 73, at 512 88 | 76), two up to kInTwoTiles, then
+// four (at 512 76 | 91, at 750 103 | 99, at 1,024 121 | 114, at 1,500 179 | 198, at 2,500 281 | 295:
+// four lose there what they gain where they fill the chip).
+// Inner layers: one up to kMidOneTiles, then two (at 256 58 | 62, at 375 77 | 73, at
+// 512 80 | 76).
+// Input gradient: up to kSplitTiles groups of 16 columns in blocks of their own, of
+// one tile up to kOutOneTiles, then two (at 64 24 | 29, at 125 26 | 30, at 183 32 | 31), then whole rows of
+// four tiles (with the backward embedding, which reads the parts: at 375 89 | 101, at
+// 512 103 | 111, at 750 139 | 126, at 1,875 362 | 292).
+constexpr int kInOneTiles = 256, kInTwoTiles = 1024, kMidOneTiles = 256, kOutOneTiles = 64, kSplitTiles = 512;
 
 }  // namespace
 
@@ -486,8 +497,8 @@ void launch_mix_fwd(const FitRows &fr, int nt, const float *T, const FitWeights 
         const size_t lds = (size_t)2 * 16 * 1024 + RT * kMlt * 256;
         hipLaunchKernelGGL(kern, dim3(div_up(nrt, RT)), dim3(512), lds, st, fr, nrt, ks, T, (const bf8v *)fw.in, z);
     };
-    if (nrt <= 256) in(k_mix_in<1>, 1);
-    else if (nrt <= 1024) in(k_mix_in<2>, 2);
+    if (nrt <= kInOneTiles) in(k_mix_in<1>, 1);
+    else if (nrt <= kInTwoTiles) in(k_mix_in<2>, 2);
     else in(k_mix_in<4>, 4);
     auto mid = [&](auto kern, int RT) {
         const size_t lds = (size_t)2 * ks * RT * 2 * 1024;
@@ -497,7 +508,7 @@ void launch_mix_fwd(const FitRows &fr, int nt, const float *T, const FitWeights 
     // (widths of 225 to 256 columns, 240 among them, with the steps unrolled whole)
     auto mids = [&](auto KS) {
         constexpr int k = decltype(KS)::value;
-        if (nrt <= 256) {
+        if (nrt <= kMidOneTiles) {
             if (tanh_tab) mid(k_mix_mid<1, k, true>, 1);
             else mid(k_mix_mid<1, k, false>, 1);
         } else {
@@ -509,7 +520,7 @@ void launch_mix_fwd(const FitRows &fr, int nt, const float *T, const FitWeights 
     else mids(std::integral_constant<int, 0>{});
 }
 
-int mix_out_parts(const FitRows &fr) { return row_tiles(fr) * 16 <= kSplitRows ? kM / kMixOutB : 1; }
+int mix_out_parts(const FitRows &fr) { return row_tiles(fr) <= kSplitTiles ? kM / kMixOutB : 1; }
 
 void launch_mix_out(const FitRows &fr, int nt, long natoms, const void *dz1, const float *T, const void *W, float *dT,
                     float *part, hipStream_t st)
@@ -523,7 +534,7 @@ void launch_mix_out(const FitRows &fr, int nt, long natoms, const void *dz1, con
     auto out = [&](auto KS) {
         constexpr int k = decltype(KS)::value;
         if (mix_out_parts(fr) == 1) go(k_mix_out<4, 8, k>, 4, 8);
-        else if (nrt <= 64) go(k_mix_out<1, 2, k>, 1, 2);
+        else if (nrt <= kOutOneTiles) go(k_mix_out<1, 2, k>, 1, 2);
         else go(k_mix_out<2, 4, k>, 2, 4);
     };
     if (ks == 8) out(std::integral_constant<int, 8>{});
