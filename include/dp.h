@@ -342,7 +342,7 @@ dp_status dp_batch_destroy(dp_batch *batch);
 /* energy_d[nreq], force_d[total*3], virial_d[nreq*9], atom_energy_d[total]
  * (device, FP64, NULL skips).  Enqueued on `stream`; one batch object must
  * not be used by two streams at once.  `model` may be another than the one
- * the batch was created for: its rcut must lie below that one's rcut + skin
+ * the batch was created for: its rcut must not exceed that one's rcut + skin
  * (DP_ERR_ARG), and one that keeps more neighbors (sel) grows the batch's
  * scratch at its first call.  Returns DP_ERR_CAPACITY when the requests
  * exceed max_atoms or max_requests. */

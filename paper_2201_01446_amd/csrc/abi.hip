@@ -955,7 +955,8 @@ dp_status dp_batch_compute(dp_model *m, dp_batch *b, int nreq, const dp_request 
     hipStream_t st = (hipStream_t)stream;
     dp_nlist *nl = b->nl;
     double rcs = nl->rc_build;
-    if (m->cfg.rcut >= rcs) return fail(DP_ERR_ARG, "the model's rcut reaches past the batch's rcut + skin");
+    // (equal will do: no atom moves between the list's build and its evaluation)
+    if (m->cfg.rcut > rcs) return fail(DP_ERR_ARG, "the model's rcut reaches past the batch's rcut + skin");
     long total = 0;
     int cellcap = 0;
     bool uniq = true;   // no list holds two images of one atom

@@ -50,22 +50,34 @@ def test_model_with_more_neighbors(cu_cfg, cu_params, precision):
     assert np.any(got["F"] != first["F"])
 
 
-def test_model_with_a_longer_cut_off(cu_cfg, cu_params):
-    import paper_2201_01446_amd as P
-    from paper_2201_01446_amd.serve import Batch
-    cells = requests()
-    base = make(P, cu_cfg)[2]
-    b = Batch(base, sum(len(x) for x, _ in cells), 2, skin=2.0)
-    cfg, prm, longer = make(P, cu_cfg, rcut=9.0, sel=300)
-    out, off = run(b, longer, cells, P.FP64), 0
-    table = oracle.Table(cfg, prm, 0.7, 0.01, 1.5, 0.1)
+def check_against_oracle(P, cfg, prm, out, cells):
+    off, table = 0, oracle.Table(cfg, prm, 0.7, 0.01, 1.5, 0.1)
     for k, (x, box) in enumerate(cells):
         ref = oracle.evaluate(cfg, prm, x, box, table=table)
         assert abs(out["E"][k] - ref["E"]) <= 1e-10 * abs(ref["E"])
         assert np.max(np.abs(out["F"][off:off + len(x)] - ref["F"])) <= 1e-10 * np.max(np.abs(ref["F"]))
         off += len(x)
+
+
+@pytest.mark.parametrize("rcut", [9.0, 10.0])   # inside the batch's reach, and at it
+def test_model_with_a_longer_cut_off(cu_cfg, rcut):
+    import paper_2201_01446_amd as P
+    from paper_2201_01446_amd.serve import Batch
+    cells = requests()
+    base = make(P, cu_cfg)[2]
+    b = Batch(base, sum(len(x) for x, _ in cells), 2, skin=2.0)
+    cfg, prm, longer = make(P, cu_cfg, rcut=rcut, sel=420)
+    check_against_oracle(P, cfg, prm, run(b, longer, cells, P.FP64), cells)
     assert b.stats()["sel_overflow"] == 0
-    for rcut in (10.0, 10.5):   # at the batch's reach, and past it
-        past = make(P, cu_cfg, rcut=rcut, sel=400)[2]
-        with pytest.raises(P.DPError, match="rcut"):
-            run(b, past, cells, P.FP64)
+    past = make(P, cu_cfg, rcut=10.5, sel=420)[2]
+    with pytest.raises(P.DPError, match="rcut"):
+        run(b, past, cells, P.FP64)
+
+
+def test_batch_without_a_skin(cu_cfg, cu_params):
+    import paper_2201_01446_amd as P
+    from paper_2201_01446_amd.serve import Batch
+    cells = requests()
+    cfg, prm, model = make(P, cu_cfg)
+    b = Batch(model, sum(len(x) for x, _ in cells), 2, skin=0.0)
+    check_against_oracle(P, cfg, prm, run(b, model, cells, P.FP64), cells)
